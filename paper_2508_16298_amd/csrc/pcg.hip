@@ -33,6 +33,7 @@
 #include <cstdlib>
 #include <cstring>
 #include "cg_common.h"
+#include "spectral.h"
 
 namespace qh {
 
@@ -82,17 +83,41 @@ __global__ void k_unit(cplx<double>* __restrict__ e, size_t n, size_t k) {
 // inverse DFT (its 1 / (L L/2) folded into H).  Same operator, far fewer
 // operations than the taps at the sizes the stencil is latency-bound at.
 // ---------------------------------------------------------------------------
-static constexpr int kSpecNA = 2 * kCapMax + 1;  // combined tau offsets at most
-static constexpr int kSpecE = 8;                // DFT outputs per thread at most (L * L/2 <= 8192)
-static constexpr int kSpecChunk = 13;           // tau offsets per load batch of the fused tau sum
+static_assert(kCapMax == kSpTau, "the tau sum's registers hold kSpTau offsets either way");
+static constexpr int kSpecMaxNK = 8192;  // momenta per parity plane at most (4096 in FP64)
+
+// Blocks of 16 DFT outputs per axis (y, x): the kernels' instantiations
+static void spec_blocks(int L, int& ny, int& nx) {
+    const int b = (L / 2 + 1 + 15) / 16;
+    ny = b <= 3 ? b : 5;
+    nx = b <= 2 ? 1 : (b <= 3 ? 2 : 3);
+}
+
+// DFT weights of n points in the fragment order of sp_tile: cos and sin of
+// 2 pi j k / n at k = 4 step + lane / 16, j = 16 block + lane % 16, both up to
+// n / 2 (zero beyond); half the cosine at the k paired with itself.
+template <typename R>
+static void spec_table(int n, int nt, R* t) {
+    const int steps = sp_steps(n);
+    for (int b = 0; b < nt; b++)
+        for (int s = 0; s < steps; s++)
+            for (int l = 0; l < 64; l++) {
+                const int k = 4 * s + l / 16, j = 16 * b + l % 16;
+                const bool on = k <= n / 2 && j <= n / 2;
+                const double a = 2 * M_PI * ((long)j * k % n) / n, w = (k == 0 || 2 * k == n) ? 0.5 : 1.0;
+                R* f = t + (size_t)((b * steps + s) * 2) * 64 + l;
+                f[0] = on ? (R)(w * std::cos(a)) : R(0);
+                f[64] = on && w == 1.0 ? (R)std::sin(a) : R(0);
+            }
+}
 
 static qedhmc_status build_spectral(qedhmc_ctx* h, const std::vector<HostTap> (&pass)[2][2]) {
     h->pc_spec_na = 0;
     const int L = h->lat.L, Lh = L / 2, nk = L * Lh;
-    if (L % 2 || h->lat.Nt <= h->pc_cap || nk > kSpecE * 1024) return QEDHMC_OK;
+    if (L % 2 || h->lat.Nt <= h->pc_cap || nk > kSpecMaxNK) return QEDHMC_OK;
     const int a0 = h->pc_pass[0].amin + h->pc_pass[1].amin, a1 = h->pc_pass[0].amax + h->pc_pass[1].amax;
     const int na = a1 - a0 + 1;
-    if (na > kSpecNA) return QEDHMC_OK;
+    if (a0 != -a1 || a1 > kSpTau) return QEDHMC_OK;
     // e^{+2 pi i j / n} by integer index, so every phase is one table entry
     auto unit = [](int n) {
         std::vector<cplx<double>> t(n);
@@ -137,23 +162,36 @@ static qedhmc_status build_spectral(qedhmc_ctx* h, const std::vector<HostTap> (&
                         }
                 }
         }
+    // only the offsets a >= 0 are kept (H(k, -a) = H(k, a)^dagger), as
+    // [a][row][k] pairs of a row's two entries, normalised for the DFT pair
     const double norm = 1.0 / nk;
-    for (auto& e : H) e = mk<double>(e.re * norm, e.im * norm);
-    // forward twiddles e^{-2 pi i j / n}: L/2 for x, then L for y
-    std::vector<cplx<double>> tw(Lh + L);
-    for (int j = 0; j < Lh; j++) tw[j] = mk<double>(ex[j].re, -ex[j].im);
-    for (int j = 0; j < L; j++) tw[Lh + j] = mk<double>(ey[j].re, -ey[j].im);
-    std::vector<cplx<float>> H32(H.size()), tw32(tw.size());
-    for (size_t i = 0; i < H.size(); i++) H32[i] = mk<float>((float)H[i].re, (float)H[i].im);
-    for (size_t i = 0; i < tw.size(); i++) tw32[i] = mk<float>((float)tw[i].re, (float)tw[i].im);
-    QH_HIP(hipMalloc(&h->pc_spec64, H.size() * sizeof(cplx<double>)));
-    QH_HIP(hipMalloc(&h->pc_spec32, H.size() * sizeof(cplx<float>)));
-    QH_HIP(hipMalloc(&h->pc_tw64, tw.size() * sizeof(cplx<double>)));
-    QH_HIP(hipMalloc(&h->pc_tw32, tw.size() * sizeof(cplx<float>)));
-    QH_HIP(hipMemcpyAsync(h->pc_spec64, H.data(), H.size() * sizeof(cplx<double>), hipMemcpyHostToDevice, h->stream));
+    std::vector<cplx<double>> Hh((size_t)(a1 + 1) * 4 * nk);
+    for (int a = 0; a <= a1; a++)
+        for (int row = 0; row < 2; row++)
+            for (int k = 0; k < nk; k++)
+                for (int c = 0; c < 2; c++) {
+                    const cplx<double> e = H[((size_t)(a - a0) * 4 + 2 * row + c) * nk + k];
+                    Hh[((size_t)(2 * a + row) * nk + k) * 2 + c] = mk<double>(e.re * norm, e.im * norm);
+                }
+    int ny, nx;
+    spec_blocks(L, ny, nx);
+    const size_t ntab = sp_table(L, ny) + sp_table(Lh, nx);
+    std::vector<double> tw(ntab);
+    std::vector<float> tw32(ntab);
+    spec_table<double>(L, ny, tw.data());
+    spec_table<double>(Lh, nx, tw.data() + sp_table(L, ny));
+    spec_table<float>(L, ny, tw32.data());
+    spec_table<float>(Lh, nx, tw32.data() + sp_table(L, ny));
+    std::vector<cplx<float>> H32(Hh.size());
+    for (size_t i = 0; i < Hh.size(); i++) H32[i] = mk<float>((float)Hh[i].re, (float)Hh[i].im);
+    QH_HIP(hipMalloc(&h->pc_spec64, Hh.size() * sizeof(cplx<double>)));
+    QH_HIP(hipMalloc(&h->pc_spec32, H32.size() * sizeof(cplx<float>)));
+    QH_HIP(hipMalloc(&h->pc_tw64, tw.size() * sizeof(double)));
+    QH_HIP(hipMalloc(&h->pc_tw32, tw32.size() * sizeof(float)));
+    QH_HIP(hipMemcpyAsync(h->pc_spec64, Hh.data(), Hh.size() * sizeof(cplx<double>), hipMemcpyHostToDevice, h->stream));
     QH_HIP(hipMemcpyAsync(h->pc_spec32, H32.data(), H32.size() * sizeof(cplx<float>), hipMemcpyHostToDevice, h->stream));
-    QH_HIP(hipMemcpyAsync(h->pc_tw64, tw.data(), tw.size() * sizeof(cplx<double>), hipMemcpyHostToDevice, h->stream));
-    QH_HIP(hipMemcpyAsync(h->pc_tw32, tw32.data(), tw32.size() * sizeof(cplx<float>), hipMemcpyHostToDevice, h->stream));
+    QH_HIP(hipMemcpyAsync(h->pc_tw64, tw.data(), tw.size() * sizeof(double), hipMemcpyHostToDevice, h->stream));
+    QH_HIP(hipMemcpyAsync(h->pc_tw32, tw32.data(), tw32.size() * sizeof(float), hipMemcpyHostToDevice, h->stream));
     // the host vectors die at return: wait for the copies
     QH_HIP(hipStreamSynchronize(h->stream));
     h->pc_spec_a0 = a0;
@@ -840,35 +878,9 @@ static qedhmc_status launch_pc(qedhmc_ctx* h, int ps, const cplx<R>* in, cplx<R>
 }
 
 // ---------------------------------------------------------------------------
-// Spectral application (the tables of build_spectral).  Momentum-space
-// vectors use the memory of a site vector: slice tau holds the even plane
-// [ny][nx] and then the odd one.
+// Spectral application (the tables of build_spectral; spectral.h).  Momentum
+// vectors use the memory of a site vector, [tau][ny][nx][parity].
 // ---------------------------------------------------------------------------
-// acc += m v (complex), four FMAs
-template <typename R>
-__device__ __forceinline__ void v_cmac(cplx<R>& acc, cplx<R> m, cplx<R> v) {
-    acc.re = fma(m.re, v.re, acc.re);
-    acc.re = fma(-m.im, v.im, acc.re);
-    acc.im = fma(m.re, v.im, acc.im);
-    acc.im = fma(m.im, v.re, acc.im);
-}
-
-struct PcSpecGeo {
-    int L, Lh, Nt, Vs, nk, a0, na;
-};
-
-// (slice, parity) of a workgroup of the per-plane spectral kernels: both
-// planes of a slice on the XCD that slice_of_block gives the slice (so
-// momentum planes written and read by consecutive launches stay in that
-// XCD's L2); spec_grid(Nt) workgroups, the surplus ones get -1
-__host__ __device__ __forceinline__ int spec_grid(int Nt) { return 16 * ((Nt + 7) / 8); }
-__device__ __forceinline__ int spec_slice_of_block(int b, int Nt, int& p) {
-    const int per = (Nt + 7) >> 3, j = b >> 3;
-    const int tau = (b & 7) * per + (j >> 1);
-    p = j & 1;
-    return tau < Nt ? tau : -1;
-}
-
 // Workgroup size cap of the spectral kernels: FP64 takes at most 512
 // threads (at 1024 its registers spill)
 template <typename R>
@@ -876,265 +888,201 @@ constexpr int spec_max_threads() {
     return sizeof(R) == 8 ? 512 : 1024;
 }
 
-// 2D DFT of nplanes parity planes held in LDS (buf[plane][row][column],
-// Lh columns), by the whole workgroup: a direct DFT over the column index
-// (L/2 points) for every row, written back to buf, then one over the row
-// index (L points) for every column, whose results go to
-// emit(plane, kr * Lh + col, value).  Twiddles twx[Lh], twy[L] hold
-// e^{-2 pi i j / n} (forward) or their conjugates (inverse).  Outputs per
-// thread: at most kSpecE (nplanes * L * L/2 <= kSpecE * blockDim.x).
-template <typename R, typename Emit>
-__device__ __forceinline__ void dft_planes(cplx<R>* buf, const cplx<R>* twx, const cplx<R>* twy, int L, int Lh,
-                                           int nplanes, Emit emit) {
-    const int n = L * Lh, tot = nplanes * n;
-    cplx<R> acc[kSpecE];
-#pragma unroll
-    for (int j = 0; j < kSpecE; j++) {
-        const int ea = (int)threadIdx.x + j * (int)blockDim.x;
-        if (ea < tot) {
-            const int pl = ea / n, e = ea - pl * n;
-            const int row = e / Lh, kc = e - row * Lh;
-            const cplx<R>* src = buf + pl * n + row * Lh;
-            R ar = 0, ai = 0;
-            int idx = 0;
-            for (int m = 0; m < Lh; m++) {
-                const cplx<R> v = src[m], t = twx[idx];
-                ar = fma(v.re, t.re, ar);
-                ar = fma(-v.im, t.im, ar);
-                ai = fma(v.re, t.im, ai);
-                ai = fma(v.im, t.re, ai);
-                idx += kc;
-                idx = idx >= Lh ? idx - Lh : idx;
-            }
-            acc[j] = mk<R>(ar, ai);
-        }
+// Site vector -> momentum planes, a slice per workgroup.  With the transform
+// on the matrix cores (spectral.h) against direct sums through LDS, which were
+// bound by LDS reads: L = 24 5.3 -> 4.6 us, L = 66, N_tau = 660 83 -> 27 us
+// (46 MB, 1.7 TB/s; the inverse the same).  What is left at L = 66 is the
+// chain load, y products, barrier, x products, store of each workgroup, with
+// two workgroups in a compute unit, and 7 us of FP32 products.
+template <typename R, int NY, int NX, bool TL>
+__global__ __launch_bounds__(spec_max_threads<R>()) void k_pcs_fwd(PcSpecGeo g, const R* __restrict__ tab,
+                                                                  const cplx<R>* __restrict__ in,
+                                                                  cplx<R>* __restrict__ out,
+                                                                  const double* __restrict__ stop) {
+    if (stop && *stop != 0.0) return;
+    extern __shared__ __align__(32) unsigned char smem[];
+    R* V = reinterpret_cast<R*>(smem);
+    const int tau = slice_of_block(blockIdx.x, g.Nt);
+    if (tau < 0) return;
+    const R* tb = sp_tables<R, TL>(tab, V + g.L * g.ld, g);
+    const cplx<R>* src = in + (size_t)tau * g.Vs;
+    for (int e = threadIdx.x; e < g.Vs; e += blockDim.x) {
+        const int y = e / g.L;
+        *reinterpret_cast<cplx<R>*>(V + y * g.ld + 2 * (e - y * g.L)) = src[e];
     }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kSpecE; j++) {
-        const int ea = (int)threadIdx.x + j * (int)blockDim.x;
-        if (ea < tot) buf[ea] = acc[j];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kSpecE; j++) {
-        const int ea = (int)threadIdx.x + j * (int)blockDim.x;
-        if (ea < tot) {
-            const int pl = ea / n, e = ea - pl * n;
-            const int kr = e / Lh, col = e - kr * Lh;
-            const cplx<R>* src = buf + pl * n + col;
-            R ar = 0, ai = 0;
-            int idx = 0;
-            for (int r = 0; r < L; r++) {
-                const cplx<R> v = src[r * Lh], t = twy[idx];
-                ar = fma(v.re, t.re, ar);
-                ar = fma(-v.im, t.im, ar);
-                ai = fma(v.re, t.im, ai);
-                ai = fma(v.im, t.re, ai);
-                idx += kr;
-                idx = idx >= L ? idx - L : idx;
-            }
-            emit(pl, e, mk<R>(ar, ai));
-        }
-    }
+    sp_forward<R, NY, NX>(V, g, tb, out + (size_t)tau * g.Vs);
 }
 
-// twiddles of both axes into LDS (twx then twy, contiguous), conjugated for
-// the inverse
-template <typename R, bool INV>
-__device__ __forceinline__ void load_twiddles(const cplx<R>* __restrict__ tw, cplx<R>* twx, int n) {
-    for (int j = threadIdx.x; j < n; j += blockDim.x) {
-        const cplx<R> t = tw[j];
-        twx[j] = INV ? mk<R>(t.re, -t.im) : t;
+// Momentum planes -> site vector, a slice per workgroup.
+template <typename R, int NY, int NX, bool TL>
+__global__ __launch_bounds__(spec_max_threads<R>()) void k_pcs_inv(PcSpecGeo g, const R* __restrict__ tab,
+                                                                  const cplx<R>* __restrict__ in,
+                                                                  cplx<R>* __restrict__ out,
+                                                                  const double* __restrict__ stop) {
+    if (stop && *stop != 0.0) return;
+    extern __shared__ __align__(32) unsigned char smem[];
+    R* V = reinterpret_cast<R*>(smem);
+    const int tau = slice_of_block(blockIdx.x, g.Nt);
+    if (tau < 0) return;
+    const R* tb = sp_tables<R, TL>(tab, V + g.L * g.ld, g);
+    const cpair<R>* src = reinterpret_cast<const cpair<R>*>(in + (size_t)tau * g.Vs);
+    for (int k = threadIdx.x; k < g.nk; k += blockDim.x) {
+        const int y = k / g.Lh;
+        *reinterpret_cast<cpair<R>*>(V + y * g.ld + 4 * (k - y * g.Lh)) = src[k];
     }
+    sp_inverse<R, NY, NX>(V, g, tb, out + (size_t)tau * g.Vs);
 }
 
-// Site vector <-> momentum planes, a workgroup per (slice, parity).
-// Forward: in a site vector, out momentum planes (e^{-i k.r}); INV: the
-// reverse with e^{+i k.r} (the normalisation sits in H).
-template <typename R, bool INV>
-__global__ __launch_bounds__(spec_max_threads<R>()) void k_pcs_dft(PcSpecGeo g, const cplx<R>* __restrict__ tw,
+// slice tau + a (|a| < N_tau) in [0, N_tau) and its sign (-1 where it wraps)
+template <typename R>
+__device__ __forceinline__ int sp_slice(int s, int Nt, R& sign) {
+    sign = (s < 0 || s >= Nt) ? R(-1) : R(1);
+    return s < 0 ? s + Nt : (s >= Nt ? s - Nt : s);
+}
+
+// z^(k, tau) = sum_a sign H(k, a) v^(k, tau + a): a thread per (momentum, run
+// of T slices) holds the T + 2 kSpTau input slices it needs in registers and
+// reads each block of H once for the run.  Bound by the FMAs (400 per
+// momentum and slice: 15 us of the 32 at L = 66, N_tau = 660).
+template <typename R, int T>
+__global__ __launch_bounds__(256) void k_pcs_tsum(PcSpecGeo g, const cpair<R>* __restrict__ H,
                                                   const cplx<R>* __restrict__ in, cplx<R>* __restrict__ out,
                                                   const double* __restrict__ stop) {
     if (stop && *stop != 0.0) return;
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int L = g.L, Lh = g.Lh, n = g.nk;
-    cplx<R>* buf = reinterpret_cast<cplx<R>*>(smem);  // [row][column]
-    cplx<R>* twx = buf + n;                           // [Lh], then twy [L]
-    int p;
-    const int tau = spec_slice_of_block(blockIdx.x, g.Nt, p);
-    if (tau < 0) return;
-    const size_t sbase = (size_t)tau * g.Vs;
-    load_twiddles<R, INV>(tw, twx, Lh + L);
-    for (int e = threadIdx.x; e < n; e += blockDim.x) {
-        const int row = e / Lh, col = e - row * Lh;
-        buf[e] = INV ? in[sbase + (size_t)p * n + e] : in[sbase + (size_t)row * L + 2 * col + p];
-    }
-    __syncthreads();
-    dft_planes<R>(buf, twx, twx + Lh, L, Lh, 1, [&](int, int e, cplx<R> v) {
-        if (INV) {
-            const int y = e / Lh, m = e - y * Lh;
-            out[sbase + (size_t)y * L + 2 * m + p] = v;
-        } else {
-            out[sbase + (size_t)p * n + e] = v;
-        }
-    });
-}
-
-// input slice s of the banded tau sum: its index in [0, N_tau) and the sign
-// (-1 per wrap of the antiperiodic direction)
-__device__ __forceinline__ int wrap_slice(int s, int Nt, int& flip) {
-    const int q = s >= 0 ? s / Nt : -((-s + Nt - 1) / Nt);  // floor(s / Nt)
-    flip = q & 1;
-    return s - q * Nt;
-}
-
-// z^(k, tau) = sum_a sign H(k, a) v^(k, tau + a) on momentum planes: a thread
-// per (momentum, run of TC slices) holds the TC + na - 1 input slices it
-// needs in registers.  H is [a][entry][k] (coalesced across k).
-template <typename R, int TC>
-__global__ __launch_bounds__(256) void k_pcs_tconv(PcSpecGeo g, const cplx<R>* __restrict__ H,
-                                                   const cplx<R>* __restrict__ in, cplx<R>* __restrict__ out,
-                                                   const double* __restrict__ stop) {
-    if (stop && *stop != 0.0) return;
-    const int nk = g.nk;
-    const int nrun = (g.Nt + TC - 1) / TC;
+    const int nk = g.nk, nrun = (g.Nt + T - 1) / T;
     const int gid = blockIdx.x * blockDim.x + threadIdx.x;
     if (gid >= nk * nrun) return;
-    const int k = gid % nk, tau0 = (gid / nk) * TC;
-    constexpr int NW = TC + kSpecNA - 1;
-    // window slices past the last one needed read slice 0 with sign 0: no
-    // branches, every load in flight together
-    cplx<R> v0[NW], v1[NW];
-    R sgw[NW];
+    const int k = gid % nk, tau0 = (gid / nk) * T;
+    constexpr int NW = T + 2 * kSpTau;
+    cpair<R> v[NW];
+    // window slices past the last one needed read the run's first slice and
+    // are not used: every load in flight together
 #pragma unroll
     for (int j = 0; j < NW; j++) {
-        int flip = 0;
-        const bool on = j < TC + g.na - 1;
-        const int sr = on ? wrap_slice(tau0 + g.a0 + j, g.Nt, flip) : 0;
-        sgw[j] = on ? (flip ? R(-1) : R(1)) : R(0);
-        const cplx<R>* src = in + (size_t)sr * g.Vs + k;
-        v0[j] = src[0];
-        v1[j] = src[nk];
+        const int a = j - kSpTau;
+        R sg = R(1);
+        const bool on = a >= -g.reach && a < T + g.reach && tau0 + a < g.Nt + g.reach;
+        const int s = on ? sp_slice<R>(tau0 + a, g.Nt, sg) : tau0;
+        v[j] = reinterpret_cast<const cpair<R>*>(in + (size_t)s * g.Vs)[k];
+        v[j] = sp_signed(sg, v[j]);
     }
+    // the far offsets first: H falls off with |a|, so the running sums stay
+    // small for most of their roundings
+    cpair<R> z[T];
 #pragma unroll
-    for (int j = 0; j < NW; j++) {
-        v0[j] = mk<R>(sgw[j] * v0[j].re, sgw[j] * v0[j].im);
-        v1[j] = mk<R>(sgw[j] * v1[j].re, sgw[j] * v1[j].im);
-    }
-    cplx<R> z0[TC], z1[TC];
+    for (int t = 0; t < T; t++) z[t] = {mk<R>(0, 0), mk<R>(0, 0)};
 #pragma unroll
-    for (int t = 0; t < TC; t++) z0[t] = z1[t] = mk<R>(R(0), R(0));
-    // (guards rather than an early exit keep every window index a constant,
-    // so the window stays in registers)
+    for (int a = kSpTau; a >= 1; a--)
+        if (a <= g.reach) {
+            const cpair<R> h0 = H[(size_t)(2 * a) * nk + k], h1 = H[(size_t)(2 * a + 1) * nk + k];
 #pragma unroll
-    for (int ia = 0; ia < kSpecNA; ia++) {
-        if (ia < g.na) {
-            const cplx<R>* hp = H + (size_t)ia * 4 * nk + k;
-            const cplx<R> h00 = hp[0], h01 = hp[nk], h10 = hp[2 * nk], h11 = hp[3 * nk];
-#pragma unroll
-            for (int t = 0; t < TC; t++) {
-                v_cmac(z0[t], h00, v0[t + ia]);
-                v_cmac(z0[t], h01, v1[t + ia]);
-                v_cmac(z1[t], h10, v0[t + ia]);
-                v_cmac(z1[t], h11, v1[t + ia]);
+            for (int t = 0; t < T; t++) {
+                sp_up<R>(z[t], h0, h1, v[t + kSpTau + a]);
+                sp_down<R>(z[t], h0, h1, v[t + kSpTau - a]);
             }
         }
+    {
+        const cpair<R> h0 = H[k], h1 = H[nk + k];
+#pragma unroll
+        for (int t = 0; t < T; t++) sp_up<R>(z[t], h0, h1, v[t + kSpTau]);
     }
 #pragma unroll
-    for (int t = 0; t < TC; t++)
-        if (tau0 + t < g.Nt) {
-            cplx<R>* dst = out + (size_t)(tau0 + t) * g.Vs + k;
-            dst[0] = z0[t];
-            dst[nk] = z1[t];
-        }
+    for (int t = 0; t < T; t++)
+        if (tau0 + t < g.Nt) reinterpret_cast<cpair<R>*>(out + (size_t)(tau0 + t) * g.Vs)[k] = z[t];
 }
 
-// The tau sum and the inverse DFT in one launch, a workgroup per (slice,
-// parity): the plane z^_p(tau) is formed in LDS from the na input slices
-// (read through the L2; used where a slice is small), then transformed back.
-template <typename R>
-__global__ __launch_bounds__(spec_max_threads<R>()) void k_pcs_tconv_idft(PcSpecGeo g, const cplx<R>* __restrict__ H,
-                                                         const cplx<R>* __restrict__ tw,
-                                                         const cplx<R>* __restrict__ in, cplx<R>* __restrict__ out,
-                                                         const double* __restrict__ stop) {
+// The tau sum and the inverse DFT in one launch, a slice per workgroup: both
+// parities of a momentum in one thread (each input value and each block of H
+// is read once per slice, H once for the two slices it serves), straight into
+// the LDS image that is transformed back.  Used where a slice is small.  A
+// workgroup per (slice, parity) reading all 25 blocks of H took 14.3 us per
+// launch at L = 24, N_tau = 240 (110 MB of L2 reads); this one 9.2 us (56 MB),
+// of which about 1.6 us are the launch.
+template <typename R, int NY, int NX, bool TL>
+__global__ __launch_bounds__(512) void k_pcs_tsum_inv(PcSpecGeo g, const cpair<R>* __restrict__ H,
+                                                      const R* __restrict__ tab, const cplx<R>* __restrict__ in,
+                                                      cplx<R>* __restrict__ out, const double* __restrict__ stop) {
     if (stop && *stop != 0.0) return;
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int L = g.L, Lh = g.Lh, n = g.nk;
-    cplx<R>* buf = reinterpret_cast<cplx<R>*>(smem);
-    cplx<R>* twx = buf + n;
-    int p;
-    const int tau = spec_slice_of_block(blockIdx.x, g.Nt, p);
+    extern __shared__ __align__(32) unsigned char smem[];
+    R* V = reinterpret_cast<R*>(smem);
+    const int tau = slice_of_block(blockIdx.x, g.Nt), nk = g.nk;
     if (tau < 0) return;
-    const int ntw = Lh + L;  // <= blockDim.x (spec_fits)
-    const cplx<R> twv = (int)threadIdx.x < ntw ? tw[threadIdx.x] : mk<R>(R(0), R(0));
-    // the tau offsets in chunks of kSpecChunk: per chunk, the slice offset,
-    // H offset and sign of every offset (offsets past na read valid entries
-    // with sign 0, so every load is unconditional and a chunk's loads are in
-    // flight together)
-    constexpr int CH = kSpecChunk;
-    const int e0 = threadIdx.x;
-    if (e0 < ntw) {
-        twx[e0] = mk<R>(twv.re, -twv.im);  // inverse twiddles
-    }
-    for (int e = e0; e < n; e += blockDim.x) {
-        cplx<R> z = mk<R>(R(0), R(0));
-        for (int c0 = 0; c0 < g.na; c0 += CH) {
-            cplx<R> h0[CH], h1[CH], v0[CH], v1[CH];
-            R sgn[CH];
+    const R* tb = sp_tables<R, TL>(tab, V + g.L * g.ld, g);
+    constexpr int CH = sizeof(R) == 8 ? 3 : 6;  // offsets per load batch
+    static_assert(kSpTau % CH == 0, "whole batches");
+    for (int k = threadIdx.x; k < nk; k += blockDim.x) {
+        cpair<R> z{mk<R>(0, 0), mk<R>(0, 0)};
+        const cpair<R> hc0 = H[k], hc1 = H[nk + k];
+        const cpair<R> vc = reinterpret_cast<const cpair<R>*>(in + (size_t)tau * g.Vs)[k];
+        // the far offsets first (as k_pcs_tsum)
+#pragma unroll
+        for (int c = kSpTau - CH + 1; c >= 1; c -= CH) {
+            cpair<R> h0[CH], h1[CH], vu[CH], vd[CH];
+            R su[CH], sd[CH];
 #pragma unroll
             for (int i = 0; i < CH; i++) {
-                const int ia = c0 + i;
-                int flip = 0;
-                const bool on = ia < g.na;
-                const size_t so = on ? (size_t)wrap_slice(tau + g.a0 + ia, g.Nt, flip) * g.Vs : 0;
-                const size_t ho = ((size_t)(on ? ia : 0) * 4 + 2 * p) * n;
-                sgn[i] = on ? (flip ? R(-1) : R(1)) : R(0);
-                h0[i] = H[ho + e];
-                h1[i] = H[ho + n + e];
-                v0[i] = in[so + e];
-                v1[i] = in[so + n + e];
+                // offsets past the reach read valid entries with sign 0
+                const int a = c + i <= g.reach ? c + i : 0;
+                const int u = sp_slice<R>(tau + a, g.Nt, su[i]), d = sp_slice<R>(tau - a, g.Nt, sd[i]);
+                if (a == 0) su[i] = sd[i] = R(0);
+                h0[i] = H[(size_t)(2 * a) * nk + k];
+                h1[i] = H[(size_t)(2 * a + 1) * nk + k];
+                vu[i] = reinterpret_cast<const cpair<R>*>(in + (size_t)u * g.Vs)[k];
+                vd[i] = reinterpret_cast<const cpair<R>*>(in + (size_t)d * g.Vs)[k];
             }
 #pragma unroll
-            for (int i = 0; i < CH; i++) {
-                cplx<R> t = mk<R>(R(0), R(0));
-                v_cmac(t, h0[i], v0[i]);
-                v_cmac(t, h1[i], v1[i]);
-                z.re = fma(sgn[i], t.re, z.re);
-                z.im = fma(sgn[i], t.im, z.im);
+            for (int i = CH - 1; i >= 0; i--) {
+                sp_up<R>(z, h0[i], h1[i], sp_signed(su[i], vu[i]));
+                sp_down<R>(z, h0[i], h1[i], sp_signed(sd[i], vd[i]));
             }
         }
-        buf[e] = z;
+        sp_up<R>(z, hc0, hc1, vc);
+        const int y = k / g.Lh;
+        *reinterpret_cast<cpair<R>*>(V + y * g.ld + 4 * (k - y * g.Lh)) = z;
     }
-    __syncthreads();
-    const size_t sbase = (size_t)tau * g.Vs;
-    dft_planes<R>(buf, twx, twx + Lh, L, Lh, 1, [&](int, int e, cplx<R> v) {
-        const int y = e / Lh, m = e - y * Lh;
-        out[sbase + (size_t)y * L + 2 * m + p] = v;
-    });
+    sp_inverse<R, NY, NX>(V, g, tb, out + (size_t)tau * g.Vs);
+}
+
+template <typename R>
+static PcSpecGeo spec_geo(const qedhmc_ctx* h) {
+    const Lat& lt = h->lat;
+    PcSpecGeo g{lt.L, lt.L / 2, lt.Nt, lt.Vs, lt.L * (lt.L / 2), -h->pc_spec_a0, sp_ld(lt.L), 0, 0};
+    int ny, nx;
+    spec_blocks(lt.L, ny, nx);
+    g.ty = sp_table(g.L, ny);
+    g.tx = sp_table(g.Lh, nx);
+    return g;
+}
+
+// LDS of a transform: the slice image, and the tables as long as two
+// workgroups then fit a compute unit (tl)
+template <typename R>
+static size_t spec_lds(const PcSpecGeo& g, bool& tl) {
+    const size_t image = (size_t)g.L * g.ld * sizeof(R), tabs = (size_t)(g.ty + g.tx) * sizeof(R);
+    tl = image + tabs <= 79 * 1024;
+    return image + (tl ? tabs : 0);
 }
 
 // whether apply_P_t takes the spectral form: built (L even, N_tau above the
-// tau reach of a pass, L * L/2 <= 8192), a plane fits one workgroup of the
-// precision, and not overridden by QEDHMC_PC_KERNEL=roll|stream (read per
-// call)
-template <typename R>
-static bool spec_fits(const qedhmc_ctx* h, int nplanes, int& threads, size_t& lds);
-
+// tau reach of a pass, L * L/2 <= 8192), at most 4096 momenta per plane in
+// FP64 (whose slice image then fits the LDS), and not overridden by
+// QEDHMC_PC_KERNEL=roll|stream (read per call)
 template <typename R>
 static bool use_spectral(const qedhmc_ctx* h) {
     if (h->pc_spec_na <= 0) return false;
-    int threads;
-    size_t lds;
-    if (!spec_fits<R>(h, 1, threads, lds)) return false;
+    const PcSpecGeo g = spec_geo<R>(h);
+    bool tl;
+    // (room for the update kernel's static reduction scratch)
+    if (g.nk > kSpecMaxNK / (sizeof(R) == 8 ? 2 : 1) || spec_lds<R>(g, tl) + 2048 > h->max_lds) return false;
     const char* ek = std::getenv("QEDHMC_PC_KERNEL");
     return !ek || !*ek || std::strcmp(ek, "spectral") == 0;
 }
 
 // the tau sum fused into the inverse DFT up to this many momenta per plane
-// (each workgroup then reads na input planes of both parities through the
-// L2); QEDHMC_PC_FUSE=0|1 (read per call) forces either form
-static constexpr int kSpecFuseNK = 1152;  // L = 48
+// (each workgroup then reads H and 2 reach + 1 input slices through the L2):
+// P in FP32, fused / separate, L = 48 35.0 / 43.7 us, L = 56 45.4 / 47.6 us,
+// L = 66 99.4 / 81.2 us.  QEDHMC_PC_FUSE=0|1 (read per call) forces either form
+static constexpr int kSpecFuseNK = 1682;  // L = 58
 
 static bool spec_fused(const qedhmc_ctx* h) {
     const char* ef = std::getenv("QEDHMC_PC_FUSE");
@@ -1143,45 +1091,41 @@ static bool spec_fused(const qedhmc_ctx* h) {
 }
 
 template <typename R>
-static PcSpecGeo spec_geo(const qedhmc_ctx* h) {
-    const Lat& lt = h->lat;
-    return PcSpecGeo{lt.L, lt.L / 2, lt.Nt, lt.Vs, lt.L * (lt.L / 2), h->pc_spec_a0, h->pc_spec_na};
+static const R* spec_tab(const qedhmc_ctx* h) {
+    return (const R*)(sizeof(R) == 8 ? h->pc_tw64 : h->pc_tw32);
 }
 
 template <typename R>
-static const cplx<R>* spec_tw(const qedhmc_ctx* h) {
-    return (const cplx<R>*)(sizeof(R) == 8 ? h->pc_tw64 : h->pc_tw32);
+static const cpair<R>* spec_H(const qedhmc_ctx* h) {
+    return (const cpair<R>*)(sizeof(R) == 8 ? h->pc_spec64 : h->pc_spec32);
 }
 
-template <typename R>
-static const cplx<R>* spec_H(const qedhmc_ctx* h) {
-    return (const cplx<R>*)(sizeof(R) == 8 ? h->pc_spec64 : h->pc_spec32);
+// f.operator()<NY, NX, TL>() of this lattice's transform
+template <typename R, typename F>
+static qedhmc_status with_spec(const PcSpecGeo& g, F&& f) {
+    bool tl;
+    (void)spec_lds<R>(g, tl);
+    int ny, nx;
+    spec_blocks(g.L, ny, nx);
+    if (ny == 1) return f.template operator()<1, 1, true>();
+    if (ny == 2) return tl ? f.template operator()<2, 1, true>() : f.template operator()<2, 1, false>();
+    if (ny == 3) return tl ? f.template operator()<3, 2, true>() : f.template operator()<3, 2, false>();
+    if constexpr (sizeof(R) == 4) return f.template operator()<5, 3, false>();
+    set_error("paper preconditioner: the spectral plan does not fit one workgroup");
+    return QEDHMC_EUNSUPPORTED;
 }
 
-// threads of a workgroup transforming nplanes planes (kSpecE outputs each at
-// most) and its dynamic LDS; EUNSUPPORTED if the plan does not fit
-template <typename R>
-static bool spec_fits(const qedhmc_ctx* h, int nplanes, int& threads, size_t& lds) {
-    const int L = h->lat.L, tot = nplanes * L * (L / 2);
-    threads = std::min(spec_max_threads<R>(), (tot + 63) / 64 * 64);
-    lds = (size_t)(tot + L / 2 + L) * sizeof(cplx<R>);
-    // (room for the update kernel's static reduction scratch; one thread per
-    // twiddle)
-    return (tot + threads - 1) / threads <= kSpecE && lds + 2048 <= h->max_lds && L / 2 + L <= threads;
+// threads of a transform's workgroup: a wavefront per 16 columns of reals
+// (the y axis' share of one turn), at least enough to load n elements a few
+// at a time
+static int spec_threads(const PcSpecGeo& g, int n, int most) {
+    const int t = std::max(64 * ((2 * g.L + 15) / 16), (n + 63) / 64 * 64);
+    return std::min(t, most);
 }
 
-template <typename R>
-static qedhmc_status spec_plan(qedhmc_ctx* h, int nplanes, int& threads, size_t& lds) {
-    if (!spec_fits<R>(h, nplanes, threads, lds)) {
-        set_error("paper preconditioner: the spectral plan does not fit one workgroup");
-        return QEDHMC_EUNSUPPORTED;
-    }
-    return QEDHMC_OK;
-}
-
-// where the forward transform of r should land for launch_pcs_rest(z, tmp):
-// tmp when the rest is fused (it reads neighbouring slices and writes z),
-// z otherwise
+// where the forward transform of r should land for launch_pcs_rest(m0, z,
+// m1) of the solver's buffers: tmp when the rest is fused (it reads
+// neighbouring slices and writes z), z otherwise
 template <typename R>
 static cplx<R>* spec_vhat(const qedhmc_ctx* h, cplx<R>* z, cplx<R>* tmp) {
     return spec_fused(h) ? tmp : z;
@@ -1189,66 +1133,78 @@ static cplx<R>* spec_vhat(const qedhmc_ctx* h, cplx<R>* z, cplx<R>* tmp) {
 
 template <typename R>
 static qedhmc_status launch_pcs_fwd(qedhmc_ctx* h, const cplx<R>* r, cplx<R>* vhat, const double* stop) {
-    int threads;
-    size_t lds;
-    QH_TRY(spec_plan<R>(h, 1, threads, lds));
-    if (lds > 65536) QH_TRY(allow_lds((const void*)k_pcs_dft<R, false>, h->max_lds));
-    hipLaunchKernelGGL((k_pcs_dft<R, false>), dim3(spec_grid(h->lat.Nt)), dim3(threads), lds, h->stream,
-                       spec_geo<R>(h), spec_tw<R>(h), r, vhat, stop);
-    QH_HIP(hipGetLastError());
-    return QEDHMC_OK;
-}
-
-// z = P r from vhat = the forward transform of r (at spec_vhat(z, tmp))
-template <typename R>
-static qedhmc_status launch_pcs_rest(qedhmc_ctx* h, const cplx<R>* vhat, cplx<R>* z, cplx<R>* tmp,
-                                     const double* stop) {
     const PcSpecGeo g = spec_geo<R>(h);
-    int threads;
-    size_t lds;
-    QH_TRY(spec_plan<R>(h, 1, threads, lds));
-    const dim3 dgrid(spec_grid(g.Nt));
-    if (spec_fused(h)) {
-        if (lds > 65536) QH_TRY(allow_lds((const void*)k_pcs_tconv_idft<R>, h->max_lds));
-        hipEvent_t e0, e1;
-        if (prof_sample(h, sizeof(R) == 4 ? QEDHMC_K_PC_SPEC_FP32 : QEDHMC_K_PC_SPEC_FP64, e0, e1))
-            hipExtLaunchKernelGGL(k_pcs_tconv_idft<R>, dgrid, dim3(threads), lds, h->stream, e0, e1, 0, g,
-                                  spec_H<R>(h), spec_tw<R>(h), vhat, z, stop);
-        else
-            hipLaunchKernelGGL(k_pcs_tconv_idft<R>, dgrid, dim3(threads), lds, h->stream, g, spec_H<R>(h),
-                               spec_tw<R>(h), vhat, z, stop);
+    return with_spec<R>(g, [&]<int NY, int NX, bool TL>() -> qedhmc_status {
+        bool tl;
+        const size_t lds = spec_lds<R>(g, tl);
+        if (lds > 65536) QH_TRY(allow_lds((const void*)k_pcs_fwd<R, NY, NX, TL>, h->max_lds));
+        hipLaunchKernelGGL((k_pcs_fwd<R, NY, NX, TL>), dim3(slice_grid(g.Nt)),
+                           dim3(spec_threads(g, g.Vs / 2, spec_max_threads<R>())), lds, h->stream, g, spec_tab<R>(h),
+                           r, vhat, stop);
         QH_HIP(hipGetLastError());
         return QEDHMC_OK;
-    }
-    // longer runs once there are enough threads without them
-    if (sizeof(R) == 4 && (size_t)g.nk * g.Nt >= ((size_t)1 << 20)) {
-        const int nth = g.nk * ((g.Nt + 7) / 8);
-        hipLaunchKernelGGL((k_pcs_tconv<R, 8>), dim3((nth + 255) / 256), dim3(256), 0, h->stream, g, spec_H<R>(h),
-                           vhat, tmp, stop);
-    } else {
-        const int nth = g.nk * ((g.Nt + 3) / 4);
-        hipLaunchKernelGGL((k_pcs_tconv<R, 4>), dim3((nth + 255) / 256), dim3(256), 0, h->stream, g, spec_H<R>(h),
-                           vhat, tmp, stop);
-    }
-    QH_HIP(hipGetLastError());
-    if (lds > 65536) QH_TRY(allow_lds((const void*)k_pcs_dft<R, true>, h->max_lds));
-    hipLaunchKernelGGL((k_pcs_dft<R, true>), dgrid, dim3(threads), lds, h->stream, g, spec_tw<R>(h),
-                       (const cplx<R>*)tmp, z, stop);
-    QH_HIP(hipGetLastError());
-    return QEDHMC_OK;
+    });
 }
 
-// z = G^dag (G r); tmp: scratch vector of the same precision (r, z and tmp
-// distinct)
+// z = P r from vhat = the forward transform of r; m1: momentum scratch (not
+// used when the tau sum is fused), may be neither vhat nor z
 template <typename R>
-static qedhmc_status apply_P_t(qedhmc_ctx* h, const cplx<R>* r, cplx<R>* z, cplx<R>* tmp, const double* stop) {
-    if (use_spectral<R>(h)) {
-        cplx<R>* vhat = spec_vhat<R>(h, z, tmp);
-        QH_TRY(launch_pcs_fwd<R>(h, r, vhat, stop));
-        return launch_pcs_rest<R>(h, vhat, z, tmp, stop);
+static qedhmc_status launch_pcs_rest(qedhmc_ctx* h, const cplx<R>* vhat, cplx<R>* z, cplx<R>* m1,
+                                     const double* stop) {
+    const PcSpecGeo g = spec_geo<R>(h);
+    if (!spec_fused(h)) {
+        // Runs of 6 slices (a run reads 24 slices more than it writes) once
+        // they give a thread to every lane of the chip, of 3 below.  P at
+        // L = 66, N_tau = 660 with runs of 4 / 6 / 8 / 10: FP32 87.4 / 81.2 /
+        // 82.3 / 83.7 us, FP64 (N_tau = 640) 171 / 156 / - / 154 us.
+        auto runs = [&]<int T>() {
+            const int nth = g.nk * ((g.Nt + T - 1) / T);
+            hipLaunchKernelGGL((k_pcs_tsum<R, T>), dim3((nth + 255) / 256), dim3(256), 0, h->stream, g, spec_H<R>(h),
+                               vhat, m1, stop);
+        };
+        if ((size_t)g.nk * g.Nt >= ((size_t)1 << 20))
+            runs.template operator()<6>();
+        else
+            runs.template operator()<3>();
+        QH_HIP(hipGetLastError());
     }
-    QH_TRY(launch_pc<R>(h, 0, r, tmp, stop));
-    return launch_pc<R>(h, 1, tmp, z, stop);
+    return with_spec<R>(g, [&]<int NY, int NX, bool TL>() -> qedhmc_status {
+        bool tl;
+        const size_t lds = spec_lds<R>(g, tl);
+        if (!spec_fused(h)) {
+            if (lds > 65536) QH_TRY(allow_lds((const void*)k_pcs_inv<R, NY, NX, TL>, h->max_lds));
+            hipLaunchKernelGGL((k_pcs_inv<R, NY, NX, TL>), dim3(slice_grid(g.Nt)),
+                               dim3(spec_threads(g, g.nk / 2, spec_max_threads<R>())), lds, h->stream, g,
+                               spec_tab<R>(h), (const cplx<R>*)m1, z, stop);
+            QH_HIP(hipGetLastError());
+            return QEDHMC_OK;
+        }
+        if (lds > 65536) QH_TRY(allow_lds((const void*)k_pcs_tsum_inv<R, NY, NX, TL>, h->max_lds));
+        const dim3 grid(slice_grid(g.Nt)), blk(spec_threads(g, g.nk, 512));
+        hipEvent_t e0, e1;
+        if (prof_sample(h, sizeof(R) == 4 ? QEDHMC_K_PC_SPEC_FP32 : QEDHMC_K_PC_SPEC_FP64, e0, e1))
+            hipExtLaunchKernelGGL((k_pcs_tsum_inv<R, NY, NX, TL>), grid, blk, lds, h->stream, e0, e1, 0, g,
+                                  spec_H<R>(h), spec_tab<R>(h), vhat, z, stop);
+        else
+            hipLaunchKernelGGL((k_pcs_tsum_inv<R, NY, NX, TL>), grid, blk, lds, h->stream, g, spec_H<R>(h),
+                               spec_tab<R>(h), vhat, z, stop);
+        QH_HIP(hipGetLastError());
+        return QEDHMC_OK;
+    });
+}
+
+// z = G^dag (G r); m0 and m1: scratch vectors of the same precision for the
+// momentum form (r, z and m0 distinct; m1 distinct from r and m0; where the tau
+// sum is not fused m0 may be z, if z is aligned to 32 bytes)
+template <typename R>
+static qedhmc_status apply_P_t(qedhmc_ctx* h, const cplx<R>* r, cplx<R>* z, cplx<R>* m0, cplx<R>* m1,
+                               const double* stop) {
+    if (use_spectral<R>(h)) {
+        QH_TRY(launch_pcs_fwd<R>(h, r, m0, stop));
+        return launch_pcs_rest<R>(h, m0, z, m1, stop);
+    }
+    QH_TRY(launch_pc<R>(h, 0, r, m1, stop));
+    return launch_pc<R>(h, 1, m1, z, stop);
 }
 
 template <typename A, typename B>
@@ -1270,7 +1226,7 @@ qedhmc_status launch_apply_precond_fp32(qedhmc_ctx* h, const double* in, double*
     hipLaunchKernelGGL((k_pc_convert<double, float>), dim3(grid), dim3(256), 0, h->stream,
                        reinterpret_cast<const cplx<double>*>(in), r32, N);
     QH_HIP(hipGetLastError());
-    QH_TRY(apply_P_t<float>(h, r32, z32, t32, nullptr));
+    QH_TRY(apply_P_t<float>(h, r32, z32, t32, z32 + N, nullptr));
     hipLaunchKernelGGL((k_pc_convert<float, double>), dim3(grid), dim3(256), 0, h->stream, (const cplx<float>*)z32,
                        reinterpret_cast<cplx<double>*>(out), N);
     QH_HIP(hipGetLastError());
@@ -1279,9 +1235,13 @@ qedhmc_status launch_apply_precond_fp32(qedhmc_ctx* h, const double* in, double*
 
 qedhmc_status launch_apply_precond(qedhmc_ctx* h, qedhmc_precision prec, const void* in, void* out) {
     QH_TRY(ensure_paper_precond(h));
+    // the caller's vectors are read and written element by element; the
+    // momentum form lives in the handle's scratch
     if (prec == QEDHMC_FP64)
-        return apply_P_t<double>(h, (const cplx<double>*)in, (cplx<double>*)out, (cplx<double>*)h->ws[9], nullptr);
-    return apply_P_t<float>(h, (const cplx<float>*)in, (cplx<float>*)out, (cplx<float>*)h->ws[9], nullptr);
+        return apply_P_t<double>(h, (const cplx<double>*)in, (cplx<double>*)out, (cplx<double>*)h->ws[9],
+                                 (cplx<double>*)h->ws[8], nullptr);
+    return apply_P_t<float>(h, (const cplx<float>*)in, (cplx<float>*)out, (cplx<float>*)h->ws[9],
+                            (cplx<float>*)h->ws[8], nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1369,14 +1329,14 @@ __device__ __forceinline__ void reduce_k(const double* __restrict__ part, int Nt
 // together (one round trip to memory instead of two in a row).
 static constexpr int kUpdPre = 4;
 
-template <typename R, bool DFT>
+template <typename R, int NY, int NX, bool TL>
 __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBufs<R> B, double* __restrict__ scal, int kpar,
-                                                  int mixed, int maxit, PcSpecGeo sg, const cplx<R>* __restrict__ tw,
+                                                  int mixed, int maxit, PcSpecGeo sg, const R* __restrict__ tab,
                                                   cplx<R>* __restrict__ vhat) {
+    constexpr bool DFT = NY > 0;
     __shared__ double red[kNP7 * 16 + 16];
-    extern __shared__ __align__(16) unsigned char smem[];
-    cplx<R>* buf = reinterpret_cast<cplx<R>*>(smem);  // [plane][row][column]: the new r by x parity
-    cplx<R>* twx = buf + (DFT ? 2 * sg.nk : 0);
+    extern __shared__ __align__(32) unsigned char smem[];
+    R* V = reinterpret_cast<R*>(smem);  // the new r, as the transform reads it
     const double* sin_ = scal + S_NSLOT * kpar;
     double* sout = scal + S_NSLOT * (kpar ^ 1);
     const int tau = slice_of_block(blockIdx.x, lt.Nt);
@@ -1400,8 +1360,8 @@ __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBu
         r0[j] = B.r[i];
         x0[j] = B.x[i];
     }
-    const int ntw = DFT ? sg.Lh + sg.L : 0;  // <= blockDim.x (spec_fits)
-    const cplx<R> twv = (int)threadIdx.x < ntw ? tw[threadIdx.x] : mk<R>(R(0), R(0));
+    const R* tb = nullptr;
+    if constexpr (DFT) tb = sp_tables<R, TL>(tab, V + sg.L * sg.ld, sg);
     double sl[S_NSLOT];
 #pragma unroll
     for (int k = 0; k < S_NSLOT; k++) sl[k] = sin_[k];
@@ -1455,7 +1415,6 @@ __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBu
         sout[threadIdx.x] = v;
     }
     if (stop || tau < 0) return;
-    if (DFT && (int)threadIdx.x < ntw) twx[threadIdx.x] = twv;
     const R a = (R)alpha, b = (R)beta;
     auto update = [&](int k, cplx<R> pk, cplx<R> uk, cplx<R> sk, cplx<R> wk, cplx<R> rk, cplx<double> xv) {
         const size_t i = base + k;
@@ -1469,8 +1428,8 @@ __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBu
         const cplx<R> rn = cfma(-a, sn, rk);
         B.r[i] = rn;
         if (DFT) {
-            const int y = k / sg.L, x = k - y * sg.L;
-            buf[(x & 1) * sg.nk + y * sg.Lh + (x >> 1)] = rn;
+            const int y = k / sg.L;
+            *reinterpret_cast<cplx<R>*>(V + y * sg.ld + 2 * (k - y * sg.L)) = rn;
         }
     };
 #pragma unroll
@@ -1482,11 +1441,7 @@ __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBu
         const size_t i = base + k;
         update(k, B.p[i], B.u[i], B.s[i], B.w[i], B.r[i], B.x[i]);
     }
-    if (DFT) {
-        __syncthreads();
-        dft_planes<R>(buf, twx, twx + sg.Lh, sg.L, sg.Lh, 2,
-                      [&](int pl, int e, cplx<R> v) { vhat[base + (size_t)pl * sg.nk + e] = v; });
-    }
+    if constexpr (DFT) sp_forward<R, NY, NX>(V, sg, tb, vhat + base);
 }
 
 // w = O u (own slice) and the partials of the next iteration
@@ -1707,35 +1662,34 @@ static qedhmc_status launch_mv(qedhmc_ctx* h, const PcgBufs<R>& B, const double*
 // preconditioner u is r itself and only w = O r is launched
 template <typename R>
 static qedhmc_status pcg_tail(qedhmc_ctx* h, const PcgBufs<R>& B, const double* stop, bool identity) {
-    if (!identity) QH_TRY(apply_P_t<R>(h, B.r, B.u, B.t, stop));
+    if (!identity) QH_TRY(apply_P_t<R>(h, B.r, B.u, spec_vhat<R>(h, B.u, B.t), B.t, stop));
     return launch_mv<R>(h, B, stop, stop != nullptr);
 }
 
 // n iterations from launch parity kpar: update, then preconditioner and
 // matvec, each gated on the slot's stop flag
-// Spectral P with the update kernel doing its first step: the plan's
-// threads and LDS for both planes of a slice, or false where it does not fit
-template <typename R>
-static bool upd_dft_plan(qedhmc_ctx* h, int& threads, size_t& lds) {
-    return use_spectral<R>(h) && spec_fits<R>(h, 2, threads, lds);
-}
-
 template <typename R>
 static qedhmc_status pcg_chunk(qedhmc_ctx* h, const PcgBufs<R>& B, int kpar, int n, bool mixed, bool identity,
                                int maxit) {
-    int threads = 256;
-    size_t lds = 0;
-    const bool fdft = !identity && upd_dft_plan<R>(h, threads, lds);
-    if (fdft && lds > 65536) QH_TRY(allow_lds((const void*)k_pcg_upd<R, true>, h->max_lds));
+    // spectral P: the update kernel does its first step
+    const bool fdft = !identity && use_spectral<R>(h);
     const PcSpecGeo sg = fdft ? spec_geo<R>(h) : PcSpecGeo{};
     cplx<R>* vhat = fdft ? spec_vhat<R>(h, B.u, B.t) : nullptr;
     for (int k = 0; k < n; k++) {
         if (fdft)
-            hipLaunchKernelGGL((k_pcg_upd<R, true>), dim3(slice_grid(h->lat.Nt)), dim3(threads), lds, h->stream, h->lat, B, h->scal,
-                               kpar, mixed ? 1 : 0, maxit, sg, spec_tw<R>(h), vhat);
+            QH_TRY(with_spec<R>(sg, [&]<int NY, int NX, bool TL>() -> qedhmc_status {
+                bool tl;
+                const size_t lds = spec_lds<R>(sg, tl);
+                if (lds > 65536 - 2048) QH_TRY(allow_lds((const void*)k_pcg_upd<R, NY, NX, TL>, h->max_lds));
+                hipLaunchKernelGGL((k_pcg_upd<R, NY, NX, TL>), dim3(slice_grid(h->lat.Nt)),
+                                   dim3(spec_threads(sg, sg.Vs, spec_max_threads<R>())), lds, h->stream, h->lat, B,
+                                   h->scal, kpar, mixed ? 1 : 0, maxit, sg, spec_tab<R>(h), vhat);
+                return QEDHMC_OK;
+            }));
         else
-            hipLaunchKernelGGL((k_pcg_upd<R, false>), dim3(slice_grid(h->lat.Nt)), dim3(256), 0, h->stream, h->lat, B, h->scal,
-                               kpar, mixed ? 1 : 0, maxit, sg, (const cplx<R>*)nullptr, (cplx<R>*)nullptr);
+            hipLaunchKernelGGL((k_pcg_upd<R, 0, 0, false>), dim3(slice_grid(h->lat.Nt)), dim3(256), 0, h->stream,
+                               h->lat, B, h->scal, kpar, mixed ? 1 : 0, maxit, sg, (const R*)nullptr,
+                               (cplx<R>*)nullptr);
         kpar ^= 1;
         const double* stop = h->scal + S_NSLOT * kpar + S_DONE;
         if (fdft) {
