@@ -93,24 +93,6 @@ static void spec_blocks(int L, int& ny, int& nx) {
     nx = b <= 2 ? 1 : (b <= 3 ? 2 : 3);
 }
 
-// DFT weights of n points in the fragment order of sp_tile: cos and sin of
-// 2 pi j k / n at k = 4 step + lane / 16, j = 16 block + lane % 16, both up to
-// n / 2 (zero beyond); half the cosine at the k paired with itself.
-template <typename R>
-static void spec_table(int n, int nt, R* t) {
-    const int steps = sp_steps(n);
-    for (int b = 0; b < nt; b++)
-        for (int s = 0; s < steps; s++)
-            for (int l = 0; l < 64; l++) {
-                const int k = 4 * s + l / 16, j = 16 * b + l % 16;
-                const bool on = k <= n / 2 && j <= n / 2;
-                const double a = 2 * M_PI * ((long)j * k % n) / n, w = (k == 0 || 2 * k == n) ? 0.5 : 1.0;
-                R* f = t + (size_t)((b * steps + s) * 2) * 64 + l;
-                f[0] = on ? (R)(w * std::cos(a)) : R(0);
-                f[64] = on && w == 1.0 ? (R)std::sin(a) : R(0);
-            }
-}
-
 static qedhmc_status build_spectral(qedhmc_ctx* h, const std::vector<HostTap> (&pass)[2][2]) {
     h->pc_spec_na = 0;
     const int L = h->lat.L, Lh = L / 2, nk = L * Lh;
@@ -178,10 +160,10 @@ static qedhmc_status build_spectral(qedhmc_ctx* h, const std::vector<HostTap> (&
     const size_t ntab = sp_table(L, ny) + sp_table(Lh, nx);
     std::vector<double> tw(ntab);
     std::vector<float> tw32(ntab);
-    spec_table<double>(L, ny, tw.data());
-    spec_table<double>(Lh, nx, tw.data() + sp_table(L, ny));
-    spec_table<float>(L, ny, tw32.data());
-    spec_table<float>(Lh, nx, tw32.data() + sp_table(L, ny));
+    sp_fill_table<double>(L, ny, tw.data());
+    sp_fill_table<double>(Lh, nx, tw.data() + sp_table(L, ny));
+    sp_fill_table<float>(L, ny, tw32.data());
+    sp_fill_table<float>(Lh, nx, tw32.data() + sp_table(L, ny));
     std::vector<cplx<float>> H32(Hh.size());
     for (size_t i = 0; i < Hh.size(); i++) H32[i] = mk<float>((float)Hh[i].re, (float)Hh[i].im);
     QH_HIP(hipMalloc(&h->pc_spec64, Hh.size() * sizeof(cplx<double>)));

@@ -1,5 +1,6 @@
-// Device side of the paper preconditioner's spectral form (pcg.hip): the 2D
-// DFT of a slice on the matrix cores and the banded tau sum.
+// DFTs on the matrix cores (the paper preconditioner's spectral form, pcg.hip;
+// the spin correlator's transforms, se.hip) and the preconditioner's banded
+// tau sum.
 //
 // A slice of a site vector is a matrix of L rows (y) of 2 L reals (x, re/im
 // interleaved).  Its momentum form on the two-site cell (2 in x, 1 in y) is
@@ -19,6 +20,8 @@
 // is the A operand (16 reals along the untransformed axis x 4 points), the
 // weights the B operand (4 points x 16 outputs), packed in fragment order.
 #pragma once
+#include <cmath>
+
 #include "qedhmc_internal.h"
 
 namespace qh {
@@ -57,6 +60,24 @@ constexpr int kSpTau = QEDHMC_PC_TAU_REACH;  // tau offsets of P at most, either
 __host__ __device__ constexpr int sp_steps(int n) { return n / 2 / 4 + 1; }
 __host__ __device__ constexpr int sp_table(int n, int nt) { return nt * sp_steps(n) * 2 * 64; }
 
+// Weights of n points in nt blocks in the fragment order of sp_tile: cos and
+// sin of 2 pi j k / n at k = 4 step + lane / 16, j = 16 block + lane % 16, both
+// up to n / 2 (zero beyond); half the cosine at a k paired with itself.
+template <typename R>
+inline void sp_fill_table(int n, int nt, R* t) {
+    const int steps = sp_steps(n);
+    for (int b = 0; b < nt; b++)
+        for (int s = 0; s < steps; s++)
+            for (int l = 0; l < 64; l++) {
+                const int k = 4 * s + l / 16, j = 16 * b + l % 16;
+                const bool on = k <= n / 2 && j <= n / 2;
+                const double a = 2 * M_PI * ((long)j * k % n) / n, w = (k == 0 || 2 * k == n) ? 0.5 : 1.0;
+                R* f = t + (size_t)((b * steps + s) * 2) * 64 + l;
+                f[0] = on ? (R)(w * std::cos(a)) : R(0);
+                f[64] = on && w == 1.0 ? (R)std::sin(a) : R(0);
+            }
+}
+
 struct PcSpecGeo {
     int L, Lh, Nt, Vs, nk;
     int reach;  // tau offsets of P: -reach .. reach
@@ -83,7 +104,8 @@ __device__ __forceinline__ void sp_tile(const R* pt, int stride, int n, int part
     for (int b = 0; b < NT; b++)
 #pragma unroll
         for (int i = 0; i < 4; i++) P[b][i] = Q[b][i] = R(0);
-#pragma unroll 4
+    // (one step at a time: batches of four steps measured 91 against 81 us for
+    // P at L = 66, where the padding of the last batch costs LDS reads)
     for (int s = 0; s < steps; s++) {
         int k = 4 * s + g;
         k = k <= hn ? k : 0;  // padding points carry zero weights
@@ -101,65 +123,75 @@ __device__ __forceinline__ void sp_tile(const R* pt, int stride, int n, int part
     }
 }
 
-// Along y, in place, 16 columns of reals per wavefront and turn: V[y][c] ->
-// V[j][c].  emit(j, c, quad) stores four consecutive reals of a row (default:
-// back into the image).
+// One tile along the rows of an image with n rows of `cols` reals, `ld` reals
+// apart: 16 columns, V[k][c] -> j.  emit(j, c, quad) takes four consecutive
+// reals of output row j (default: back into the image).
 template <typename R, int NT, bool INV, typename Emit>
-__device__ __forceinline__ void sp_dft_y(R* V, const PcSpecGeo& g, const R* tab, Emit emit) {
+__device__ __forceinline__ void sp_y_tile(const R* V, int n, int cols, int ld, int t, const R* tab, Emit emit) {
     const int lane = threadIdx.x & 63, q = lane >> 4, col = lane & 15;
-    const int nw = (int)blockDim.x >> 6, cols = 2 * g.L, ntile = (cols + 15) >> 4, n = g.L;
-    for (int t = (int)threadIdx.x >> 6; t < ntile; t += nw) {
-        const int c = min(16 * t + sp_row<R>(col), cols - 1);
-        vec4<R> P[NT], Q[NT];
-        sp_tile<R, NT>(V + (c & ~1), g.ld, n, c & 1, tab, P, Q);
-        const int c0 = 16 * t + 4 * q;  // this lane's four consecutive outputs start at an even real
-        if (c0 < cols)
+    const int c = min(16 * t + sp_row<R>(col), cols - 1);
+    vec4<R> P[NT], Q[NT];
+    sp_tile<R, NT>(V + (c & ~1), ld, n, c & 1, tab, P, Q);
+    const int c0 = 16 * t + 4 * q;  // this lane's four consecutive outputs start at an even real
+    if (c0 < cols)
 #pragma unroll
-            for (int b = 0; b < NT; b++) {
-                const int j = 16 * b + col;
-                if (j > n / 2) continue;
-                vec4<R> u, w;
+        for (int b = 0; b < NT; b++) {
+            const int j = 16 * b + col;
+            if (j > n / 2) continue;
+            vec4<R> u, w;
 #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const R s = ((i & 1) != 0) != INV ? -Q[b][i] : Q[b][i];
-                    u[i] = P[b][i] + s;
-                    w[i] = P[b][i] - s;
-                }
-                emit(j, c0, u);
-                if (j && j != n - j) emit(n - j, c0, w);
+            for (int i = 0; i < 4; i++) {
+                const R s = ((i & 1) != 0) != INV ? -Q[b][i] : Q[b][i];
+                u[i] = P[b][i] + s;
+                w[i] = P[b][i] - s;
             }
-    }
+            emit(j, c0, u);
+            if (j && j != n - j) emit(n - j, c0, w);
+        }
 }
 
-// Along x on the parity planes, 4 rows x (2 parities x re/im) per wavefront
-// and turn: V[r][4 m + 2 p + part] -> the same at momentum j.  emit(r, j,
-// quad) stores the four reals of (row r, j).
-template <typename R, int NT, bool INV, typename Emit>
-__device__ __forceinline__ void sp_dft_x(R* V, const PcSpecGeo& g, const R* tab, Emit emit) {
+// One tile along a row: G interleaved sequences of n complex values (the
+// parity planes, G = 2, or a plain row, G = 1), 8 / G rows.  emit(r, j, quad)
+// takes the four reals of (row r, point j) for G = 2, of (rows r and r + 1,
+// point j) for G = 1.
+template <typename R, int NT, bool INV, int G, typename Emit>
+__device__ __forceinline__ void sp_x_tile(const R* V, int n, int rows, int ld, int t, const R* tab, Emit emit) {
     const int lane = threadIdx.x & 63, q = lane >> 4, col = lane & 15;
-    const int nw = (int)blockDim.x >> 6, ntile = (g.L + 3) >> 2, n = g.Lh;
-    for (int t = (int)threadIdx.x >> 6; t < ntile; t += nw) {
-        const int m = sp_row<R>(col);
-        const int r = min(4 * t + (m >> 2), g.L - 1);
-        vec4<R> P[NT], Q[NT];
-        sp_tile<R, NT>(V + r * g.ld + (m & 2), 4, n, m & 1, tab, P, Q);
-        const int ro = 4 * t + q;
-        if (ro < g.L)
+    const int m = sp_row<R>(col);
+    const int r = min((8 / G) * t + m / (2 * G), rows - 1);
+    vec4<R> P[NT], Q[NT];
+    sp_tile<R, NT>(V + r * ld + (m & (2 * G - 2)), 2 * G, n, m & 1, tab, P, Q);
+    const int ro = (8 / G) * t + q * 2 / G;
+    if (ro < rows)
 #pragma unroll
-            for (int b = 0; b < NT; b++) {
-                const int j = 16 * b + col;
-                if (j > n / 2) continue;
-                vec4<R> u, w;
+        for (int b = 0; b < NT; b++) {
+            const int j = 16 * b + col;
+            if (j > n / 2) continue;
+            vec4<R> u, w;
 #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const R s = ((i & 1) != 0) != INV ? -Q[b][i] : Q[b][i];
-                    u[i] = P[b][i] + s;
-                    w[i] = P[b][i] - s;
-                }
-                emit(ro, j, u);
-                if (j && j != n - j) emit(ro, n - j, w);
+            for (int i = 0; i < 4; i++) {
+                const R s = ((i & 1) != 0) != INV ? -Q[b][i] : Q[b][i];
+                u[i] = P[b][i] + s;
+                w[i] = P[b][i] - s;
             }
-    }
+            emit(ro, j, u);
+            if (j && j != n - j) emit(ro, n - j, w);
+        }
+}
+
+// All tiles of a slice image by the workgroup's wavefronts in turn.  A tile
+// reads and writes its own columns (rows) alone, so in-place emits need no
+// barrier within an axis.
+template <typename R, int NT, bool INV, typename Emit>
+__device__ __forceinline__ void sp_dft_y(const R* V, const PcSpecGeo& g, const R* tab, Emit emit) {
+    const int nw = (int)blockDim.x >> 6, cols = 2 * g.L, ntile = (cols + 15) >> 4;
+    for (int t = (int)threadIdx.x >> 6; t < ntile; t += nw) sp_y_tile<R, NT, INV>(V, g.L, cols, g.ld, t, tab, emit);
+}
+template <typename R, int NT, bool INV, typename Emit>
+__device__ __forceinline__ void sp_dft_x(const R* V, const PcSpecGeo& g, const R* tab, Emit emit) {
+    const int nw = (int)blockDim.x >> 6, ntile = (g.L + 3) >> 2;
+    for (int t = (int)threadIdx.x >> 6; t < ntile; t += nw)
+        sp_x_tile<R, NT, INV, 2>(V, g.Lh, g.L, g.ld, t, tab, emit);
 }
 
 // The slice image V (sites) to momentum planes at dst ([ny][nx][parity], 16
@@ -224,7 +256,7 @@ __device__ __forceinline__ void v_cmacc(cplx<R>& acc, cplx<R> m, cplx<R> v) {
 
 // The two parity values of a momentum.
 template <typename R>
-struct alignas(4 * sizeof(R) > 16 ? 16 : 4 * sizeof(R)) cpair {
+struct alignas(16) cpair {
     cplx<R> a, b;
 };
 
