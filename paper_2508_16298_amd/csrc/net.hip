@@ -231,96 +231,6 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(NetGeo g, const float* __res
     if (bias) out[E + threadIdx.x] = accb;
 }
 
-// Weight gradients on the matrix cores: per tap k the product dW_k = A_k^T G
-// over a chunk of sites, A_k[n][c] = in[n + tap k][c] and G[n][o] =
-// gout[n][o], as v_mfma_f32_16x16x4f32 (FP32 operands, FP32 accumulation:
-// the same arithmetic as the vector kernel, summed in another order), the
-// channels in blocks of 16 (zero-padded: the first layer's 6 inputs, the last
-// layer's 2 outputs).  A wavefront holds 7 taps (k = wave + 4 j) as
-// CINB x COUTB output blocks each; the last wavefront's seventh slot is the
-// bias gradient, the same product with A = 1.  Per step of 4 sites a lane
-// loads one G value per output block (shared by its taps) and one input value
-// per tap and input block.  The first layer reads the feature map from feat
-// ([N][8], the residual channels 4, 5 sign-flipped where the tap wraps in
-// tau).  Partials per chunk as the vector kernel writes them.
-typedef float wg_f32x4 __attribute__((ext_vector_type(4)));
-static constexpr int kWgTaps = 7;
-
-template <int CIN, int COUT, bool FIRST>
-__global__ __launch_bounds__(256) void k_wgrad_mfma(NetGeo g, int chunk, const float* __restrict__ in,
-                                                    const float* __restrict__ gout, float* __restrict__ part) {
-    constexpr int CINB = (CIN + 15) / 16, COUTB = (COUT + 15) / 16;
-    constexpr int EK = CIN * COUT, E = 27 * EK;
-    constexpr int IS = FIRST ? 8 : CIN;  // row stride of the input
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n0 = blockIdx.x * chunk, n1 = min(n0 + chunk, g.N);
-    const int c16 = lane & 15, kq = lane >> 4;
-    wg_f32x4 acc[kWgTaps][CINB][COUTB];
-#pragma unroll
-    for (int j = 0; j < kWgTaps; j++)
-#pragma unroll
-        for (int cb = 0; cb < CINB; cb++)
-#pragma unroll
-            for (int ob = 0; ob < COUTB; ob++) acc[j][cb][ob] = wg_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 1
-    for (int n = n0; n < n1; n += 4) {
-        const int nn = n + kq;  // this lane's site of the 4-site step
-        const bool valid = nn < n1;
-        int tau, y, x;
-        site_of(g, valid ? nn : n0, tau, y, x);
-        float b[COUTB];
-#pragma unroll
-        for (int ob = 0; ob < COUTB; ob++) {
-            const int o = 16 * ob + c16;
-            b[ob] = (valid && o < COUT) ? gout[(size_t)nn * COUT + o] : 0.0f;
-        }
-#pragma unroll
-        for (int j = 0; j < kWgTaps; j++) {
-            const int k = wave + 4 * j;
-            float a[CINB];
-#pragma unroll
-            for (int cb = 0; cb < CINB; cb++) a[cb] = 1.0f;  // k = 27: the bias slot
-            if (k < 27) {
-                const int dt = k / 9 - 1, dy = (k / 3) % 3 - 1, dx = k % 3 - 1;
-                float sg = 1.0f;
-                const int tt = wrap_tau(tau + dt, g.Nt, sg);
-                const int m = tt * g.Vs + wrap(y + dy, g.L) * g.L + wrap(x + dx, g.L);
-#pragma unroll
-                for (int cb = 0; cb < CINB; cb++) {
-                    const int c = 16 * cb + c16;
-                    float v = c < CIN ? in[(size_t)m * IS + c] : 0.0f;
-                    if (FIRST && c >= 4) v *= sg;
-                    a[cb] = v;
-                }
-            }
-#pragma unroll
-            for (int cb = 0; cb < CINB; cb++)
-#pragma unroll
-                for (int ob = 0; ob < COUTB; ob++)
-                    acc[j][cb][ob] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[cb], b[ob], acc[j][cb][ob], 0, 0, 0);
-        }
-    }
-    // D fragment: lane holds rows 4 (lane / 16) + r (input channels), column lane % 16 (output channel)
-    float* out = part + (size_t)blockIdx.x * (E + COUT);
-#pragma unroll
-    for (int j = 0; j < kWgTaps; j++) {
-        const int k = wave + 4 * j;
-#pragma unroll
-        for (int cb = 0; cb < CINB; cb++)
-#pragma unroll
-            for (int ob = 0; ob < COUTB; ob++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int c = 16 * cb + 4 * kq + r, o = 16 * ob + c16;
-                    if (o >= COUT) continue;
-                    if (k < 27 && c < CIN)
-                        out[(size_t)k * EK + c * COUT + o] = acc[j][cb][ob][r];
-                    else if (k == 27 && c == 0)
-                        out[E + o] = acc[j][cb][ob][r];
-                }
-    }
-}
-
 // the first layer's feature map [N][8] (channels 6, 7 zero), unsigned
 template <typename TR>
 __global__ void k_features(NetGeo g, const cplx<float>* __restrict__ g32, const cplx<TR>* __restrict__ r,
@@ -333,14 +243,6 @@ __global__ void k_features(NetGeo g, const cplx<float>* __restrict__ g32, const 
     for (int c = 0; c < 6; c++) feat[(size_t)m * 8 + c] = f[c];
     feat[(size_t)m * 8 + 6] = 0.0f;
     feat[(size_t)m * 8 + 7] = 0.0f;
-}
-
-// sites per weight-gradient chunk on the matrix cores: about 2048 chunks,
-// 256 .. 4096 sites each (a multiple of 4)
-int wgrad_mfma_chunk(int N) {
-    int c = (N + 2047) / 2048;
-    c = ((c + 255) / 256) * 256;
-    return c < 256 ? 256 : (c > 4096 ? 4096 : c);
 }
 
 // grad[e] = sum over chunks b (in order) of part[b][e]
@@ -429,6 +331,18 @@ __global__ void k_net_resgrad(int N, const cplx<double>* __restrict__ Od, const 
     }
 }
 
+// device layout W[27][ci][co], b[co] per layer to the host layout, on the device
+__global__ void k_host_layout(int ci_n, int co_n, const float* __restrict__ dev, float* __restrict__ out) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, nw = 27 * ci_n * co_n;
+    if (i >= nw + co_n) return;
+    if (i >= nw) {
+        out[i] = dev[i];
+        return;
+    }
+    const int k = i % 27, ci = i / 27 % ci_n, co = i / (27 * ci_n);
+    out[i] = dev[((size_t)k * ci_n + ci) * co_n + co];
+}
+
 // Adam (Kingma and Ba 2015): m = b1 m + (1 - b1) g; v = b2 v + (1 - b2) g^2;
 // p -= lr (m / (1 - b1^t)) / (sqrt(v / (1 - b2^t)) + eps)
 __global__ void k_adam(int n, float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
@@ -470,12 +384,13 @@ __global__ __launch_bounds__(256) void k_cdot2(int N, const cplx<double>* __rest
     }
 }
 
-__global__ void k_sum1(const double* __restrict__ part, int nb, double* __restrict__ out) {
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int b = 0; b < nb; b++) s += part[b];
-        *out = s;
-    }
+// *out = sum of nb block partials, by one workgroup in a fixed order
+__global__ __launch_bounds__(256) void k_sum1(const double* __restrict__ part, int nb, double* __restrict__ out) {
+    __shared__ double red[16];
+    double s = 0.0;
+    for (int b = threadIdx.x; b < nb; b += blockDim.x) s += part[b];
+    s = block_sum(s, red);
+    if (threadIdx.x == 0) *out = s;
 }
 
 __global__ void k_sum4(const double* __restrict__ part, int nb, double* __restrict__ out) {
@@ -596,11 +511,14 @@ qedhmc_status net_alloc_train(qedhmc_net* n) {
     ok = ok && hipMalloc(&n->pre[kNetLayers - 1], N * 2 * sizeof(float)) == hipSuccess;
     // act[kNetLayers] (the output channels) and gbuf exist from creation
     for (int l = 1; l < kNetLayers; l++) ok = ok && hipMalloc(&n->act[l], N * 32 * sizeof(float)) == hipSuccess;
-    const size_t nchunk = std::max((N + kWChunk - 1) / kWChunk,
-                                   (N + wgrad_mfma_chunk((int)N) - 1) / (size_t)wgrad_mfma_chunk((int)N));
-    ok = ok && hipMalloc(&n->wpart, nchunk * (27 * 32 * 32 + 32) * sizeof(float)) == hipSuccess;
+    // partials of the vector kernels' chunks, or of the bricks' workgroups
+    size_t elems = (N + kWChunk - 1) / kWChunk * (27 * 32 * 32 + 32);
+    for (int l = 0; l < kNetLayers; l++)
+        elems = std::max(elems, (size_t)wgrad_parts(n, l) * (27 * kNetCh[l] * kNetCh[l + 1] + kNetCh[l + 1]));
+    ok = ok && hipMalloc(&n->wpart, elems * sizeof(float)) == hipSuccess;
     ok = ok && hipMalloc(&n->feat, N * 8 * sizeof(float)) == hipSuccess;
-    ok = ok && hipMalloc(&n->wtmp, (size_t)kWgGroups * (27 * 32 * 32 + 32) * sizeof(float)) == hipSuccess;
+    ok = ok && hipMalloc(&n->wtmp, std::max((size_t)kWgGroups * (27 * 32 * 32 + 32), n->nparam) * sizeof(float)) ==
+                   hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         return net_fail(n, "net: training buffers: device allocation failed", QEDHMC_ENOMEM);
@@ -655,12 +573,22 @@ static qedhmc_status net_forward(qedhmc_net* n, const double* theta, const doubl
     QH_TRY(sumsq_to(n, r, 2 * (size_t)n->g.N, n->dscal + 0));
     if (a == QEDHMC_NET_BF16 && !keep) return net_forward_bf16(n, r, false, n->dscal);
     const float* in = nullptr;
+    if (keep)
+        hipLaunchKernelGGL(k_features<double>, dim3(blocks_for(n->g.N, 256)), dim3(256), 0, n->h->stream, n->g,
+                           (const cplx<float>*)n->h->gauge32, reinterpret_cast<const cplx<double>*>(r),
+                           (const double*)n->dscal, n->feat);
     for (int l = 0; l < kNetLayers; l++) {
         float* out;
         float* pre = nullptr;
         if (keep) {
             out = n->act[l + 1];
             pre = n->pre[l];
+            if (!net_f32_on_vector_alus()) {
+                // training: every layer on the matrix cores
+                QH_TRY(launch_fwd_mfma32(n, l, l == 0 ? n->feat : in, pre, out));
+                in = out;
+                continue;
+            }
         } else {
             out = (l == kNetLayers - 1) ? n->act[kNetLayers] : n->gbuf[l & 1];
         }
@@ -715,20 +643,9 @@ static qedhmc_status launch_wgrad(qedhmc_net* n, int l, const double* r, const f
             hipLaunchKernelGGL((k_conv_wgrad<32, 2, false>), grid, dim3(256), 0, st, g, n->act[l], g32, rc,
                                n->dscal, gout, n->wpart);
     } else {
-        const int chunk = wgrad_mfma_chunk(g.N);
-        nchunk = blocks_for(g.N, chunk);
-        if (l == 0) {
-            hipLaunchKernelGGL(k_features<double>, dim3(blocks_for(g.N, 256)), dim3(256), 0, st, g, g32, rc,
-                               (const double*)n->dscal, n->feat);
-            hipLaunchKernelGGL((k_wgrad_mfma<6, 32, true>), dim3(nchunk), dim3(256), 0, st, g, chunk,
-                               (const float*)n->feat, gout, n->wpart);
-        } else if (l < kNetLayers - 1) {
-            hipLaunchKernelGGL((k_wgrad_mfma<32, 32, false>), dim3(nchunk), dim3(256), 0, st, g, chunk,
-                               (const float*)n->act[l], gout, n->wpart);
-        } else {
-            hipLaunchKernelGGL((k_wgrad_mfma<32, 2, false>), dim3(nchunk), dim3(256), 0, st, g, chunk,
-                               (const float*)n->act[l], gout, n->wpart);
-        }
+        // (the forward left the feature map)
+        nchunk = wgrad_parts(n, l);
+        QH_TRY(launch_wgrad_mfma(n, l, l == 0 ? n->feat : n->act[l], gout));
     }
     // W and b are contiguous in the parameter vector (b follows W)
     if (nchunk > 4 * kWgGroups) {
@@ -882,19 +799,16 @@ qedhmc_status qedhmc_net_set_params(qedhmc_net_t n, const float* host, int64_t c
     return QEDHMC_OK;
 }
 
-static qedhmc_status to_host_layout(qedhmc_net* n, const float* dptr, float* host) {
-    std::vector<float> dev(n->nparam);
-    QH_HIP(hipMemcpyAsync(dev.data(), dptr, n->nparam * sizeof(float), hipMemcpyDeviceToHost, n->h->stream));
-    QH_HIP(hipStreamSynchronize(n->h->stream));
+// scratch: nparam floats on the device
+static qedhmc_status to_host_layout(qedhmc_net* n, const float* dptr, float* scratch, float* host) {
     for (int l = 0; l < kNetLayers; l++) {
-        const int ci_n = kNetCh[l], co_n = kNetCh[l + 1];
-        const float* dw = dev.data() + n->woff[l];
-        float* hw = host + n->woff[l];
-        for (int co = 0; co < co_n; co++)
-            for (int ci = 0; ci < ci_n; ci++)
-                for (int k = 0; k < 27; k++) hw[((size_t)co * ci_n + ci) * 27 + k] = dw[((size_t)k * ci_n + ci) * co_n + co];
-        for (int co = 0; co < co_n; co++) host[n->boff[l] + co] = dev[n->boff[l] + co];
+        const int total = 27 * kNetCh[l] * kNetCh[l + 1] + kNetCh[l + 1];
+        hipLaunchKernelGGL(k_host_layout, dim3(blocks_for(total, 256)), dim3(256), 0, n->h->stream, kNetCh[l],
+                           kNetCh[l + 1], dptr + n->woff[l], scratch + n->woff[l]);
     }
+    QH_HIP(hipGetLastError());
+    QH_HIP(hipMemcpyAsync(host, scratch, n->nparam * sizeof(float), hipMemcpyDeviceToHost, n->h->stream));
+    QH_HIP(hipStreamSynchronize(n->h->stream));
     return QEDHMC_OK;
 }
 
@@ -903,7 +817,7 @@ qedhmc_status qedhmc_net_get_params(qedhmc_net_t n, float* host, int64_t count) 
         set_error("net: null argument or wrong parameter count");
         return QEDHMC_EINVAL;
     }
-    return to_host_layout(n, n->params, host);
+    return to_host_layout(n, n->params, n->grads, host);
 }
 
 qedhmc_status qedhmc_net_reset_optimizer(qedhmc_net_t n) {
@@ -964,7 +878,7 @@ qedhmc_status qedhmc_net_train_step(qedhmc_net_t n, const double* theta, const d
     hipLaunchKernelGGL(k_net_loss, dim3(kRedBlocks), dim3(256), 0, st, g.N, (const float*)n->act[kNetLayers],
                        (const double*)n->dscal, (const cplx<double>*)e, (const double*)(n->dscal + 1), n->gbuf[0],
                        n->dpart);
-    hipLaunchKernelGGL(k_sum1, dim3(1), dim3(64), 0, st, (const double*)n->dpart, kRedBlocks, n->dscal + 2);
+    hipLaunchKernelGGL(k_sum1, dim3(1), dim3(256), 0, st, (const double*)n->dpart, kRedBlocks, n->dscal + 2);
     QH_HIP(hipGetLastError());
     QH_TRY(net_backward_adam(n, r, lr, grad_host));
     QH_HIP(hipMemcpyAsync(n->hpin, n->dscal, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
@@ -996,7 +910,7 @@ qedhmc_status qedhmc_net_train_step_residual(qedhmc_net_t n, const double* theta
     QH_TRY(launch_mdagm(n->h, QEDHMC_FP64, n->fz, n->fs));
     hipLaunchKernelGGL(k_net_resid, dim3(kRedBlocks), dim3(256), 0, st, g.N, n->fs,
                        reinterpret_cast<const cplx<double>*>(r), n->dpart);
-    hipLaunchKernelGGL(k_sum1, dim3(1), dim3(64), 0, st, (const double*)n->dpart, kRedBlocks, n->dscal + 2);
+    hipLaunchKernelGGL(k_sum1, dim3(1), dim3(256), 0, st, (const double*)n->dpart, kRedBlocks, n->dscal + 2);
     QH_HIP(hipGetLastError());
     QH_TRY(launch_mdagm(n->h, QEDHMC_FP64, n->fs, n->fp));
     hipLaunchKernelGGL(k_net_resgrad, dim3(blocks_for(g.N, 256)), dim3(256), 0, st, g.N,
@@ -1027,7 +941,7 @@ qedhmc_status net_backward_adam(qedhmc_net* n, const double* r, double lr, float
             cur ^= 1;
         }
     }
-    if (grad_host) QH_TRY(to_host_layout(n, n->grads, grad_host));
+    if (grad_host) QH_TRY(to_host_layout(n, n->grads, n->wtmp, grad_host));
     // Adam
     n->adam_t++;
     const double b1 = 0.9, b2 = 0.999;

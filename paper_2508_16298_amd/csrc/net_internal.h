@@ -81,11 +81,15 @@ qedhmc_status net_forward_bf16(qedhmc_net* n, const void* r, bool r32, const dou
 qedhmc_status net_infer(qedhmc_net* n, const void* r, bool r32, const double* rr, qedhmc_net_arith a);
 // number of BF16 weight elements the MFMA layers keep (fragment order)
 size_t net_bf16_weight_elems();
-// FP32 hidden layers of training on the matrix cores: the packed weights
-// (forward and transposed, fragment order), the forward with the
-// pre-activations and the data gradient of layer l (1 .. 4)
+// FP32 layers of training on the matrix cores (nettrain.hip): the packed
+// weights (forward and transposed, fragment order), the forward of layer l
+// with the pre-activations (l = 0: in is the feature map [N][8]), the data
+// gradient of layer l (1 .. 4), and the weight gradient of layer l as
+// wgrad_parts partials in n->wpart (l = 0: in is the feature map)
 size_t net_f32_weight_elems();
 qedhmc_status net_pack_f32(qedhmc_net* n);
+int wgrad_parts(const qedhmc_net* n, int l);
+qedhmc_status launch_wgrad_mfma(qedhmc_net* n, int l, const float* in, const float* gout);
 qedhmc_status launch_fwd_mfma32(qedhmc_net* n, int l, const float* in, float* pre, float* act);
 qedhmc_status launch_dgrad_mfma32(qedhmc_net* n, int l, const float* gout, const float* pre_prev, float* gin);
 // QEDHMC_NET_F32=valu (read per call) keeps the FP32 hidden layers on the
@@ -119,7 +123,7 @@ struct qedhmc_net {
     float* pre[qh::kNetLayers] = {};
     float* gbuf[2] = {nullptr, nullptr};
     float* wpart = nullptr;  // weight-gradient partials
-    float* feat = nullptr;   // the first layer's feature map [N][8] (weight gradient on the matrix cores)
+    float* feat = nullptr;   // the first layer's feature map [N][8] (training)
     float* wtmp = nullptr;   // group sums of the weight-gradient partials
     uint16_t* actb[2] = {nullptr, nullptr};  // BF16 ping-pong activations (inference)
     double* dscal = nullptr;  // [0] |r|^2, [1] |e|^2, [8..12) reductions
