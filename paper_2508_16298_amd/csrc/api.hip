@@ -298,8 +298,7 @@ qedhmc_status qedhmc_apply_MdagM(qedhmc_t h, const double* theta, const void* in
     if (!theta || !in || !out) return einval("null pointer");
     if (in == out) return einval("in and out alias");
     QH_TRY(check_prec(prec));
-    QH_TRY(ensure_gauge(h, theta, prec));
-    return launch_mdagm(h, prec, in, out, nullptr);
+    return launch_mdagm_theta(h, prec, theta, in, out);
 }
 
 // switched (nullable): with the learned preconditioner, the iteration at

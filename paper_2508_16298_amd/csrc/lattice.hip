@@ -5,6 +5,7 @@
 // of its 2x2 cells in registers, applies the in-cell families f0 and f2 there
 // and exchanges values through LDS only for the cross-cell families f1 and f3
 // (four exchanges per B_tau instead of seven full sweeps through memory).
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 
@@ -210,6 +211,52 @@ __global__ __launch_bounds__(BS) void k_mdagm(Lat lt, const cplx<R>* __restrict_
     load_cells<R, MC>(vn, in + (size_t)tp * lt.Vs, g, own);
     mdagm_cells<R, MC, NB>(vm, vt, vn, hm, ht, g, own, co, eps_m, eps_t, buf2, lt.Vs, o);
     store_cells<R, MC>(o, out + (size_t)tau * lt.Vs, g, own);
+}
+
+// ---------------------------------------------------------------------------
+// The same from theta itself: a workgroup forms e^{i theta} of its two slices
+// in LDS (the arithmetic of k_gauge, so the result is bitwise the same),
+// instead of a launch that writes the phases of the lattice and a second that
+// reads them back.  Every slice's phases are formed twice (by the workgroups
+// of tau and tau + 1): worth it while the call is bound by its launches.
+// ---------------------------------------------------------------------------
+template <typename R, int BS>
+__global__ __launch_bounds__(BS) void k_mdagm_theta(Lat lt, const cplx<R>* __restrict__ in, cplx<R>* __restrict__ out,
+                                                    const double* __restrict__ theta, Coef<R> co) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    cplx<R>* buf2 = reinterpret_cast<cplx<R>*>(smem);  // phases [d][slice tau - 1, tau][Vs], then the exchanges
+    const int tau = slice_of_block(blockIdx.x, lt.Nt), Nt = lt.Nt, Vs = lt.Vs;
+    if (tau < 0) return;
+    const int tm = tau == 0 ? Nt - 1 : tau - 1, tp = tau == Nt - 1 ? 0 : tau + 1;
+    CellGeo g[1];
+    bool own[1];
+    int idx[1][12];
+    my_cells<1>(lt, g, own, idx);
+    Cells<R, 1> vm, vt, vn, o;
+    load_cells<R, 1>(vm, in + (size_t)tm * Vs, g, own);
+    load_cells<R, 1>(vt, in + (size_t)tau * Vs, g, own);
+    load_cells<R, 1>(vn, in + (size_t)tp * Vs, g, own);
+    for (int s = threadIdx.x; s < Vs; s += blockDim.x) {
+        double t[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) t[k] = theta[((size_t)(k >> 1) * Nt + (k & 1 ? tau : tm)) * Vs + s];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            double sn, cs;
+            sincos(t[k], &sn, &cs);
+            buf2[(size_t)k * Vs + s] = mk<R>((R)cs, (R)sn);
+        }
+    }
+    __syncthreads();
+    Lat two = lt;
+    two.Nt = 2;
+    cplx<R> hm[1][12], ht[1][12];
+    load_hops_all<R, 1, true>(buf2, two, 0, idx, co, hm);
+    load_hops_all<R, 1, true>(buf2, two, 1, idx, co, ht);
+    __syncthreads();
+    mdagm_cells<R, 1, 2>(vm, vt, vn, hm, ht, g, own, co, tau == 0 ? R(-1) : R(1), tau == Nt - 1 ? R(-1) : R(1), buf2,
+                         Vs, o);
+    store_cells<R, 1>(o, out + (size_t)tau * Vs, g, own);
 }
 
 // ---------------------------------------------------------------------------
@@ -473,6 +520,49 @@ static bool use_tiled(const qedhmc_ctx* h, const double* gate) {
 qedhmc_status launch_mdagm(qedhmc_ctx* h, qedhmc_precision prec, const void* in, void* out, const double* gate) {
     if (use_tiled(h, gate)) return launch_mdagm_tiled(h, prec, in, out);
     return prec == QEDHMC_FP64 ? mdagm_t<double>(h, in, out, gate) : mdagm_t<float>(h, in, out, gate);
+}
+
+template <typename R>
+static qedhmc_status mdagm_theta_t(qedhmc_ctx* h, const double* theta, const void* in, void* out) {
+    const Lat& lt = h->lat;
+    const Shape s = shape_of(lt);
+    const size_t lds = 4 * (size_t)lt.Vs * sizeof(cplx<R>);
+    // a thread per cell (more threads to share the sines and cosines leave a
+    // compute unit one workgroup: L = 32 FP32 11.3 against 15.2 us); past 512
+    // cells one workgroup fills a unit anyway, and the wider one wins (L = 48
+    // 24.2 against 27.3 us)
+    const int nt = s.nt <= 512 ? s.nt : 1024;
+    auto run = [&]<int BS>() -> qedhmc_status {
+        QH_TRY(allow_lds(h, k_mdagm_theta<R, BS>, lds));
+        hipEvent_t e0, e1;
+        if (prof_sample(h, sizeof(R) == 4 ? QEDHMC_K_MDAGM_FP32 : QEDHMC_K_MDAGM_FP64, e0, e1))
+            hipExtLaunchKernelGGL((k_mdagm_theta<R, BS>), dim3(slice_grid(lt.Nt)), dim3(nt), lds, h->stream, e0, e1, 0, lt,
+                                  (const cplx<R>*)in, (cplx<R>*)out, theta, coef_of<R>(h->p));
+        else
+            hipLaunchKernelGGL((k_mdagm_theta<R, BS>), dim3(slice_grid(lt.Nt)), dim3(nt), lds, h->stream, lt,
+                               (const cplx<R>*)in, (cplx<R>*)out, theta, coef_of<R>(h->p));
+        QH_HIP(hipGetLastError());
+        return QEDHMC_OK;
+    };
+    if (nt <= 256) return run.template operator()<256>();
+    if (nt <= 512) return run.template operator()<512>();
+    return run.template operator()<1024>();
+}
+
+// Up to this many cells per slice the phases are formed inside M^dag M: FP32
+// L = 24 12.6 -> 10.0 us a call, L = 40 19.2 -> 16.1, L = 48 26.0 -> 24.2,
+// L = 62 46.4 -> 51.9; FP64 L = 24 12.8 -> 10.3, L = 44 32.1 -> 28.2, L = 48
+// (which spills at its 1024 threads) 70.4 -> 72.2.  Below L = 24 a call is bound
+// by the host's launches, one instead of two.
+static int theta_cells(qedhmc_precision prec) { return prec == QEDHMC_FP64 ? 512 : 576; }
+
+qedhmc_status launch_mdagm_theta(qedhmc_ctx* h, qedhmc_precision prec, const double* theta, const void* in, void* out) {
+    const size_t lds = 4 * (size_t)h->lat.Vs * (prec == QEDHMC_FP64 ? sizeof(cplx<double>) : sizeof(cplx<float>));
+    if (h->lat.ncell > theta_cells(prec) || lds > h->max_lds || use_tiled(h, nullptr)) {
+        QH_TRY(ensure_gauge(h, theta, prec));
+        return launch_mdagm(h, prec, in, out, nullptr);
+    }
+    return prec == QEDHMC_FP64 ? mdagm_theta_t<double>(h, theta, in, out) : mdagm_theta_t<float>(h, theta, in, out);
 }
 
 template <typename R>

@@ -652,6 +652,9 @@ qedhmc_status launch_apply_B(qedhmc_ctx* h, qedhmc_precision prec, int tau, cons
 // only when the flag asks for a reliable update (1, 2 or 3; see gate_open)
 qedhmc_status launch_mdagm(qedhmc_ctx* h, qedhmc_precision prec, const void* in, void* out,
                            const double* gate = nullptr);
+// out = M^dag M in at theta, the phases formed on the way where that is faster
+// than rebuilding the cache first (which is then left as it was)
+qedhmc_status launch_mdagm_theta(qedhmc_ctx* h, qedhmc_precision prec, const double* theta, const void* in, void* out);
 qedhmc_status launch_force(qedhmc_ctx* h, qedhmc_precision prec, const double* X, double* F);
 // Per-launch host work done once per kernel (api.hip): allow_lds lets kernel
 // k take up to max_lds bytes of LDS, its static LDS included (every caller
