@@ -190,11 +190,12 @@ qedhmc_status qedhmc_apply_MdagM_noalloc(const qedhmc_params *params,
  * breakdown (non-finite inner products or residual) or when three reliable
  * updates in a row make no progress; qedhmc_last_error says which.  The call
  * synchronises the handle's stream before it returns.  Iterations run as
- * graph-captured chunks; without a preconditioner on slices of at most 1024
- * cells the stop, pause and reliable-update decisions are also taken on the
- * device (otherwise by the host between chunks).  The environment variable
- * QEDHMC_NO_GRAPH (read on every call) makes the host launch every iteration
- * and take every decision itself (same results bit for bit; tests). */
+ * graph-captured chunks; the stop, pause and reliable-update decisions are also
+ * taken on the device on slices of at most 1024 cells without a preconditioner
+ * and of at most 512 with one (otherwise by the host between chunks).  The
+ * environment variable QEDHMC_NO_GRAPH (read on every call) makes the host
+ * launch every iteration itself and, without a preconditioner, take every
+ * decision (same results bit for bit; tests). */
 qedhmc_status qedhmc_cg_solve(qedhmc_t h, const double *theta,
                               const double *rhs, double *x, double tol,
                               int32_t maxit, qedhmc_precision prec,
@@ -250,9 +251,9 @@ qedhmc_status qedhmc_heatbath(qedhmc_t h, uint64_t traj_index, double *mom,
 
 /* One HQMC trajectory: heat bath, eta = M^dag R, n_steps leapfrog steps of
  * length traj_len / n_steps with a solve at every theta (the first from
- * x = 0, each later one started from the previous solution: it solves for the
- * correction to the same absolute target tol |eta|; QEDHMC_WARM_START=0,
- * read per call, starts every solve from x = 0), Metropolis with u from
+ * x = 0, each later one started from the previous solution, to the same
+ * target tol |eta|; QEDHMC_WARM_START=0, read per call, starts every solve
+ * from x = 0), Metropolis with u from
  * Philox.  theta_inout: device double[2][Nt][L][L], overwritten by the
  * proposal on acceptance, unchanged on rejection. */
 qedhmc_status qedhmc_hmc_trajectory(qedhmc_t h, double *theta_inout,

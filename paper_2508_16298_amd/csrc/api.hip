@@ -460,6 +460,12 @@ qedhmc_status qedhmc_hmc_trajectory(qedhmc_t h, double* theta, uint64_t traj, in
         qedhmc_status st = QEDHMC_OK;
         if (!(warm && warm_ok)) {
             st = solve_at(h, th, eta, X, tol, maxit, prec, pc, &it, &rel, &nr, &sw);
+        } else if (pc == QEDHMC_PC_PAPER && pcg_warm_ok(h)) {
+            // the solver itself starts from X
+            QH_TRY(ensure_gauge(h, th, QEDHMC_FP64));
+            if (prec != QEDHMC_FP64) QH_TRY(ensure_gauge(h, th, QEDHMC_FP32));
+            st = pcg_solve_impl(h, eta, X, tol, maxit, prec, &it, &rel, &nr, true);
+            if (!std::isfinite(rel)) rel = HUGE_VAL;
         } else {
             QH_TRY(ensure_gauge(h, th, QEDHMC_FP64));
             QH_TRY(launch_mdagm(h, QEDHMC_FP64, X, bres, nullptr));

@@ -25,7 +25,9 @@ enum {
     S_GCUR = 10,   // gamma_i of the current state
     S_STALL = 11,  // batched driver: consecutive updates without progress
     S_LASTUP = 12, // batched driver: 1 + iteration of the last update (0: none)
-    S_NREL = 13,   // batched driver: updates so far
+    S_NREL = 13,   // updates so far (drivers that count them on the device)
+    S_WHY = 14,    // PCG: cause of a failure (WHY_*)
+    S_MAXIT = 15,  // PCG: iteration budget
     S_NSLOT = 16,
 };
 // Record of a solve kept on the device (pipelined drivers of cg.hip and

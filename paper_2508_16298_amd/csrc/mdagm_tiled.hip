@@ -322,7 +322,7 @@ static constexpr int kTileMaxThreads = sizeof(R) == 8 ? 512 : 1024;
 
 // Extra operands of the CG form (PART): with w = out = O u, the partial sums
 // <r,r>, <r,u>, <w,u>, <u,s>, <p,w>, <p,s> of every (slice, tile) over the
-// tile's output cells go to part[kTileParts * (tau * ntile + tile)]; a
+// tile's output cells go to part[q * Nt * ntile + tau * ntile + tile]; a
 // non-zero *stop makes the launch a no-op.
 static constexpr int kTileParts = 7;
 
@@ -458,9 +458,9 @@ __global__ __launch_bounds__(kTileMaxThreads<R>) void k_mdagm_tiled(TiledGeo G, 
                 for (int i = 0; i < nw; i++)
 #pragma unroll
                     for (int q = 0; q < kTileParts - 1; q++) t[q] += red[(kTileParts - 1) * i + q];
-                double* dst = ops.part + (size_t)kTileParts * ((size_t)tau * ntile + tile);
+                double* dst = ops.part + (size_t)tau * ntile + tile;
 #pragma unroll
-                for (int q = 0; q < kTileParts; q++) dst[q] = t[q];
+                for (int q = 0; q < kTileParts - 1; q++) dst[(size_t)q * Nt * ntile] = t[q];
             }
         }
 #pragma unroll

@@ -18,15 +18,25 @@
 // -1 when tau-dtau wraps (antiperiodic), and P = G^dag G as two stencil
 // passes.  P is Hermitian positive definite whenever G is non-singular.
 //
-// PCG, one iteration = four launches (every read of a neighbouring slice
-// crosses a launch boundary, so no buffer is read and written in one launch):
-//   k_pcg_upd   partial sums -> beta, alpha (single reduction phase as in the
-//               unpreconditioned solver, denominator <p,s> expanded);
-//               p = u + beta p, s = w + beta s, x += alpha p, r -= alpha s
-//   k_pc_apply  t = G r
-//   k_pc_apply  u = G^dag t
-//   k_pcg_mv    w = O u and the partials <r,r>, <r,u>, <w,u>, <u,s>, <p,w>, <p,s>
+// PCG, one iteration = three launches in spectral form (every read of a
+// neighbouring slice crosses a launch boundary, so no buffer is read and
+// written in one launch):
+//   k_pcg_upd       partial sums -> beta, alpha (single reduction phase as in
+//                   the unpreconditioned solver, denominator <p,s> expanded);
+//                   p = u + beta p, s = w + beta s, x += alpha p, r -= alpha s;
+//                   the forward DFT of r
+//   k_pcs_tsum_inv  u = P r (k_pcs_tsum and k_pcs_inv on large slices; two
+//                   stencil passes where the spectral form is not built)
+//   k_pcg_mv        w = O u and the partials <r,r>, <r,u>, <w,u>, <u,s>, <p,w>, <p,s>
 // with gamma = <r, P r>; stopping and reliable updates on |r| as in cg.hip.
+//
+// Up to 512 cells per slice the same three launches also carry out the
+// reliable updates (no gated launches beside them, and none wasted after a
+// pause): an update kernel that pauses the recursion leaves its request in the
+// slot; the matvec of that triple, which would have nothing to do, forms
+// r = rhs - O x in FP64 and s = O p instead; the next update kernel decides on
+// the true residual and, where the solve goes on, transforms the new r.  A
+// solve starts as if it had just paused.
 #include <algorithm>
 #include <vector>
 
@@ -42,7 +52,7 @@ static constexpr int kBuildNt = 24;
 static constexpr int kCapTau = QEDHMC_PC_TAU_REACH;  // tau reach of G (QEDHMC_PC_CAP overrides, up to kCapMax)
 static constexpr int kCapMax = 12;
 static constexpr double kThresh = 1e-3;
-static constexpr int kNP7 = 7;  // PCG partials: <r,r>, <r,u>, <w,u>, <u,s>, <p,w>, <p,s>, unused
+static constexpr int kNP6 = 6;  // PCG partials: <r,r>, <r,u>, <w,u>, <u,s>, <p,w>, <p,s>
 
 static constexpr int kPcSlots = 16;  // tau offsets per stencil pass at most (0 <= dt <= kCapMax, plus spare)
 
@@ -984,11 +994,12 @@ template <typename R, int NY, int NX, bool TL>
 __global__ __launch_bounds__(512) void k_pcs_tsum_inv(PcSpecGeo g, const cpair<R>* __restrict__ H,
                                                       const R* __restrict__ tab, const cplx<R>* __restrict__ in,
                                                       cplx<R>* __restrict__ out, const double* __restrict__ stop) {
-    if (stop && *stop != 0.0) return;
     extern __shared__ __align__(32) unsigned char smem[];
     R* V = reinterpret_cast<R*>(smem);
     const int tau = slice_of_block(blockIdx.x, g.Nt), nk = g.nk;
     if (tau < 0) return;
+    // (looked at once the first momentum's sum is in LDS: one round trip less)
+    const double done = stop ? *stop : 0.0;
     const R* tb = sp_tables<R, TL>(tab, V + g.L * g.ld, g);
     constexpr int CH = sizeof(R) == 8 ? 3 : 6;  // offsets per load batch
     static_assert(kSpTau % CH == 0, "whole batches");
@@ -1021,6 +1032,7 @@ __global__ __launch_bounds__(512) void k_pcs_tsum_inv(PcSpecGeo g, const cpair<R
         sp_up<R>(z, hc0, hc1, vc);
         const int y = k / g.Lh;
         *reinterpret_cast<cpair<R>*>(V + y * g.ld + 4 * (k - y * g.Lh)) = z;
+        if (done != 0.0) return;
     }
     sp_inverse<R, NY, NX>(V, g, tb, out + (size_t)tau * g.Vs);
 }
@@ -1240,19 +1252,21 @@ struct PcgBufs {
     cplx<double>* x;
     const cplx<double>* rhs;
     const cplx<double>* Ox;
-    double* part;   // [nparts][kNP7]: per slice, or per (slice, tile) for the tiled matvec
+    double* part;   // [kNP6][nparts]: per slice, or per (slice, tile) for the tiled matvec
     double* partb;  // [Nt]: |rhs|^2 or the FP64 true |r|^2
     int nparts;
 };
 
-// r = rhs, x = p = s = 0; partb = |rhs|^2 per slice
+// r = rhs (kept in B.rhs), x = p = s = 0; partb = |rhs|^2 per slice
 template <typename R>
-__global__ __launch_bounds__(256) void k_pcg_start(Lat lt, PcgBufs<R> B) {
+__global__ __launch_bounds__(256) void k_pcg_start(Lat lt, PcgBufs<R> B, const cplx<double>* __restrict__ rhs,
+                                                   cplx<double>* __restrict__ keep) {
     __shared__ double red[64];
     const size_t base = (size_t)blockIdx.x * lt.Vs;
     double b2 = 0.0;
     for (int k = threadIdx.x; k < lt.Vs; k += blockDim.x) {
-        const cplx<double> b = B.rhs[base + k];
+        const cplx<double> b = rhs[base + k];
+        keep[base + k] = b;
         B.r[base + k] = mk<R>((R)b.re, (R)b.im);
         B.p[base + k] = mk<R>(0, 0);
         B.s[base + k] = mk<R>(0, 0);
@@ -1265,7 +1279,8 @@ __global__ __launch_bounds__(256) void k_pcg_start(Lat lt, PcgBufs<R> B) {
 }
 
 // slot 0 from the |rhs|^2 partials
-__global__ void k_pcg_init_slot(double* __restrict__ scal, const double* __restrict__ partb, int Nt, double tol2) {
+__global__ void k_pcg_init_slot(double* __restrict__ scal, const double* __restrict__ partb, int Nt, double tol2,
+                                int maxit) {
     __shared__ double red[64];
     double v[1] = {0.0};
     for (int t = threadIdx.x; t < Nt; t += blockDim.x) v[0] += partb[t];
@@ -1273,6 +1288,7 @@ __global__ void k_pcg_init_slot(double* __restrict__ scal, const double* __restr
     if (threadIdx.x < S_NSLOT) {
         double val = 0.0;
         if (threadIdx.x == S_FIRST || threadIdx.x == S_GPREV || threadIdx.x == S_APREV) val = 1.0;
+        if (threadIdx.x == S_MAXIT) val = maxit;
         scal[threadIdx.x] = val;
     }
     __syncthreads();
@@ -1283,52 +1299,127 @@ __global__ void k_pcg_init_slot(double* __restrict__ scal, const double* __restr
     }
 }
 
-template <int K>
-__device__ __forceinline__ void reduce_k(const double* __restrict__ part, int Nt, double* red, double* bc,
-                                         double (&out)[K]) {
-    double v[K];
+// The start of a solve whose reliable updates run inside the triples: B.rhs =
+// rhs, r = rhs - O x0 (FP64; x0 null: zero start, r = rhs), x = x0, p = s = 0,
+// partb = |r|^2 and part[0] = |rhs|^2 per slice, and a slot that looks like one
+// that has just paused (S_B2 < 0: |rhs|^2 to be taken from part; S_TARGET
+// holds tol^2 until then).  Budget and tolerance live in the slot, so that the
+// graphs of the triples serve every solve of a handle.
+template <typename R, int MC, int NB, int BS>
+__global__ __launch_bounds__(BS) void k_pcg_begin(Lat lt, PcgBufs<R> B, const cplx<double>* __restrict__ gauge64,
+                                                  Coef<double> co64, const cplx<double>* __restrict__ rhs,
+                                                  cplx<double>* __restrict__ keep, const cplx<double>* __restrict__ x0,
+                                                  double* __restrict__ scal, double tol2, int maxit) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    cplx<double>* buf2 = reinterpret_cast<cplx<double>*>(smem);
+    double* red = reinterpret_cast<double*>(smem + (size_t)NB * 2 * lt.Vs * sizeof(cplx<double>));
+    const int tau = slice_of_block(blockIdx.x, lt.Nt);
+    if (blockIdx.x == 0 && threadIdx.x < S_NSLOT) {
+        const int k = threadIdx.x;
+        double val = 0.0;
+        if (k == S_DONE) val = 2.0;
+        if (k == S_B2 || k == S_NREL) val = -1.0;
+        if (k == S_GPREV || k == S_APREV) val = 1.0;
+        if (k == S_TARGET) val = tol2;
+        if (k == S_MAXIT) val = maxit;
+        scal[k] = val;
+    }
+    if (tau < 0) return;
+    SliceCtx<MC> c;
+    slice_ctx<MC>(lt, c, tau, whole_block_tile(smem, red));
+    const size_t Vs = lt.Vs;
+    Cells<double, MC> b, o;
+    load_cells<double, MC>(b, rhs + c.tau * Vs, c.g, c.own);
+    store_cells<double, MC>(b, keep + c.tau * Vs, c.g, c.own);
+    double v[2] = {0.0, dot_cells<double, MC>(b, b, c.own)};
+    Cells<double, MC> xt;
 #pragma unroll
-    for (int k = 0; k < K; k++) v[k] = 0.0;
-    for (int t = threadIdx.x; t < Nt; t += blockDim.x)
+    for (int m = 0; m < MC; m++)
 #pragma unroll
-        for (int k = 0; k < K; k++) v[k] += part[K * t + k];
-    block_sumk<K>(v, red);
-    if (threadIdx.x == 0)
+        for (int q = 0; q < 4; q++) xt.v[m][q] = o.v[m][q] = mk<double>(0, 0);
+    if (x0) {
+        cplx<double> hm[MC][12], ht[MC][12];
+        hops_of<double, MC>(gauge64, lt, c.tm, c.idx, co64, hm);
+        hops_of<double, MC>(gauge64, lt, c.tau, c.idx, co64, ht);
+        Cells<double, MC> xm, xn;
+        load_cells<double, MC>(xm, x0 + c.tm * Vs, c.g, c.own);
+        load_cells<double, MC>(xt, x0 + c.tau * Vs, c.g, c.own);
+        load_cells<double, MC>(xn, x0 + c.tp * Vs, c.g, c.own);
+        mdagm_cells<double, MC, NB>(xm, xt, xn, hm, ht, c.g, c.own, co64, c.tau == 0 ? -1.0 : 1.0,
+                                    c.tau == lt.Nt - 1 ? -1.0 : 1.0, buf2, lt.Vs, o);
+    }
+    Cells<R, MC> r, zero;
 #pragma unroll
-        for (int k = 0; k < K; k++) bc[k] = v[k];
-    __syncthreads();
+    for (int m = 0; m < MC; m++)
 #pragma unroll
-    for (int k = 0; k < K; k++) out[k] = bc[k];
+        for (int q = 0; q < 4; q++) {
+            const double re = b.v[m][q].re - o.v[m][q].re, im = b.v[m][q].im - o.v[m][q].im;
+            if (c.own[m]) v[0] += re * re + im * im;
+            r.v[m][q] = mk<R>((R)re, (R)im);
+            zero.v[m][q] = mk<R>(0, 0);
+        }
+    store_cells<double, MC>(xt, B.x + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(r, B.r + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(zero, B.p + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(zero, B.s + c.tau * Vs, c.g, c.own);
+    block_sumk<2>(v, red);
+    if (threadIdx.x == 0) {
+        B.partb[c.tau] = v[0];
+        B.part[c.tau] = v[1];
+    }
 }
 
 // One slice per block (dealt to the XCDs as slice_of_block deals them):
 // scalars from the partials, then the elementwise update.
-// DFT: the block then also transforms the new r of its slice (both parity
-// planes, through LDS) into vhat, the first step of the spectral P r; vhat
-// may be u itself, whose slice only this block reads.
-// Latency: once the slot says the solve runs, this block's share of the
-// partials and the vectors of the thread's first kUpdPre sites are requested
-// together (one round trip to memory instead of two in a row).
+// DFT (NY > 0): the block then also transforms the new r of its slice (both
+// parity planes, through LDS) into vhat, the first step of the spectral P r;
+// vhat may be u itself, whose slice only this block reads.
+// updates: the reliable updates run inside the triples; a slot that asks for
+// one is decided here (converged, failed with S_WHY, or resume), and a solve
+// that resumes transforms the replaced r.
+// Latency: every load (the partials first: each wavefront adds one of the
+// sums, then the vectors of the thread's first kUpdPre sites) is requested
+// before the slot is looked at, one round trip to memory for all of them, so
+// that a launch of a finished solve costs as much as one that works; those are
+// few where the updates run inside the triples.  8.5 -> 6.6 us at L = 24, N_tau
+// = 240 (FP32).
 static constexpr int kUpdPre = 4;
 
 template <typename R, int NY, int NX, bool TL>
 __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBufs<R> B, double* __restrict__ scal, int kpar,
-                                                  int mixed, int maxit, PcSpecGeo sg, const R* __restrict__ tab,
-                                                  cplx<R>* __restrict__ vhat) {
+                                                  int mixed, int updates, PcSpecGeo sg,
+                                                  const R* __restrict__ tab, cplx<R>* __restrict__ vhat) {
     constexpr bool DFT = NY > 0;
-    __shared__ double red[kNP7 * 16 + 16];
+    __shared__ double red[8];
     extern __shared__ __align__(32) unsigned char smem[];
     R* V = reinterpret_cast<R*>(smem);  // the new r, as the transform reads it
     const double* sin_ = scal + S_NSLOT * kpar;
     double* sout = scal + S_NSLOT * (kpar ^ 1);
     const int tau = slice_of_block(blockIdx.x, lt.Nt);
     const size_t base = (size_t)(tau < 0 ? 0 : tau) * lt.Vs;
-    if (sin_[S_DONE] != 0.0) {
+    if (!updates && sin_[S_DONE] != 0.0) {
         if (blockIdx.x == 0 && threadIdx.x < S_NSLOT) sout[threadIdx.x] = sin_[threadIdx.x];
         return;
     }
-    // requests, all in flight together: the vectors first (the partials'
-    // loop waits inside)
+    double sl[S_NSLOT];
+#pragma unroll
+    for (int k = 0; k < S_NSLOT; k++) sl[k] = sin_[k];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
+    // sum q over the partials: q < 6 the inner products, q = 6 partb
+    auto partial = [&](int q) {
+        const double* src = q < kNP6 ? B.part + (size_t)q * B.nparts : B.partb;
+        const int n = q < kNP6 ? B.nparts : lt.Nt;
+        double s = 0.0;
+        for (int i0 = lane; i0 < n; i0 += 4 * 64) {
+            double a[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) a[u] = i0 + 64 * u < n ? src[i0 + 64 * u] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 4; u++) s += a[u];
+        }
+        return s;
+    };
+    double sum = wave <= kNP6 ? partial(wave) : 0.0;
     cplx<R> p0[kUpdPre], u0[kUpdPre], s0[kUpdPre], w0[kUpdPre], r0[kUpdPre];
     cplx<double> x0[kUpdPre];
 #pragma unroll
@@ -1344,59 +1435,100 @@ __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBu
     }
     const R* tb = nullptr;
     if constexpr (DFT) tb = sp_tables<R, TL>(tab, V + sg.L * sg.ld, sg);
-    double sl[S_NSLOT];
-#pragma unroll
-    for (int k = 0; k < S_NSLOT; k++) sl[k] = sin_[k];
-    double pv[kNP7];
-#pragma unroll
-    for (int k = 0; k < kNP7; k++) pv[k] = 0.0;
-    for (int t = threadIdx.x; t < B.nparts; t += blockDim.x)
-#pragma unroll
-        for (int k = 0; k < kNP7; k++) pv[k] += B.part[kNP7 * t + k];
-    double pr[kNP7];
-    block_sumk<kNP7>(pv, red);
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int k = 0; k < kNP7; k++) red[kNP7 * 16 + k] = pv[k];
+    for (int q = wave; q <= kNP6; q += nw) {
+        sum = wave_sum_f64(q == wave ? sum : partial(q));
+        if (lane == 63) red[q] = sum;
+    }
     __syncthreads();
+    double pr[kNP6 + 1];
 #pragma unroll
-    for (int k = 0; k < kNP7; k++) pr[k] = red[kNP7 * 16 + k];
-    const double rr = pr[0], gam = pr[1], del = pr[2];
-    const int it = (int)sl[S_ITERS];
-    int stop = 0;
+    for (int k = 0; k <= kNP6; k++) pr[k] = red[k];
+    const double rr = pr[0], gam = pr[1], del = pr[2], done = sl[S_DONE];
+    const int it = (int)sl[S_ITERS], maxit = (int)sl[S_MAXIT];
     double alpha = 0.0, beta = 0.0;
-    const bool first = sl[S_FIRST] != 0.0;
-    if (!isfinite(rr) || !isfinite(gam) || !isfinite(del))
-        stop = 4;
-    else if (rr <= sl[S_TARGET])
-        stop = 1;
-    else if (it >= maxit)
-        stop = 2;  // the budget is used: the update decides
-    else if (mixed && (rr <= kDecade2 * sl[S_RRUPD] || it - (int)sl[S_ITUPD] >= kCap))
-        stop = 2;
-    else {
-        beta = first ? 0.0 : gam / sl[S_GPREV];
-        const double den = first ? del : del + beta * (pr[3] + pr[4]) + beta * beta * pr[5];
-        if (!(den > 0.0))
-            stop = 3;
-        else
-            alpha = gam / den;
-    }
-    if (blockIdx.x == 0 && threadIdx.x < S_NSLOT) {
-        double v = sin_[threadIdx.x];
-        if (stop) {
-            if (threadIdx.x == S_DONE) v = (double)stop;
-            if (threadIdx.x == S_GCUR) v = rr;
-        } else {
-            if (threadIdx.x == S_GPREV) v = gam;
-            if (threadIdx.x == S_APREV) v = alpha;
-            if (threadIdx.x == S_ITERS) v = (double)(it + 1);
-            if (threadIdx.x == S_FIRST) v = 0.0;
-            if (threadIdx.x == S_GCUR) v = rr;
+    bool go = false, resume = false;
+    if (done == 0.0) {
+        int stop = 0;
+        const bool first = sl[S_FIRST] != 0.0;
+        if (!isfinite(rr) || !isfinite(gam) || !isfinite(del))
+            stop = 4;
+        else if (rr <= sl[S_TARGET])
+            stop = 1;
+        else if (it >= maxit)
+            stop = 2;  // the budget is used: the update decides
+        else if (mixed && (rr <= kDecade2 * sl[S_RRUPD] || it - (int)sl[S_ITUPD] >= kCap))
+            stop = 2;
+        else {
+            beta = first ? 0.0 : gam / sl[S_GPREV];
+            const double den = first ? del : del + beta * (pr[3] + pr[4]) + beta * beta * pr[5];
+            if (!(den > 0.0))
+                stop = 3;
+            else
+                alpha = gam / den;
         }
-        sout[threadIdx.x] = v;
+        go = stop == 0;
+        sl[S_GCUR] = rr;
+        if (stop) {
+            sl[S_DONE] = (double)stop;
+            if (stop == 4) sl[S_WHY] = WHY_BREAKDOWN;
+        } else {
+            sl[S_GPREV] = gam;
+            sl[S_APREV] = alpha;
+            sl[S_ITERS] = (double)(it + 1);
+            sl[S_FIRST] = 0.0;
+        }
+    } else if (gate_open(done)) {
+        // (updates) the replaced residual decides
+        const double tr = pr[kNP6];
+        const bool begin = sl[S_B2] < 0.0;
+        if (begin) {
+            sl[S_B2] = rr;  // the start kernel's |rhs|^2
+            sl[S_TARGET] *= rr;  // tol^2 until here
+        }
+        const int stall = (it + 1 == (int)sl[S_LASTUP]) ? (int)sl[S_STALL] + 1 : 0;
+        sl[S_STALL] = begin ? 0 : stall;
+        sl[S_LASTUP] = begin ? 0 : it + 1;
+        sl[S_NREL] += 1.0;
+        sl[S_TRUE] = tr;
+        sl[S_GCUR] = tr;
+        if (!isfinite(tr) || !isfinite(sl[S_B2])) {
+            sl[S_DONE] = 4.0;
+            sl[S_WHY] = begin ? WHY_BREAKDOWN : WHY_NONFINITE;
+        } else if (tr <= sl[S_TARGET]) {
+            sl[S_DONE] = 5.0;
+            if (begin) sl[S_NREL] = 1.0;  // the start was this solve's check
+        } else if (!begin && (it >= maxit || stall >= 3)) {
+            sl[S_DONE] = 4.0;
+            sl[S_WHY] = it >= maxit ? WHY_BUDGET : WHY_STALL;
+        } else {
+            resume = true;
+            sl[S_DONE] = 0.0;
+            if (begin || !mixed || done == 3.0) sl[S_FIRST] = 1.0;
+            sl[S_ITUPD] = it;
+            sl[S_RRUPD] = tr;
+        }
     }
-    if (stop || tau < 0) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+#pragma unroll
+        for (int k = 0; k < S_NSLOT; k++) sout[k] = sl[k];
+    if (tau < 0 || !(go || resume)) return;
+    if (resume) {
+        if constexpr (DFT) {
+            auto place = [&](int k, cplx<R> v) {
+                const int y = k / sg.L;
+                *reinterpret_cast<cplx<R>*>(V + y * sg.ld + 2 * (k - y * sg.L)) = v;
+            };
+#pragma unroll
+            for (int j = 0; j < kUpdPre; j++) {
+                const int k = (int)threadIdx.x + j * (int)blockDim.x;
+                if (k < lt.Vs) place(k, r0[j]);
+            }
+            for (int k = (int)threadIdx.x + kUpdPre * (int)blockDim.x; k < lt.Vs; k += blockDim.x)
+                place(k, B.r[base + k]);
+            sp_forward<R, NY, NX>(V, sg, tb, vhat + base);
+        }
+        return;
+    }
     const R a = (R)alpha, b = (R)beta;
     auto update = [&](int k, cplx<R> pk, cplx<R> uk, cplx<R> sk, cplx<R> wk, cplx<R> rk, cplx<double> xv) {
         const size_t i = base + k;
@@ -1426,21 +1558,30 @@ __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBu
     if constexpr (DFT) sp_forward<R, NY, NX>(V, sg, tb, vhat + base);
 }
 
-// w = O u (own slice) and the partials of the next iteration
-template <typename R, int MC, int NB, int BS>
+// w = O u (own slice) and the partials of the next iteration; or (UPD), where
+// the slot asks for a reliable update, r = rhs - O x (FP64, partb its norm) and
+// s = O p.  flag: the slot's stop flag (null: none).  Its own slice's vectors
+// of the inner products are requested with u with one cell a thread and at
+// most 512 threads (1024-thread workgroups would spill), else after the matvec;
+// the slot is looked at once they are on their way.  A workgroup has a CU to
+// itself here, so the time is one round trip to memory and the operator's chain
+// of exchanges: 7.3 us at L = 24, N_tau = 240 (FP32).  No launch bound below 512
+// registers is set: with 168 the FP32 form spills 184 and takes 15.7 us.
+template <typename R, int MC, int NB, int BS, bool UPD>
 __global__ __launch_bounds__(BS) void k_pcg_mv(Lat lt, PcgBufs<R> B, const cplx<R>* __restrict__ gauge, Coef<R> co,
-                                               const double* __restrict__ stop) {
-    // (testing the flag only once the slice's data is in flight measured
-    // slower: the launches after a pause then load everything too)
-    if (stop && *stop != 0.0) return;
+                                               const cplx<double>* __restrict__ gauge64, Coef<double> co64,
+                                               const double* __restrict__ flag) {
     extern __shared__ __align__(16) unsigned char smem[];
     cplx<R>* buf2 = reinterpret_cast<cplx<R>*>(smem);
     double* red = reinterpret_cast<double*>(smem + (size_t)NB * 2 * lt.Vs * sizeof(cplx<R>));
     const int tau = slice_of_block(blockIdx.x, lt.Nt);
     if (tau < 0) return;
+    const double done = flag ? *flag : 0.0;
+    if (!UPD && done != 0.0) return;
     SliceCtx<MC> c;
     slice_ctx<MC>(lt, c, tau, whole_block_tile(smem, red));
     const size_t Vs = lt.Vs;
+    const R em = c.tau == 0 ? R(-1) : R(1), et = c.tau == lt.Nt - 1 ? R(-1) : R(1);
     cplx<R> hm[MC][12], ht[MC][12];
     hops_of<R, MC>(gauge, lt, c.tm, c.idx, co, hm);
     hops_of<R, MC>(gauge, lt, c.tau, c.idx, co, ht);
@@ -1448,19 +1589,78 @@ __global__ __launch_bounds__(BS) void k_pcg_mv(Lat lt, PcgBufs<R> B, const cplx<
     load_cells<R, MC>(um, B.u + c.tm * Vs, c.g, c.own);
     load_cells<R, MC>(ut, B.u + c.tau * Vs, c.g, c.own);
     load_cells<R, MC>(un, B.u + c.tp * Vs, c.g, c.own);
-    // the own-slice vectors of the inner products: with one cell a thread
-    // and at most 512 threads requested with u (one round trip less);
-    // otherwise after the matvec so they are not live across it (fewer
-    // registers)
     Cells<R, MC> rt, pt, st;
-    constexpr bool early = MC == 1 && BS <= 512;  // 1024-thread workgroups would spill
+    constexpr bool early = MC == 1 && BS <= 512;
     if constexpr (early) {
         load_cells<R, MC>(rt, B.r + c.tau * Vs, c.g, c.own);
         load_cells<R, MC>(pt, B.p + c.tau * Vs, c.g, c.own);
         load_cells<R, MC>(st, B.s + c.tau * Vs, c.g, c.own);
     }
-    mdagm_cells<R, MC, NB>(um, ut, un, hm, ht, c.g, c.own, co, c.tau == 0 ? R(-1) : R(1),
-                           c.tau == lt.Nt - 1 ? R(-1) : R(1), buf2, lt.Vs, w);
+    if (UPD && done != 0.0) {
+        if (!gate_open(done)) return;
+        if constexpr (sizeof(R) == 8) {
+            // x takes the place of u below (an FP64 solve restarts after every
+            // update, so s is not needed)
+            load_cells<R, MC>(um, reinterpret_cast<const cplx<R>*>(B.x) + c.tm * Vs, c.g, c.own);
+            load_cells<R, MC>(ut, reinterpret_cast<const cplx<R>*>(B.x) + c.tau * Vs, c.g, c.own);
+            load_cells<R, MC>(un, reinterpret_cast<const cplx<R>*>(B.x) + c.tp * Vs, c.g, c.own);
+        } else if constexpr (UPD) {
+            static_assert(NB == 2, "one FP64 exchange buffer fits the two FP32 ones");
+            Cells<double, MC> b, o;
+            load_cells<double, MC>(b, B.rhs + c.tau * Vs, c.g, c.own);
+            {
+                cplx<double> gm[MC][12], gt[MC][12];
+                hops_of<double, MC>(gauge64, lt, c.tm, c.idx, co64, gm);
+                hops_of<double, MC>(gauge64, lt, c.tau, c.idx, co64, gt);
+                Cells<double, MC> xm, xt, xn;
+                load_cells<double, MC>(xm, B.x + c.tm * Vs, c.g, c.own);
+                load_cells<double, MC>(xt, B.x + c.tau * Vs, c.g, c.own);
+                load_cells<double, MC>(xn, B.x + c.tp * Vs, c.g, c.own);
+                mdagm_cells<double, MC, 1>(xm, xt, xn, gm, gt, c.g, c.own, co64, (double)em, (double)et,
+                                            reinterpret_cast<cplx<double>*>(smem), lt.Vs, o);
+            }
+            double v[1] = {0.0};
+            Cells<R, MC> r, pm, po, pn;
+#pragma unroll
+            for (int m = 0; m < MC; m++)
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const double re = b.v[m][q].re - o.v[m][q].re, im = b.v[m][q].im - o.v[m][q].im;
+                    if (c.own[m]) v[0] += re * re + im * im;
+                    r.v[m][q] = mk<R>((R)re, (R)im);
+                }
+            store_cells<R, MC>(r, B.r + c.tau * Vs, c.g, c.own);
+            block_sumk<1>(v, red);
+            if (threadIdx.x == 0) B.partb[c.tau] = v[0];
+            load_cells<R, MC>(pm, B.p + c.tm * Vs, c.g, c.own);
+            load_cells<R, MC>(po, B.p + c.tau * Vs, c.g, c.own);
+            load_cells<R, MC>(pn, B.p + c.tp * Vs, c.g, c.own);
+            // (fetched again rather than held across the FP64 operator)
+            cplx<R> gm[MC][12], gt[MC][12];
+            hops_of<R, MC>(gauge, lt, c.tm, c.idx, co, gm);
+            hops_of<R, MC>(gauge, lt, c.tau, c.idx, co, gt);
+            __syncthreads();  // the exchange buffers are reused
+            mdagm_cells<R, MC, NB>(pm, po, pn, gm, gt, c.g, c.own, co, em, et, buf2, lt.Vs, w);
+            store_cells<R, MC>(w, B.s + c.tau * Vs, c.g, c.own);
+            return;
+        }
+    }
+    mdagm_cells<R, MC, NB>(um, ut, un, hm, ht, c.g, c.own, co, em, et, buf2, lt.Vs, w);
+    if constexpr (UPD && sizeof(R) == 8) {
+        if (done != 0.0) {
+            Cells<R, MC> b;
+            load_cells<R, MC>(b, reinterpret_cast<const cplx<R>*>(B.rhs) + c.tau * Vs, c.g, c.own);
+#pragma unroll
+            for (int m = 0; m < MC; m++)
+#pragma unroll
+                for (int q = 0; q < 4; q++) b.v[m][q] = csub(b.v[m][q], w.v[m][q]);
+            store_cells<R, MC>(b, B.r + c.tau * Vs, c.g, c.own);
+            double v[1] = {dot_cells<R, MC>(b, b, c.own)};
+            block_sumk<1>(v, red);
+            if (threadIdx.x == 0) B.partb[c.tau] = v[0];
+            return;
+        }
+    }
     store_cells<R, MC>(w, B.w + c.tau * Vs, c.g, c.own);
     if constexpr (!early) {
         load_cells<R, MC>(rt, B.r + c.tau * Vs, c.g, c.own);
@@ -1468,21 +1668,27 @@ __global__ __launch_bounds__(BS) void k_pcg_mv(Lat lt, PcgBufs<R> B, const cplx<
         load_cells<R, MC>(st, B.s + c.tau * Vs, c.g, c.own);
     }
     const Cells<R, MC>& u0 = ut;  // the matvec reads its own slice without changing it
-    double v[kNP7] = {dot_cells<R, MC>(rt, rt, c.own), dot_cells<R, MC>(rt, u0, c.own),
+    double v[kNP6] = {dot_cells<R, MC>(rt, rt, c.own), dot_cells<R, MC>(rt, u0, c.own),
                       dot_cells<R, MC>(w, u0, c.own),  dot_cells<R, MC>(u0, st, c.own),
-                      dot_cells<R, MC>(pt, w, c.own),  dot_cells<R, MC>(pt, st, c.own), 0.0};
-    block_sumk<kNP7>(v, red);
-    if (threadIdx.x == 0)
+                      dot_cells<R, MC>(pt, w, c.own),  dot_cells<R, MC>(pt, st, c.own)};
 #pragma unroll
-        for (int k = 0; k < kNP7; k++) B.part[kNP7 * (size_t)c.tau + k] = v[k];
+    for (int k = 0; k < kNP6; k++) v[k] = wave_sum_f64(v[k]);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (lane == 63)
+#pragma unroll
+        for (int k = 0; k < kNP6; k++) red[kNP6 * wv + k] = v[k];
+    __syncthreads();
+    if (threadIdx.x < kNP6) {
+        double t = 0.0;
+        const int nw = (int)(blockDim.x + 63) >> 6;
+        for (int i = 0; i < nw; i++) t += red[kNP6 * i + threadIdx.x];
+        B.part[(size_t)threadIdx.x * B.nparts + c.tau] = t;
+    }
 }
 
-// r = rhs - O x from the FP64 O x; partb = FP64 |rhs - O x|^2 per slice.
-// gate (nullable): a slot's stop flag; the launch is a no-op unless it asks
-// for a reliable update.
+// r = rhs - O x from the FP64 O x; partb = FP64 |rhs - O x|^2 per slice
 template <typename R>
-__global__ __launch_bounds__(256) void k_pcg_rep(Lat lt, PcgBufs<R> B, const double* __restrict__ gate) {
-    if (gate && !gate_open(*gate)) return;
+__global__ __launch_bounds__(256) void k_pcg_rep(Lat lt, PcgBufs<R> B) {
     __shared__ double red[64];
     const size_t base = (size_t)blockIdx.x * lt.Vs;
     double t2 = 0.0;
@@ -1504,7 +1710,7 @@ __global__ void k_pcg_check(double* __restrict__ scal, int kpar, const double* _
     __shared__ double red[64];
     double v[2] = {0.0, 0.0};
     for (int t = threadIdx.x; t < Nt; t += blockDim.x) v[0] += partb[t];
-    for (int t = threadIdx.x; t < nparts; t += blockDim.x) v[1] += part[kNP7 * t];
+    for (int t = threadIdx.x; t < nparts; t += blockDim.x) v[1] += part[t];
     block_sumk<2>(v, red);
     if (threadIdx.x == 0) {
         double* sl = scal + S_NSLOT * kpar;
@@ -1520,83 +1726,26 @@ __global__ void k_pcg_check(double* __restrict__ scal, int kpar, const double* _
     }
 }
 
-// skip = 0 when the slot's flag asks for a reliable update, else 1: the stop
-// flag of the gated preconditioner and matvec of the update
-__global__ void k_pcg_gate(const double* __restrict__ flag, double* __restrict__ skip) {
-    if (threadIdx.x == 0) *skip = gate_open(*flag) ? 0.0 : 1.0;
-}
-
-// The reliable-update decision on the device (pipelined driver), after the
-// gated replacement: converged (5) when the FP64 true residual meets the
-// target; failed (4) on a non-finite residual, the iteration budget used or
-// no progress across three updates, or a breakdown flagged by the recursion;
-// otherwise resume (0; restart with beta = 0 after a non-positive
-// denominator, and after every update with restart_all).  A solve already
-// final is left as it is.  The record is mirrored to out (pinned host
-// memory).
-__global__ void k_pcg_check_dev(double* __restrict__ scal, int kpar, const double* __restrict__ part, int nparts,
-                                const double* __restrict__ partb, int Nt, int maxit, int restart_all,
-                                double* __restrict__ rec, double* __restrict__ out) {
-    __shared__ double red[64];
-    double* sl = scal + S_NSLOT * kpar;
-    const double done = sl[S_DONE];
-    const int it = (int)sl[S_ITERS];
-    int nd = -1, why = 0;
-    double est = sl[S_GCUR];
-    if (done == 4.0 && rec[CR_DONE] != 4.0) {
-        nd = 4;
-        why = WHY_BREAKDOWN;
-    }
-    if (gate_open(done)) {
-        double v[2] = {0.0, 0.0};
-        for (int t = threadIdx.x; t < Nt; t += blockDim.x) v[0] += partb[t];
-        for (int t = threadIdx.x; t < nparts; t += blockDim.x) v[1] += part[kNP7 * t];
-        block_sumk<2>(v, red);
-        if (threadIdx.x == 0) {
-            const double tr = v[0];
-            const int stall = (it + 1 == (int)sl[S_LASTUP]) ? (int)sl[S_STALL] + 1 : 0;
-            sl[S_STALL] = stall;
-            sl[S_LASTUP] = it + 1;
-            sl[S_NREL] += 1.0;
-            sl[S_TRUE] = tr;
-            est = tr;
-            if (!isfinite(tr)) {
-                nd = 4;
-                why = WHY_NONFINITE;
-            } else if (tr <= sl[S_TARGET]) {
-                nd = 5;
-            } else if (it >= maxit || stall >= 3) {
-                nd = 4;
-                why = it >= maxit ? WHY_BUDGET : WHY_STALL;
-            } else {
-                nd = 0;
-                if (restart_all || done == 3.0) sl[S_FIRST] = 1.0;
-                sl[S_ITUPD] = it;
-                sl[S_RRUPD] = v[1];
-            }
-        }
-    }
+// a slot to a solve's record in pinned host memory
+__global__ void k_pcg_record(const double* __restrict__ sl, double* __restrict__ out) {
     if (threadIdx.x == 0) {
-        rec[CR_ITERS] = it;
-        rec[CR_B2] = sl[S_B2];
-        rec[CR_EST] = est;
-        if (nd >= 0) {
-            sl[S_DONE] = nd;
-            rec[CR_TRUE] = sl[S_TRUE];
-            rec[CR_NREL] = sl[S_NREL];
-            rec[CR_DONE] = nd;
-            rec[CR_WHY] = why;
-        }
-#pragma unroll
-        for (int k = 0; k < CR_N; k++) out[k] = rec[k];
+        out[CR_ITERS] = sl[S_ITERS];
+        out[CR_TRUE] = sl[S_TRUE];
+        out[CR_B2] = sl[S_B2];
+        out[CR_NREL] = sl[S_NREL];
+        out[CR_WHY] = sl[S_WHY];
+        out[CR_EST] = sl[S_GCUR];
+        out[CR_DONE] = sl[S_DONE];
     }
 }
 
 // ---------------------------------------------------------------------------
 // Host driver
 // ---------------------------------------------------------------------------
+// The solver keeps its right-hand side and solution in the handle's workspace
+// (ws[2], ws[7]), so captured graphs do not depend on a caller's buffers.
 template <typename R>
-static PcgBufs<R> pbufs_of(qedhmc_ctx* h, const double* rhs, double* x) {
+static PcgBufs<R> pbufs_of(qedhmc_ctx* h) {
     PcgBufs<R> B;
     const size_t N = (size_t)h->lat.Nt * h->lat.Vs;
     cplx<R>* base = reinterpret_cast<cplx<R>*>(h->cg_arena);
@@ -1606,53 +1755,66 @@ static PcgBufs<R> pbufs_of(qedhmc_ctx* h, const double* rhs, double* x) {
     B.u = base + 3 * N;
     B.w = base + 4 * N;
     B.t = base + 5 * N;
-    B.x = reinterpret_cast<cplx<double>*>(x);
-    B.rhs = reinterpret_cast<const cplx<double>*>(rhs);
+    B.x = reinterpret_cast<cplx<double>*>(h->ws[7]);
+    B.rhs = reinterpret_cast<const cplx<double>*>(h->ws[2]);
     B.Ox = reinterpret_cast<const cplx<double>*>(h->ws[3]);
     if (h->lat.ncell > 1024) {
         // the tiled matvec writes one partial tuple per (slice, tile)
         B.nparts = h->lat.Nt * mdagm_tiled_tiles(h->lat, sizeof(R) == 8);
         B.part = h->tpart;
-        B.partb = h->tpart + kNP7 * (size_t)h->lat.Nt * h->tpart_tiles;
+        B.partb = h->tpart + kNP6 * (size_t)h->lat.Nt * h->tpart_tiles;
     } else {
         B.nparts = h->lat.Nt;
         B.part = h->partial;
-        B.partb = h->partial + kNP7 * (size_t)h->lat.Nt;
+        B.partb = h->partial + kNP6 * (size_t)h->lat.Nt;
     }
     return B;
 }
 
+// whether the reliable updates run inside the triples: slices of up to so many
+// cells, one a thread, whose FP64 operator fits the matvec's registers (with
+// 1024 threads a workgroup it has 128 of the 233 it takes)
+static constexpr int kUpdCells = 512;
+
 template <typename R>
-static qedhmc_status launch_mv(qedhmc_ctx* h, const PcgBufs<R>& B, const double* stop, bool timed) {
+static qedhmc_status launch_mv(qedhmc_ctx* h, const PcgBufs<R>& B, const double* stop, bool timed, bool updates) {
     if (h->lat.ncell > 1024) return launch_mdagm_tiled_parts<R>(h, B.u, B.w, B.r, B.p, B.s, B.part, stop);
     return with_shape<R>(h, [&]<int MC, int NB, int BS>(int nt, size_t lds) -> qedhmc_status {
-        QH_TRY(lds_attr(h, k_pcg_mv<R, MC, NB, BS>, lds));
-        hipEvent_t e0, e1;
-        const int cls = sizeof(R) == 4 ? QEDHMC_K_PCG_MV_FP32 : QEDHMC_K_PCG_MV_FP64;
-        if (timed && prof_sample(h, cls, e0, e1))
-            hipExtLaunchKernelGGL((k_pcg_mv<R, MC, NB, BS>), dim3(slice_grid(h->lat.Nt)), dim3(nt), lds, h->stream, e0, e1, 0,
-                                  h->lat, B, gauge_for<R>(h), coef_of<R>(h->p), stop);
-        else
-            hipLaunchKernelGGL((k_pcg_mv<R, MC, NB, BS>), dim3(slice_grid(h->lat.Nt)), dim3(nt), lds, h->stream, h->lat, B,
-                               gauge_for<R>(h), coef_of<R>(h->p), stop);
-        QH_HIP(hipGetLastError());
-        return QEDHMC_OK;
+        auto go = [&](auto kern) -> qedhmc_status {
+            QH_TRY(lds_attr(h, kern, lds));
+            hipEvent_t e0, e1;
+            const int cls = sizeof(R) == 4 ? QEDHMC_K_PCG_MV_FP32 : QEDHMC_K_PCG_MV_FP64;
+            if (timed && prof_sample(h, cls, e0, e1))
+                hipExtLaunchKernelGGL(kern, dim3(slice_grid(h->lat.Nt)), dim3(nt), lds, h->stream, e0, e1, 0, h->lat, B,
+                                      gauge_for<R>(h), coef_of<R>(h->p), (const cplx<double>*)h->gauge64,
+                                      coef_of<double>(h->p), stop);
+            else
+                hipLaunchKernelGGL(kern, dim3(slice_grid(h->lat.Nt)), dim3(nt), lds, h->stream, h->lat, B,
+                                   gauge_for<R>(h), coef_of<R>(h->p), (const cplx<double>*)h->gauge64,
+                                   coef_of<double>(h->p), stop);
+            QH_HIP(hipGetLastError());
+            return QEDHMC_OK;
+        };
+        if constexpr (MC == 1 && BS <= 512 && (sizeof(R) == 8 || NB == 2))
+            if (updates) return go(k_pcg_mv<R, MC, NB, BS, true>);
+        return go(k_pcg_mv<R, MC, NB, BS, false>);
     });
 }
 
 // u = P r, w = O u, partials (stop: nullable slot flag); with the identity
 // preconditioner u is r itself and only w = O r is launched
 template <typename R>
-static qedhmc_status pcg_tail(qedhmc_ctx* h, const PcgBufs<R>& B, const double* stop, bool identity) {
+static qedhmc_status pcg_tail(qedhmc_ctx* h, const PcgBufs<R>& B, const double* stop, bool identity,
+                              bool updates = false) {
     if (!identity) QH_TRY(apply_P_t<R>(h, B.r, B.u, spec_vhat<R>(h, B.u, B.t), B.t, stop));
-    return launch_mv<R>(h, B, stop, stop != nullptr);
+    return launch_mv<R>(h, B, stop, stop != nullptr, updates);
 }
 
 // n iterations from launch parity kpar: update, then preconditioner and
 // matvec, each gated on the slot's stop flag
 template <typename R>
-static qedhmc_status pcg_chunk(qedhmc_ctx* h, const PcgBufs<R>& B, int kpar, int n, bool mixed, bool identity,
-                               int maxit) {
+static qedhmc_status pcg_chunk(qedhmc_ctx* h, const PcgBufs<R>& B, int kpar, int n, bool mixed, bool identity) {
+    const bool updates = !identity && h->lat.ncell <= kUpdCells;  // inside the triples
     // spectral P: the update kernel does its first step
     const bool fdft = !identity && use_spectral<R>(h);
     const PcSpecGeo sg = fdft ? spec_geo<R>(h) : PcSpecGeo{};
@@ -1665,37 +1827,32 @@ static qedhmc_status pcg_chunk(qedhmc_ctx* h, const PcgBufs<R>& B, int kpar, int
                 if (lds > 65536 - 2048) QH_TRY(allow_lds((const void*)k_pcg_upd<R, NY, NX, TL>, h->max_lds));
                 hipLaunchKernelGGL((k_pcg_upd<R, NY, NX, TL>), dim3(slice_grid(h->lat.Nt)),
                                    dim3(spec_threads(sg, sg.Vs, spec_max_threads<R>())), lds, h->stream, h->lat, B,
-                                   h->scal, kpar, mixed ? 1 : 0, maxit, sg, spec_tab<R>(h), vhat);
+                                   h->scal, kpar, mixed ? 1 : 0, updates ? 1 : 0, sg, spec_tab<R>(h), vhat);
                 return QEDHMC_OK;
             }));
         else
             hipLaunchKernelGGL((k_pcg_upd<R, 0, 0, false>), dim3(slice_grid(h->lat.Nt)), dim3(256), 0, h->stream,
-                               h->lat, B, h->scal, kpar, mixed ? 1 : 0, maxit, sg, (const R*)nullptr,
+                               h->lat, B, h->scal, kpar, mixed ? 1 : 0, updates ? 1 : 0, sg, (const R*)nullptr,
                                (cplx<R>*)nullptr);
         kpar ^= 1;
         const double* stop = h->scal + S_NSLOT * kpar + S_DONE;
         if (fdft) {
             QH_TRY(launch_pcs_rest<R>(h, vhat, B.u, B.t, stop));
-            QH_TRY(launch_mv<R>(h, B, stop, true));
+            QH_TRY(launch_mv<R>(h, B, stop, true, updates));
         } else {
-            QH_TRY(pcg_tail<R>(h, B, stop, identity));
+            QH_TRY(pcg_tail<R>(h, B, stop, identity, updates));
         }
     }
     QH_HIP(hipGetLastError());
     return QEDHMC_OK;
 }
 
-// The same chunk replayed from a graph captured the first time this
-// (buffers, mode, chunk) combination is seen on the handle; the launch
-// shapes (and kernel attributes) are those of the solve's first matvec,
-// made before any capture.
-template <typename R>
-static qedhmc_status pcg_chunk_graph(qedhmc_ctx* h, const PcgBufs<R>& B, int kpar, int n, bool mixed, bool identity,
-                                     int maxit) {
-    qedhmc_ctx::PcgGraph& gr = h->pcg_graph[sizeof(R) == 8 ? 1 : 0][identity ? 1 : 0][kpar];
-    const int plan = identity ? 0 : (use_spectral<R>(h) ? 1 : 0) | (spec_fused(h) ? 2 : 0);
-    if (gr.exec && (gr.x != B.x || gr.rhs != B.rhs || gr.mixed != (int)mixed || gr.count != n || gr.plan != plan ||
-                    gr.maxit != maxit)) {
+// Runs enqueue(), or replays it from the graph captured the first time this
+// (mode, length, plan) combination is seen; the launch
+// shapes and kernel attributes are set by an eager run before any capture.
+template <typename F>
+static qedhmc_status run_graph(qedhmc_ctx* h, qedhmc_ctx::PcgGraph& gr, const qedhmc_ctx::PcgGraph& key, F&& enqueue) {
+    if (gr.exec && (gr.mixed != key.mixed || gr.count != key.count || gr.plan != key.plan)) {
         QH_HIP(hipGraphExecDestroy(gr.exec));
         gr.exec = nullptr;
     }
@@ -1709,7 +1866,7 @@ static qedhmc_status pcg_chunk_graph(qedhmc_ctx* h, const PcgBufs<R>& B, int kpa
         qedhmc_status st = QEDHMC_OK;
         hipError_t e = hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
-            st = pcg_chunk<R>(h, B, kpar, n, mixed, identity, maxit);
+            st = enqueue();
             e = hipStreamEndCapture(h->cap_stream, &g);
         }
         h->stream = user;
@@ -1719,140 +1876,89 @@ static qedhmc_status pcg_chunk_graph(qedhmc_ctx* h, const PcgBufs<R>& B, int kpa
             return st;
         }
         QH_HIP(e);
-        e = hipGraphInstantiate(&gr.exec, g, nullptr, nullptr, 0);
+        hipGraphExec_t exec = nullptr;
+        e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
         (void)hipGraphDestroy(g);
         QH_HIP(e);
-        gr.x = B.x;
-        gr.rhs = B.rhs;
-        gr.mixed = mixed ? 1 : 0;
-        gr.count = n;
-        gr.plan = plan;
-        gr.maxit = maxit;
+        gr = key;
+        gr.exec = exec;
     }
     QH_HIP(hipGraphLaunch(gr.exec, h->stream));
     return QEDHMC_OK;
 }
 
-// One round of the pipelined PCG from launch parity kp: the chunk of n
-// iterations (the mixed recursion pauses itself for a reliable update at a
-// decade or after kCap iterations; FP64 pauses only to stop or restart, or
-// at the budget), then the replacement gated on a pause in slot ke (FP64
-// O x, r = rhs - O x, s = O p, u = P r, w = O u and the partials) and the
-// decision, which mirrors the solve's record to out (pinned host memory).
+// the launches a graph of the solver holds besides its length
 template <typename R>
-static qedhmc_status pcg_round(qedhmc_ctx* h, const PcgBufs<R>& B, double* x, int kp, int n, bool mixed, int maxit,
-                               double* out) {
-    const int ke = kp ^ (n & 1);
-    double* skip = h->scal + kRecOff - 4;  // between the two slots and the record
-    QH_TRY(pcg_chunk<R>(h, B, kp, n, mixed, false, maxit));
-    const double* gate = h->scal + S_NSLOT * ke + S_DONE;
-    QH_TRY(launch_mdagm(h, QEDHMC_FP64, x, h->ws[3], gate));
-    hipLaunchKernelGGL(k_pcg_rep<R>, dim3(h->lat.Nt), dim3(256), 0, h->stream, h->lat, B, gate);
-    QH_HIP(hipGetLastError());
-    QH_TRY(launch_mdagm(h, mixed ? QEDHMC_FP32 : QEDHMC_FP64, B.p, B.s, gate));
-    hipLaunchKernelGGL(k_pcg_gate, dim3(1), dim3(64), 0, h->stream, gate, skip);
-    QH_HIP(hipGetLastError());
-    QH_TRY(pcg_tail<R>(h, B, skip, false));
-    hipLaunchKernelGGL(k_pcg_check_dev, dim3(1), dim3(256), 0, h->stream, h->scal, ke, (const double*)B.part,
-                       B.nparts, (const double*)B.partb, h->lat.Nt, maxit, mixed ? 0 : 1, h->scal + kRecOff, out);
-    QH_HIP(hipGetLastError());
-    return QEDHMC_OK;
+static int pcg_plan(const qedhmc_ctx* h, bool identity) {
+    return identity ? 0 : (use_spectral<R>(h) ? 1 : 0) | (spec_fused(h) ? 2 : 0);
 }
 
-// The same round replayed from a graph captured the first time this
-// (buffers, mode, round parity) combination is seen on the handle (every
-// kernel attribute was set by an eager round before).
-template <typename R>
-static qedhmc_status pcg_round_graph(qedhmc_ctx* h, const PcgBufs<R>& B, double* x, int kp, int n, bool mixed,
-                                     int maxit, int par, double* out) {
-    qedhmc_ctx::PcgGraph& gr = h->pcg_round[sizeof(R) == 8 ? 1 : 0][par];
-    const int plan = (use_spectral<R>(h) ? 1 : 0) | (spec_fused(h) ? 2 : 0);
-    if (gr.exec && (gr.x != x || gr.rhs != B.rhs || gr.mixed != (int)mixed || gr.count != n || gr.plan != plan ||
-                    gr.maxit != maxit || gr.kp != kp)) {
-        QH_HIP(hipGraphExecDestroy(gr.exec));
-        gr.exec = nullptr;
-    }
-    if (!gr.exec) {
-        if (!h->cap_stream) QH_HIP(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
-        hipStream_t user = h->stream;
-        const int prof = h->prof_every;
-        h->stream = h->cap_stream;
-        h->prof_every = 0;  // no event launches inside a graph
-        hipGraph_t g = nullptr;
-        qedhmc_status st = QEDHMC_OK;
-        hipError_t e = hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal);
-        if (e == hipSuccess) {
-            st = pcg_round<R>(h, B, x, kp, n, mixed, maxit, out);
-            e = hipStreamEndCapture(h->cap_stream, &g);
-        }
-        h->stream = user;
-        h->prof_every = prof;
-        if (st != QEDHMC_OK) {
-            if (g) (void)hipGraphDestroy(g);
-            return st;
-        }
-        QH_HIP(e);
-        e = hipGraphInstantiate(&gr.exec, g, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(g);
-        QH_HIP(e);
-        gr.x = x;
-        gr.rhs = B.rhs;
-        gr.mixed = mixed ? 1 : 0;
-        gr.count = n;
-        gr.plan = plan;
-        gr.maxit = maxit;
-        gr.kp = kp;
-    }
-    QH_HIP(hipGraphLaunch(gr.exec, h->stream));
-    return QEDHMC_OK;
-}
+// Triples per graph of the solver whose reliable updates run inside them (an
+// even count: every graph starts at launch parity 0); the host reads the
+// record of each.  The launches of the last graph past the end of a solve, and
+// of one queued behind it in vain, do nothing but load (4.8 us a triple), and
+// each graph costs about 8 us between the record and the next one's first
+// launch: 4, 6, 8, 10 measured 7.69, 7.48, 7.61, 7.37 ms per trajectory at L =
+// 24, N_tau = 240 (mixed) and 4.70, 4.57, 4.45, 4.34 ms at L = 12, N_tau = 120
+// (FP64).
+static constexpr int kPcgTriples = 10;
 
-// iterations per round of the mixed pipelined PCG: odd (so the launch parity
-// alternates with the round parity) and shorter than the kCap + 1 of the
-// unpreconditioned solver, since the paper's preconditioner reaches a decade,
-// and with it a pause, within about 30 iterations (the launches of a round
-// past its pause are no-ops).  QEDHMC_PCG_CHUNK (read per solve, made odd)
-// overrides.
-static constexpr int kPcgChunk = 9;
-
-// Rounds queued on the device as in the pipelined CG: the host keeps the
-// next round queued behind the running one and reads each round's record
-// through an event; the round after the last is skipped when the residual
-// estimates of the last two rounds, extrapolated geometrically, say the
-// running round converges.  Rounds after the first replay a captured graph.
-// Whole-slice lattices (the gated M^dag M has no tiled form).
+// The solve with every decision taken on the device: graphs of kPcgTriples
+// triples and a record of the slot.  A reliable update is one triple (the stop,
+// nothing, r = rhs - O x and s = O p in the matvec's launch) and the first of
+// the next (the decision, and the transform of the new r): no launch waits for
+// the host and none is wasted between a pause and its update.  Against whole
+// rounds of 12 iterations with gated update launches, and a solve for the
+// correction where a trajectory starts warm: 8.7 -> 7.4 ms per trajectory at
+// L = 24, N_tau = 240, tol 1e-10 (mixed), 4.0 -> 3.0 ms per solve at tol 1e-12.  The host keeps the next one queued behind
+// the running one and holds it back only when the residual estimates of the
+// last two, extrapolated geometrically, say that the running one converges (a
+// wrong guess costs one host round trip).  direct (QEDHMC_NO_GRAPH): the same
+// launches without graphs.
 template <typename R>
-static qedhmc_status pcg_pipelined(qedhmc_ctx* h, const PcgBufs<R>& B, double* x, double tol, int maxit,
-                                   qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable) {
+static qedhmc_status pcg_device(qedhmc_ctx* h, const PcgBufs<R>& B, const double* rhs, double* x, bool warm, double tol,
+                                int maxit, qedhmc_precision prec, bool direct, int* iters, double* true_rel,
+                                int* n_reliable) {
     const bool mixed = prec != QEDHMC_FP64;
-    int chunk = mixed ? kPcgChunk : 64;
-    if (const char* ec = std::getenv("QEDHMC_PCG_CHUNK"); ec && mixed && std::atoi(ec) > 0)
-        chunk = std::atoi(ec) | 1;
-    const int Nt = h->lat.Nt;
     for (auto& e : h->cg_ev)
         if (!e) QH_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    hipLaunchKernelGGL(k_pcg_start<R>, dim3(Nt), dim3(256), 0, h->stream, h->lat, B);
-    hipLaunchKernelGGL(k_pcg_init_slot, dim3(1), dim3(256), 0, h->stream, h->scal, (const double*)B.partb, Nt,
-                       tol * tol);
-    QH_HIP(hipGetLastError());
-    QH_TRY(pcg_tail<R>(h, B, nullptr, false));
-    QH_HIP(hipMemsetAsync(h->scal + kRecOff, 0, CR_N * sizeof(double), h->stream));
-    // the first round of a handle's first pipelined solve runs eagerly: it
-    // sets every kernel attribute before any capture
-    const bool eager0 = !h->pcg_round[sizeof(R) == 8 ? 1 : 0][0].exec;
+    QH_TRY(with_shape<double>(h, [&]<int MC, int NB, int BS>(int nt, size_t lds) -> qedhmc_status {
+        if constexpr (MC == 1 && BS <= 512) {
+            QH_TRY(lds_attr(h, k_pcg_begin<R, MC, NB, BS>, lds));
+            hipLaunchKernelGGL((k_pcg_begin<R, MC, NB, BS>), dim3(slice_grid(h->lat.Nt)), dim3(nt), lds, h->stream,
+                               h->lat, B, (const cplx<double>*)h->gauge64, coef_of<double>(h->p),
+                               (const cplx<double>*)rhs, (cplx<double>*)h->ws[2],
+                               warm ? (const cplx<double>*)x : nullptr, h->scal, tol * tol, maxit);
+            QH_HIP(hipGetLastError());
+        }
+        return QEDHMC_OK;
+    }));
+    auto& graphs = h->pcg_round[sizeof(R) == 8 ? 1 : 0];
+    // the first launches of a handle's first solve set the kernel attributes
+    const bool eager0 = !graphs[0].exec;
+    qedhmc_ctx::PcgGraph key{};
+    key.mixed = mixed ? 1 : 0;
+    key.count = kPcgTriples;
+    key.plan = pcg_plan<R>(h, false);
     auto round = [&](long n) -> qedhmc_status {
-        const int kp = (chunk & 1) ? (int)(n & 1) : 0, par = (int)(n & 1);
+        const int par = (int)(n & 1);
         double* out = h->h_pinned + 32 + 16 * par;
-        if (n == 0 && eager0)
-            QH_TRY(pcg_round<R>(h, B, x, kp, chunk, mixed, maxit, out));
+        auto enqueue = [&]() -> qedhmc_status {
+            QH_TRY(pcg_chunk<R>(h, B, 0, kPcgTriples, mixed, false));
+            hipLaunchKernelGGL(k_pcg_record, dim3(1), dim3(64), 0, h->stream, (const double*)h->scal, out);
+            QH_HIP(hipGetLastError());
+            return QEDHMC_OK;
+        };
+        if (direct || (n == 0 && eager0))
+            QH_TRY(enqueue());
         else
-            QH_TRY(pcg_round_graph<R>(h, B, x, kp, chunk, mixed, maxit, par, out));
+            QH_TRY(run_graph(h, graphs[par], key, enqueue));
         QH_HIP(hipEventRecord(h->cg_ev[par], h->stream));
         return QEDHMC_OK;
     };
-    // every round that does not end the solve advances the iteration count
-    // or the count of updates without progress, which ends it at 3
-    const long max_rounds = 4L * maxit + 16;
+    // a triple iterates, or belongs to an update; three updates without an
+    // iteration between them end the solve
+    const long max_rounds = (9L * maxit + 32) / kPcgTriples + 4;
     long queued = 0;
     double prev = -1.0;
     const double* r = nullptr;
@@ -1874,14 +1980,18 @@ static qedhmc_status pcg_pipelined(qedhmc_ctx* h, const PcgBufs<R>& B, double* x
         prev = tr;
         if (!last && queued < n + 3) QH_TRY(round(queued++));
     }
-    QH_HIP(hipStreamSynchronize(h->stream));  // a round queued past the end runs as no-ops
-    const int it = (int)r[CR_ITERS];
-    const double b2 = r[CR_B2], rel = b2 > 0.0 ? std::sqrt(r[CR_TRUE] / b2) : 0.0;
+    const double rec[CR_N] = {r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7]};
+    QH_HIP(hipMemcpyAsync(x, B.x, (size_t)h->lat.Nt * h->lat.Vs * sizeof(cplx<double>), hipMemcpyDeviceToDevice,
+                          h->stream));
+    QH_HIP(hipStreamSynchronize(h->stream));
+    const int it = (int)rec[CR_ITERS];
     if (iters) *iters = it;
-    if (true_rel) *true_rel = rel;
-    if (n_reliable) *n_reliable = (int)r[CR_NREL];
-    if (r[CR_DONE] == 5.0) return QEDHMC_OK;
-    switch ((int)r[CR_WHY]) {
+    // (a breakdown before the first update: the start's residual, 1 from zero)
+    if (true_rel)
+        *true_rel = rec[CR_NREL] == 0.0 && !warm ? 1.0 : (rec[CR_B2] > 0.0 ? std::sqrt(rec[CR_TRUE] / rec[CR_B2]) : 0.0);
+    if (n_reliable) *n_reliable = (int)rec[CR_NREL];
+    if (rec[CR_DONE] == 5.0) return QEDHMC_OK;
+    switch ((int)rec[CR_WHY]) {
         case WHY_BREAKDOWN:
             set_error("PCG breakdown: non-finite inner products after " + std::to_string(it) + " iterations");
             break;
@@ -1903,33 +2013,43 @@ static qedhmc_status pcg_pipelined(qedhmc_ctx* h, const PcgBufs<R>& B, double* x
 // cells per thread and more registers than a 576-thread workgroup has.
 template <typename R>
 static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit, qedhmc_precision prec,
-                           int* iters, double* true_rel, int* n_reliable, bool identity) {
+                           int* iters, double* true_rel, int* n_reliable, bool identity, bool warm = false) {
     if (!identity) QH_TRY(ensure_paper_precond(h));
     const bool mixed = prec != QEDHMC_FP64;
-    PcgBufs<R> B = pbufs_of<R>(h, rhs, x);
+    PcgBufs<R> B = pbufs_of<R>(h);
     if (identity) B.u = B.r;
     const int Nt = h->lat.Nt;
-    const int chunk = mixed ? kCap + 1 : 64;
-    // QEDHMC_NO_GRAPH (read per solve) launches every chunk directly from the
-    // host-driven loop below
+    // QEDHMC_NO_GRAPH (read per solve): no captured graphs
     const bool no_graph = std::getenv("QEDHMC_NO_GRAPH") != nullptr;
-    if (!identity && !no_graph && h->lat.ncell <= 1024)
-        return pcg_pipelined<R>(h, B, x, tol, maxit, prec, iters, true_rel, n_reliable);
+    if (!identity && h->lat.ncell <= kUpdCells)
+        return pcg_device<R>(h, B, rhs, x, warm, tol, maxit, prec, no_graph, iters, true_rel, n_reliable);
+    // iterations per host round trip: the plain recursion pauses after kCap at
+    // most; with the paper's preconditioner a decade, and with it a pause, takes
+    // about 9 to 30 iterations, and the launches past a pause are wasted (chunks
+    // of 51 and 12: 34.4 and 30.1 ms per solve at L = 66, N_tau = 600, tol 1e-12)
+    const int chunk = mixed ? (identity ? kCap + 1 : 12) : 64;
     int kpar = 0, nrel = 0, it = 0, stalled = 0, last_it = -1;
     double rel = 1.0;
     bool converged = false, broken = false;
-    hipLaunchKernelGGL(k_pcg_start<R>, dim3(Nt), dim3(256), 0, h->stream, h->lat, B);
+    hipLaunchKernelGGL(k_pcg_start<R>, dim3(Nt), dim3(256), 0, h->stream, h->lat, B, (const cplx<double>*)rhs,
+                       (cplx<double>*)h->ws[2]);
     hipLaunchKernelGGL(k_pcg_init_slot, dim3(1), dim3(256), 0, h->stream, h->scal, (const double*)B.partb, Nt,
-                       tol * tol);
+                       tol * tol, maxit);
     QH_HIP(hipGetLastError());
     QH_TRY(pcg_tail<R>(h, B, nullptr, identity));
     while (true) {
         const int left = maxit - it;
         const int n = left < chunk ? left : chunk;
-        if (n == chunk && !no_graph)
-            QH_TRY(pcg_chunk_graph<R>(h, B, kpar, n, mixed, identity, maxit));
-        else
-            QH_TRY(pcg_chunk<R>(h, B, kpar, n, mixed, identity, maxit));
+        auto enqueue = [&]() { return pcg_chunk<R>(h, B, kpar, n, mixed, identity); };
+        if (n == chunk && !no_graph) {
+            qedhmc_ctx::PcgGraph key{};
+            key.mixed = mixed ? 1 : 0;
+            key.count = n;
+            key.plan = pcg_plan<R>(h, identity);
+            QH_TRY(run_graph(h, h->pcg_graph[sizeof(R) == 8 ? 1 : 0][identity ? 1 : 0][kpar], key, enqueue));
+        } else {
+            QH_TRY(enqueue());
+        }
         if (n & 1) kpar ^= 1;
         QH_TRY(read_slot(h, kpar));
         it = (int)h->h_pinned[S_ITERS];
@@ -1947,8 +2067,8 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
             break;
         }
         // FP64 true residual; r replaced, s = O p refreshed, u, w and partials recomputed
-        QH_TRY(launch_mdagm(h, QEDHMC_FP64, x, h->ws[3], nullptr));
-        hipLaunchKernelGGL(k_pcg_rep<R>, dim3(Nt), dim3(256), 0, h->stream, h->lat, B, (const double*)nullptr);
+        QH_TRY(launch_mdagm(h, QEDHMC_FP64, B.x, h->ws[3], nullptr));
+        hipLaunchKernelGGL(k_pcg_rep<R>, dim3(Nt), dim3(256), 0, h->stream, h->lat, B);
         QH_HIP(hipGetLastError());
         QH_TRY(launch_mdagm(h, prec == QEDHMC_FP64 ? QEDHMC_FP64 : QEDHMC_FP32, B.p, B.s, nullptr));
         QH_TRY(pcg_tail<R>(h, B, nullptr, identity));
@@ -1970,6 +2090,8 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
         }
         if (it >= maxit) break;
     }
+    QH_HIP(hipMemcpyAsync(x, B.x, (size_t)Nt * h->lat.Vs * sizeof(cplx<double>), hipMemcpyDeviceToDevice, h->stream));
+    QH_HIP(hipStreamSynchronize(h->stream));
     if (iters) *iters = it;
     if (true_rel) *true_rel = rel;
     if (n_reliable) *n_reliable = nrel;
@@ -1977,10 +2099,13 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
     return converged ? QEDHMC_OK : QEDHMC_ENOCONV;
 }
 
+bool pcg_warm_ok(const qedhmc_ctx* h) { return h->lat.ncell <= kUpdCells; }
+
 qedhmc_status pcg_solve_impl(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit,
-                             qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable) {
-    if (prec == QEDHMC_FP64) return pcg_t<double>(h, rhs, x, tol, maxit, prec, iters, true_rel, n_reliable, false);
-    return pcg_t<float>(h, rhs, x, tol, maxit, prec, iters, true_rel, n_reliable, false);
+                             qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable, bool warm) {
+    if (prec == QEDHMC_FP64)
+        return pcg_t<double>(h, rhs, x, tol, maxit, prec, iters, true_rel, n_reliable, false, warm);
+    return pcg_t<float>(h, rhs, x, tol, maxit, prec, iters, true_rel, n_reliable, false, warm);
 }
 
 qedhmc_status cg2_solve_impl(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit,

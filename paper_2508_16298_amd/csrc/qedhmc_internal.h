@@ -537,7 +537,7 @@ struct qedhmc_ctx {
     const double* gauge_src64;  // theta the caches were last built from (nullptr: stale)
     const double* gauge_src32;
     // workspace vectors
-    void* ws[12];               // general complex FP64-sized vectors
+    void* ws[12];               // general complex FP64-sized vectors (2 and 7: the PCG's right-hand side and solution)
     void* cg_arena;             // 7 complex FP64-sized vectors of the fused CG (r, s, w ping-pong, p)
     double* theta0;             // saved theta for Metropolis
     double* mom;                // momenta
@@ -576,15 +576,11 @@ struct qedhmc_ctx {
     // double][identity preconditioner][launch parity]
     struct PcgGraph {
         hipGraphExec_t exec;
-        const void* x;
-        const void* rhs;
         int mixed, count;
         int plan;  // the preconditioner's launch plan the graph holds
-        int maxit;
-        int kp;    // launch parity at the start (whole rounds)
     } pcg_graph[2][2][2];
-    // whole pipelined PCG rounds (chunk, gated update, decision) by
-    // precision and round parity
+    // triples of the PCG whose updates run inside them, with the record, by
+    // precision and record buffer
     PcgGraph pcg_round[2][2];
     // the paper's preconditioner (built on first use)
     bool pc_ready;
@@ -665,8 +661,8 @@ qedhmc_status blocks_per_cu(const void* k, int threads, size_t lds, int* out);
 // out = M^dag M in by spatial tiles streamed along tau (mdagm_tiled.hip)
 qedhmc_status launch_mdagm_tiled(qedhmc_ctx* h, qedhmc_precision prec, const void* in, void* out);
 // the same as the matvec of the two-launch CG: w = O u and the partial sums
-// <r,r>, <r,u>, <w,u>, <u,s>, <p,w>, <p,s> (and a zero) of every (slice,
-// tile) into part[7 * (tau * tiles + tile)]; stop: nullable slot flag
+// <r,r>, <r,u>, <w,u>, <u,s>, <p,w>, <p,s> of every (slice, tile) into
+// part[q * Nt * tiles + tau * tiles + tile]; stop: nullable slot flag
 template <typename R>
 qedhmc_status launch_mdagm_tiled_parts(qedhmc_ctx* h, const cplx<R>* u, cplx<R>* w, const cplx<R>* r,
                                        const cplx<R>* p, const cplx<R>* s, double* part, const double* stop);
@@ -677,8 +673,11 @@ qedhmc_status launch_bond_tables(qedhmc_ctx* h);
 // CG (cg.hip) and preconditioned CG (pcg.hip)
 qedhmc_status cg_solve_impl(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit,
                             qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable);
+// warm: started from x instead of zero, to the same |rhs - O x| <= tol |rhs|
+// (where pcg_warm_ok: slices whose updates run inside the solver's launches)
 qedhmc_status pcg_solve_impl(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit,
-                             qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable);
+                             qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable, bool warm = false);
+bool pcg_warm_ok(const qedhmc_ctx* h);
 // plain CG as two launches per iteration (update; M^dag M with partials), for
 // lattices with more than 1024 cells per slice
 qedhmc_status cg2_solve_impl(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit,

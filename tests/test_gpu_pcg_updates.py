@@ -1,0 +1,56 @@
+"""Preconditioned CG with its reliable updates inside the launches of the
+iteration, at the sizes where the launches change: no transform in the update
+(N_tau = 12), one and five wavefronts, the edge of 512 cells (L = 44) and the
+host-driven form behind it (L = 46).  The true residual is recomputed with the
+FP64 operator; it and the solver's own differ by the rounding of two FP64
+operators, about 1e-15 |O| |x| / |rhs| <= 1e-11, so that 1e-9 is met within
+2 %."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2508_16298_amd import inputs
+from paper_2508_16298_amd import qedhmc as Q
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-9
+
+
+def _dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+@pytest.mark.parametrize("L,Nt", [(2, 13), (4, 12), (32, 13), (34, 14), (44, 13), (46, 13)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_solves_at_edges(L, Nt, prec, monkeypatch):
+    th = _dev(inputs.noisy_pi_flux_theta(L, Nt, 0.3, 40 + L))
+    rhs = _dev(inputs.gauss_cvec(L, Nt, 41 + L).reshape(Nt, L, L))
+    with Q.Lattice(L, Nt) as lat:
+        def solve(b, tol, maxit=10_000):
+            x, st, it, rel = lat.cg_solve(th, b, tol=tol, maxit=maxit, prec=prec, precond="paper")
+            return x.cpu().numpy(), st, it, rel
+
+        x, st, it, rel = solve(rhs, TOL)
+        r = rhs - lat.apply_MdagM(th, _dev(x), prec="fp64")
+        true = float(torch.linalg.vector_norm(r) / torch.linalg.vector_norm(rhs))
+        print(L, Nt, prec, it, rel, true, flush=True)
+        assert st == Q.OK and rel <= TOL and true <= 1.02 * TOL
+        # a budget short of it, a loose tolerance, and the first solve again
+        cases = [(rhs, TOL, it - 2), (rhs, TOL, 1), (rhs, 1e-2, 10_000), (rhs, TOL, 10_000)]
+        graphs = [solve(*c) for c in cases]
+        assert [g[1] for g in graphs] == [Q.ENOCONV, Q.ENOCONV, Q.OK, Q.OK]
+        assert graphs[0][2] == it - 2 and graphs[1][2] == 1 and graphs[2][3] <= 1e-2
+        assert np.array_equal(graphs[3][0], x) and graphs[3][2:] == (it, rel)
+        monkeypatch.setenv("QEDHMC_NO_GRAPH", "1")
+        for c, g in zip(cases, graphs):
+            d = solve(*c)
+            assert np.array_equal(d[0], g[0]) and d[1:] == g[1:]
+        monkeypatch.delenv("QEDHMC_NO_GRAPH")
+        # nothing to solve, and nothing that can be solved
+        z, st, it0, rel0 = solve(torch.zeros_like(rhs), TOL)
+        assert st == Q.OK and it0 == 0 and rel0 == 0.0 and not z.any()
+        bad = rhs.clone()
+        bad[Nt // 2, 1, 1] = float("nan")
+        _, st, it0, rel0 = solve(bad, TOL)
+        assert st == Q.ENOCONV and it0 == 0 and rel0 == 1.0
+        assert np.array_equal(solve(rhs, TOL)[0], x)  # not carried over
