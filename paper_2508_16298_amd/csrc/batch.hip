@@ -46,7 +46,6 @@ struct ChainDev {
     Coef<double> co64;
     int maxit;   // host: iteration budget of the solve
     int mixed;   // host: 1 for the mixed-precision recursion
-    int it0;     // device: iterations done at the start of the current chunk
     int rel0;    // device: parity of the iterations since the last update at the start of the chunk
     int frozen;  // device: 1 once the solve of this chain is final
 };
@@ -72,6 +71,8 @@ __device__ __forceinline__ Tile blk_tile(const Blk& b, int Nt, unsigned char* sm
                 reinterpret_cast<double*>(smem + (size_t)(kBS / b.G) * gbytes)};
 }
 
+static constexpr size_t kRedBytes = (kNP * 16 + 16) * sizeof(double);  // reduction scratch
+
 template <typename R, int NB>
 __device__ __forceinline__ size_t group_lds(const Lat& lt) {
     return (size_t)NB * 2 * lt.Vs * sizeof(cplx<R>);
@@ -94,28 +95,33 @@ __global__ __launch_bounds__(kBS) void k_b_cg_start(const ChainDev<R>* __restric
     if (b.tau0 == 0 && threadIdx.x < kNRes) res[kNRes * b.chain + threadIdx.x] = 0.0;
 }
 
-template <typename R, int MC, int NB>
-__global__ __launch_bounds__(kBS) void k_b_cg_iter(const ChainDev<R>* __restrict__ tab, const Blk* __restrict__ blk,
-                                                   int kpar, int k, double tol2) {
+// Bound by its instructions and by one round of workgroups on every CU, then by
+// its bytes (about 96 a site and iteration in FP32): 16 right-hand sides at L =
+// 16, N_tau = 160 took 21 us a launch, with flat accesses, x read and written
+// every time and no halo; 15 us now (4.2 TB/s).  FP64 with the halo keeps two
+// wavefronts a SIMD at 26 spilled registers: 88.9 ms against 98.3 ms with one
+// (a trajectory of 16 chains of 8 to 20 cells a side).
+template <typename R, int MC, int NB, bool HALO>
+__global__ __launch_bounds__(kBS, HALO && MC == 1 ? (sizeof(R) == 8 ? 2 : 3) : 1) void k_b_cg_iter(
+    const ChainDev<R>* __restrict__ tab, const Blk* __restrict__ blk, int kpar, int k, double tol2) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Blk b = blk[blockIdx.x];
     if (b.chain < 0) return;
     const ChainDev<R>& d = tab[b.chain];
     if (d.frozen) return;
-    const int it = d.it0 + k;  // the iteration count if the chain ran every launch of this chunk
-    if (it >= d.maxit) {
-        // budget used: carry the state over, mark it for the final true residual
-        if (b.tau0 == 0 && threadIdx.x < S_NSLOT) {
-            double v = d.scal[S_NSLOT * kpar + threadIdx.x];
-            if (threadIdx.x == S_DONE && v == 0.0) v = 6.0;
-            d.scal[S_NSLOT * (kpar ^ 1) + threadIdx.x] = v;
-        }
-        return;
-    }
     int tau;
     const Tile tl = blk_tile(b, d.lt.Nt, smem, group_lds<R, NB>(d.lt), tau);
-    cg_iter_body<R, MC, NB>(d.lt, d.B, d.gauge, d.co, d.scal, kpar, (d.rel0 + k) & 1, tol2, d.mixed, d.maxit, tau,
-                            tl.valid && tau == 0, tl);
+    Halo hl{};
+    if constexpr (HALO) {
+        const int T = kBS / b.G, Nt = d.lt.Nt;
+        hl.g = (int)threadIdx.x / b.G;
+        hl.n = Nt - b.tau0 < T ? Nt - b.tau0 : T;
+        hl.lo = b.tau0 == 0 ? Nt - 1 : b.tau0 - 1;
+        hl.hi = b.tau0 + hl.n == Nt ? 0 : b.tau0 + hl.n;
+        hl.buf = smem + (size_t)T * group_lds<R, NB>(d.lt) + kRedBytes;
+    }
+    cg_iter_body<R, MC, NB, kBS, HALO>(d.lt, d.B, d.gauge, d.co, d.scal, kpar, (d.rel0 + k) & 1, tol2, d.mixed, d.maxit,
+                                       tau, tl.valid && tau == 0, tl, hl);
 }
 
 // FP64 O x of the chains that stopped or paused
@@ -126,22 +132,22 @@ __global__ __launch_bounds__(kBS) void k_b_ox(const ChainDev<R>* __restrict__ ta
     const Blk b = blk[blockIdx.x];
     if (b.chain < 0) return;
     const ChainDev<R>& d = tab[b.chain];
-    if (d.frozen || !gate_open(d.scal[S_NSLOT * kpar + S_DONE])) return;
+    if (d.frozen || !gate_open(gptr(d.scal)[S_NSLOT * kpar + S_DONE])) return;
     int tau;
     const Tile tl = blk_tile(b, d.lt.Nt, smem, group_lds<double, NB>(d.lt), tau);
     SliceCtx<MC> c;
     slice_ctx<MC>(d.lt, c, tau, tl);
     const size_t Vs = d.lt.Vs;
     cplx<double> hm[MC][12], ht[MC][12];
-    hops_of<double, MC>(d.gauge64, d.lt, c.tm, c.idx, d.co64, hm);
-    hops_of<double, MC>(d.gauge64, d.lt, c.tau, c.idx, d.co64, ht);
+    hops_of<double, MC>(gptr(d.gauge64), d.lt, c.tm, c.idx, d.co64, hm);
+    hops_of<double, MC>(gptr(d.gauge64), d.lt, c.tau, c.idx, d.co64, ht);
     Cells<double, MC> vm, vt, vn, o;
-    load_cells<double, MC>(vm, d.B.x + c.tm * Vs, c.g, c.own);
-    load_cells<double, MC>(vt, d.B.x + c.tau * Vs, c.g, c.own);
-    load_cells<double, MC>(vn, d.B.x + c.tp * Vs, c.g, c.own);
+    load_cells<double, MC>(vm, gptr(d.B.x) + c.tm * Vs, c.g);
+    load_cells<double, MC>(vt, gptr(d.B.x) + c.tau * Vs, c.g);
+    load_cells<double, MC>(vn, gptr(d.B.x) + c.tp * Vs, c.g);
     mdagm_cells<double, MC, NB>(vm, vt, vn, hm, ht, c.g, c.own, d.co64, c.tau == 0 ? -1.0 : 1.0,
                                 c.tau == d.lt.Nt - 1 ? -1.0 : 1.0, reinterpret_cast<cplx<double>*>(tl.buf), d.lt.Vs, o);
-    store_cells<double, MC>(o, const_cast<cplx<double>*>(d.B.Ox) + c.tau * Vs, c.g, c.own);
+    store_cells<double, MC>(o, const_cast<cplx<double>*>(gptr(d.B.Ox)) + c.tau * Vs, c.g, c.own);
 }
 
 template <typename R, int MC, int NB>
@@ -151,7 +157,7 @@ __global__ __launch_bounds__(kBS) void k_b_cg_replace(const ChainDev<R>* __restr
     const Blk b = blk[blockIdx.x];
     if (b.chain < 0) return;
     const ChainDev<R>& d = tab[b.chain];
-    if (d.frozen || !gate_open(d.scal[S_NSLOT * kpar + S_DONE])) return;
+    if (d.frozen || !gate_open(gptr(d.scal)[S_NSLOT * kpar + S_DONE])) return;
     int tau;
     const Tile tl = blk_tile(b, d.lt.Nt, smem, group_lds<R, NB>(d.lt), tau);
     cg_replace_body<R, MC, NB>(d.lt, d.B, d.gauge, d.co, d.scal, kpar, tau, tl);
@@ -166,13 +172,13 @@ __global__ void k_b_cg_check(ChainDev<R>* __restrict__ tab, int kpar, double* __
     __shared__ double red[kNP * 16 + 16];
     ChainDev<R>* d = tab + blockIdx.x;
     if (d->frozen) return;
-    double* sl = d->scal + S_NSLOT * kpar;
+    double* sl = gptr(d->scal) + S_NSLOT * kpar;
     const double done = sl[S_DONE];
     const int it = (int)sl[S_ITERS];
     int nd = done == 4.0 ? 4 : -1;
     if (gate_open(done)) {
         double pr[kNP];
-        reduce_partials(d->B.part, d->lt.Nt, whole_block_tile(nullptr, red), pr);  // the replacement's (parity 0)
+        reduce_partials(gptr(d->B.part), d->lt.Nt, whole_block_tile(nullptr, red), pr);  // the replacement's (parity 0)
         if (threadIdx.x == 0) {
             const double tr = pr[5];
             const int stall = (it + 1 == (int)sl[S_LASTUP]) ? (int)sl[S_STALL] + 1 : 0;
@@ -196,7 +202,6 @@ __global__ void k_b_cg_check(ChainDev<R>* __restrict__ tab, int kpar, double* __
         }
     }
     if (threadIdx.x == 0) {
-        d->it0 = it;
         d->rel0 = (it - (int)sl[S_ITUPD]) & 1;
         if (nd == 4 || nd == 5) {
             d->frozen = 1;
@@ -217,7 +222,7 @@ __global__ void k_b_gauge(const ChainDev<R>* __restrict__ tab, const double* __r
                           const int64_t* __restrict__ toff) {
     const int c = blockIdx.y;
     const int64_t o = toff[c], n = toff[c + 1] - o;
-    cplx<R>* g = const_cast<cplx<R>*>(tab[c].gauge);
+    cplx<R>* g = const_cast<cplx<R>*>(gptr(tab[c].gauge));
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         double s, co;
         sincos(theta[o + i], &s, &co);
@@ -292,7 +297,20 @@ static size_t shape_lds(const qedhmc_batch* b, int shape, size_t csz) {
         const int G = group_threads(h->lat, shape);
         if (G > 0) most = std::max(most, (size_t)(kBS / G) * kShapeNB[shape] * 2 * h->lat.Vs * csz);
     }
-    return most + (kNP * 16 + 16) * sizeof(double);
+    return most + kRedBytes;
+}
+
+// the same of the iteration that exchanges r between its groups; 0 where it is
+// not taken: a chain with one slice per workgroup (more than half as many cells
+// as its threads take) has nothing to exchange
+static size_t halo_lds(const qedhmc_batch* b, int shape, size_t csz) {
+    size_t most = 0;
+    for (const qedhmc_ctx* h : b->ctx) {
+        const int G = group_threads(h->lat, shape), T = G > 0 ? kBS / G : 0;
+        if (T < 2) return 0;
+        most = std::max(most, ((size_t)T * kShapeNB[shape] * 2 + T + 2) * h->lat.Vs * csz);
+    }
+    return most + kRedBytes <= b->max_lds ? most + kRedBytes : 0;
 }
 
 static bool shape_ok(const qedhmc_batch* b, int shape) {
@@ -322,20 +340,19 @@ static std::vector<Blk> work_list(const qedhmc_batch* b, int shape) {
 }
 
 template <typename K>
-static qedhmc_status set_lds(K kern, size_t bytes) {
-    if (bytes > 65536)
-        QH_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-    return QEDHMC_OK;
+static qedhmc_status set_lds(const qedhmc_batch* b, K kern, size_t bytes) {
+    return bytes > 65536 ? allow_lds((const void*)kern, b->max_lds) : QEDHMC_OK;
 }
 
 template <typename R>
 static qedhmc_status set_attrs(qedhmc_batch* b, int shape) {
     return with_bshape(shape, [&]<int MC, int NB>() -> qedhmc_status {
         const size_t l = shape_lds(b, shape, sizeof(cplx<R>)), l64 = shape_lds(b, shape, sizeof(cplx<double>));
-        QH_TRY(set_lds(k_b_cg_start<R, MC, NB>, l));
-        QH_TRY(set_lds(k_b_cg_iter<R, MC, NB>, l));
-        QH_TRY(set_lds(k_b_cg_replace<R, MC, NB>, l));
-        QH_TRY(set_lds(k_b_ox<R, MC, NB>, l64));
+        QH_TRY(set_lds(b, k_b_cg_start<R, MC, NB>, l));
+        QH_TRY(set_lds(b, k_b_cg_iter<R, MC, NB, false>, l));
+        QH_TRY(set_lds(b, k_b_cg_iter<R, MC, NB, true>, halo_lds(b, shape, sizeof(cplx<R>))));
+        QH_TRY(set_lds(b, k_b_cg_replace<R, MC, NB>, l));
+        QH_TRY(set_lds(b, k_b_ox<R, MC, NB>, l64));
         return QEDHMC_OK;
     });
 }
@@ -393,7 +410,6 @@ static qedhmc_status push_tab(qedhmc_batch* b, const std::vector<const double*>&
         tab[c].B.x = reinterpret_cast<cplx<double>*>(x[c]);
         tab[c].maxit = maxit;
         tab[c].mixed = mixed ? 1 : 0;
-        tab[c].it0 = 0;
         tab[c].rel0 = 0;
         tab[c].frozen = 0;
     }
@@ -414,10 +430,12 @@ static qedhmc_status launch_start(qedhmc_batch* b, int shape) {
 template <typename R>
 static qedhmc_status launch_iters(qedhmc_batch* b, int shape, int kpar, int count, double tol2) {
     return with_bshape(shape, [&]<int MC, int NB>() -> qedhmc_status {
-        const size_t lds = shape_lds(b, shape, sizeof(cplx<R>));
+        const size_t halo = halo_lds(b, shape, sizeof(cplx<R>));
+        const size_t lds = halo ? halo : shape_lds(b, shape, sizeof(cplx<R>));
+        auto kern = halo ? k_b_cg_iter<R, MC, NB, true> : k_b_cg_iter<R, MC, NB, false>;
         for (int k = 0; k < count; k++)
-            hipLaunchKernelGGL((k_b_cg_iter<R, MC, NB>), dim3(b->nblocks[shape]), dim3(kBS), lds, b->stream,
-                               dev_tab<R>(b), b->d_blk[shape], kpar ^ (k & 1), k, tol2);
+            hipLaunchKernelGGL(kern, dim3(b->nblocks[shape]), dim3(kBS), lds, b->stream, dev_tab<R>(b), b->d_blk[shape],
+                               kpar ^ (k & 1), k, tol2);
         QH_HIP(hipGetLastError());
         return QEDHMC_OK;
     });

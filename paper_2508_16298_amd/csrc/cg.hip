@@ -26,7 +26,7 @@ __global__ __launch_bounds__(BS) void k_cg_iter(Lat lt, CgBufs<R> B, const cplx<
     const int tau = slice_of_block(blockIdx.x, lt.Nt);
     if (tau < 0) return;
     const Tile tl = whole_block_tile(smem, reinterpret_cast<double*>(smem + (size_t)NB * 2 * lt.Vs * sizeof(cplx<R>)));
-    cg_iter_body<R, MC, NB>(lt, B, gauge, co, scal, kpar, ipar, tol2, mixed, maxit, tau, tau == 0, tl);
+    cg_iter_body<R, MC, NB, (BS > 256 ? 257 : 64), false>(lt, B, gauge, co, scal, kpar, ipar, tol2, mixed, maxit, tau, tau == 0, tl);
 }
 
 template <typename R, int MC, int NB, int BS>
@@ -348,21 +348,16 @@ static qedhmc_status cg_t(qedhmc_ctx* h, const double* rhs, double* x, double to
     static const bool trace = std::getenv("QEDHMC_CG_TRACE") != nullptr;
     QH_TRY(launch_start<R>(h, B));
     while (true) {
-        const int left = maxit - it;
-        // full chunks replay a captured graph
+        // one launch past the budget marks a running solve for its final true
+        // residual and brings x up to date
+        const int left = maxit - it + 1;
         // buffer parity: iterations since the last reliable update
-        if (left >= chunk && !no_graph) {
-            QH_TRY(launch_iters_graph<R>(h, B, kpar, (it - itupd) & 1, chunk, tol * tol, mixed ? 1 : 0, maxit));
-            if (chunk & 1) kpar ^= 1;
-        } else if (left > 0) {
-            QH_TRY(launch_iters<R>(h, B, kpar, it - itupd, left < chunk ? left : chunk, tol * tol, mixed ? 1 : 0,
-                                   maxit));
-        }
+        QH_TRY(launch_iters<R>(h, B, kpar, it - itupd, left < chunk ? left : chunk, tol * tol, mixed ? 1 : 0, maxit));
         QH_TRY(read_slot(h, kpar));
         it = (int)h->h_pinned[S_ITERS];
         itupd = (int)h->h_pinned[S_ITUPD];
         const double flag = h->h_pinned[S_DONE];
-        if (flag == 0.0 && it < maxit) continue;
+        if (flag == 0.0) continue;
         if (flag == 4.0) {
             broken = true;
             set_error("CG breakdown: non-finite inner products after " + std::to_string(it) + " iterations");

@@ -24,7 +24,10 @@
 // two neighbouring slices it needs for the stencil, and applies O to its
 // slice.  r, s and w alternate between two buffers by iteration parity; the
 // device scalars alternate between two slots by launch parity, so no launch
-// reads what a concurrent workgroup writes.
+// reads what a concurrent workgroup writes.  x takes two steps at a time, at
+// every second iteration after an update and where the recursion stops in
+// between (the launch past the last iteration always runs): alpha_{i-1} and
+// p_{i-1} are at hand there, and 16 of 112 bytes a site and iteration go.
 //
 // Stop and pause: an iteration that finds gamma_i <= tol^2 |rhs|^2 turns
 // itself and all later launches into no-ops (the host reads the flag once per
@@ -59,13 +62,13 @@ __device__ __forceinline__ void cg_start_body(const Lat& lt, const CgBufs<R>& B,
     slice_ctx<MC>(lt, c, tau, tl);
     const size_t Vs = lt.Vs;
     cplx<R> hm[MC][12], ht[MC][12];
-    hops_of<R, MC>(gauge, lt, c.tm, c.idx, co, hm);
-    hops_of<R, MC>(gauge, lt, c.tau, c.idx, co, ht);
+    hops_of<R, MC>(gptr(gauge), lt, c.tm, c.idx, co, hm);
+    hops_of<R, MC>(gptr(gauge), lt, c.tau, c.idx, co, ht);
     Cells<R, MC> vm, vt, vn, w;
     double b2 = 0.0, dummy = 0.0;
-    load_cvt<R, MC>(vm, B.rhs + c.tm * Vs, nullptr, c.g, c.own, dummy);
-    load_cvt<R, MC>(vt, B.rhs + c.tau * Vs, nullptr, c.g, c.own, b2);
-    load_cvt<R, MC>(vn, B.rhs + c.tp * Vs, nullptr, c.g, c.own, dummy);
+    load_cvt<R, MC>(vm, gptr(B.rhs) + c.tm * Vs, nullptr, c.g, c.own, dummy);
+    load_cvt<R, MC>(vt, gptr(B.rhs) + c.tau * Vs, nullptr, c.g, c.own, b2);
+    load_cvt<R, MC>(vn, gptr(B.rhs) + c.tp * Vs, nullptr, c.g, c.own, dummy);
     Cells<R, MC> zero;
     Cells<double, MC> zx;
 #pragma unroll
@@ -75,36 +78,62 @@ __device__ __forceinline__ void cg_start_body(const Lat& lt, const CgBufs<R>& B,
             zero.v[m][q] = mk<R>(0, 0);
             zx.v[m][q] = mk<double>(0, 0);
         }
-    store_cells<R, MC>(vt, B.r[0] + c.tau * Vs, c.g, c.own);
-    store_cells<R, MC>(zero, B.s[0] + c.tau * Vs, c.g, c.own);
-    store_cells<R, MC>(zero, B.p + c.tau * Vs, c.g, c.own);
-    store_cells<double, MC>(zx, B.x + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(vt, gptr(B.r[0]) + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(zero, gptr(B.s[0]) + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(zero, gptr(B.p) + c.tau * Vs, c.g, c.own);
+    store_cells<double, MC>(zx, gptr(B.x) + c.tau * Vs, c.g, c.own);
     const Cells<R, MC> r0 = vt;
     mdagm_cells<R, MC, NB>(vm, vt, vn, hm, ht, c.g, c.own, co, c.tau == 0 ? R(-1) : R(1),
                            c.tau == lt.Nt - 1 ? R(-1) : R(1), buf2, lt.Vs, w);
-    store_cells<R, MC>(w, B.w[0] + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(w, gptr(B.w[0]) + c.tau * Vs, c.g, c.own);
     double v[kNP] = {dot_cells<R, MC>(r0, r0, c.own), dot_cells<R, MC>(w, r0, c.own), 0.0, 0.0, 0.0, b2};
-    write_partials(B.part + kNP * (size_t)c.tau, v, tl);  // parity 0
+    write_partials<kNP>(gptr(B.part), lt.Nt, c.tau, v, tl);  // parity 0
     if (lead && tl.ltid < S_NSLOT) {
         double v = 0.0;
         if (tl.ltid == S_FIRST) v = 1.0;
         if (tl.ltid == S_B2) v = -1.0;
         if (tl.ltid == S_GPREV || tl.ltid == S_APREV) v = 1.0;
-        scal[tl.ltid] = v;
+        gptr(scal)[tl.ltid] = v;
     }
 }
 
+// x += a p in FP64
+template <typename R, int MC>
+__device__ __forceinline__ void add_scaled(Cells<double, MC>& x, double a, const Cells<R, MC>& p) {
+#pragma unroll
+    for (int m = 0; m < MC; m++)
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            x.v[m][q].re += a * (double)p.v[m][q].re;
+            x.v[m][q].im += a * (double)p.v[m][q].im;
+        }
+}
+
 // ---------------------------------------------------------------------------
-// One CG iteration.  kpar: launch parity (slot in = kpar, slot out = kpar^1).
+// One CG iteration (workgroups of THREADS or more).  kpar: launch parity (slot in = kpar, slot out = kpar^1).
 // ---------------------------------------------------------------------------
-template <typename R, int MC, int NB>
+// HALO (workgroups of two and more groups, which hold n consecutive slices
+// hl.lo + 1 ... hl.hi - 1 in their first n groups): every group reads and
+// advances its own slice alone, the first two the slice before and the slice
+// after as well, and the operator takes the neighbours' new r from LDS.
+// Against three slices read and advanced by every group it halves the loads
+// and, in FP32, brings 200 registers to 166, three workgroups a CU instead of
+// two: a launch of 640 workgroups (16 right-hand sides at L = 16, N_tau = 160)
+// is one round of them instead of two.
+struct Halo {
+    int g, n;            // this thread's group; the workgroup's slices
+    int lo, hi;          // the slices before and after them
+    unsigned char* buf;  // LDS: n + 2 slices of r, a cell's four sites together
+};
+
+template <typename R, int MC, int NB, int THREADS, bool HALO>
 __device__ __forceinline__ void cg_iter_body(const Lat& lt, const CgBufs<R>& B, const cplx<R>* __restrict__ gauge,
                                              const Coef<R>& co, double* __restrict__ scal, int kpar, int ipar,
                                              double tol2, int mixed, int maxit, int tau, bool lead,
-                                             const Tile& tl) {
+                                             const Tile& tl, const Halo& hl = Halo{}) {
     cplx<R>* buf2 = reinterpret_cast<cplx<R>*>(tl.buf);
-    const double* sin_ = scal + S_NSLOT * kpar;
-    double* sout = scal + S_NSLOT * (kpar ^ 1);
+    const double* sin_ = gptr(scal) + S_NSLOT * kpar;
+    double* sout = gptr(scal) + S_NSLOT * (kpar ^ 1);
     // Every load of the launch is issued before the scalars arrive: the
     // buffer parity ipar comes from the host -- the parity of the number of
     // iterations since the last reliable update (the ping-pong of r, s, w
@@ -112,34 +141,59 @@ __device__ __forceinline__ void cg_iter_body(const Lat& lt, const CgBufs<R>& B, 
     // after one has ipar = launch index & 1 whatever the iteration count; after
     // a stop or pause inside a chunk the remaining launches are no-ops, so the
     // guess is never used wrongly) -- and the stop flag is looked at only
-    // after the loads.  All loads are in bounds whatever the flag says.
+    // after the loads.  The partials come first: their sums are ready while the
+    // vectors are on their way.  All loads are in bounds whatever the flag says.
     const double done = sin_[S_DONE];
     const int it = (int)sin_[S_ITERS];
     const int ip = ipar, nx = ip ^ 1;
+    PartSum<THREADS> ps;
+    ps.load(gptr(B.part) + kNP * (size_t)lt.Nt * ip, lt.Nt);
     SliceCtx<MC> c;
     slice_ctx<MC>(lt, c, tau, tl);
     const size_t Vs = lt.Vs;
+    // (HALO: wm, sm, rm of the slice before or after the workgroup's)
     Cells<R, MC> wm, wt, wn, sm, st, sn, rm, rt, rn, pp;
-    load_cells<R, MC>(wm, B.w[ip] + c.tm * Vs, c.g, c.own);
-    load_cells<R, MC>(wt, B.w[ip] + c.tau * Vs, c.g, c.own);
-    load_cells<R, MC>(wn, B.w[ip] + c.tp * Vs, c.g, c.own);
-    load_cells<R, MC>(sm, B.s[ip] + c.tm * Vs, c.g, c.own);
-    load_cells<R, MC>(st, B.s[ip] + c.tau * Vs, c.g, c.own);
-    load_cells<R, MC>(sn, B.s[ip] + c.tp * Vs, c.g, c.own);
-    load_cells<R, MC>(rm, B.r[ip] + c.tm * Vs, c.g, c.own);
-    load_cells<R, MC>(rt, B.r[ip] + c.tau * Vs, c.g, c.own);
-    load_cells<R, MC>(rn, B.r[ip] + c.tp * Vs, c.g, c.own);
-    load_cells<R, MC>(pp, B.p + c.tau * Vs, c.g, c.own);
+    load_cells<R, MC>(wt, gptr(B.w[ip]) + c.tau * Vs, c.g);
+    load_cells<R, MC>(st, gptr(B.s[ip]) + c.tau * Vs, c.g);
+    load_cells<R, MC>(rt, gptr(B.r[ip]) + c.tau * Vs, c.g);
+    load_cells<R, MC>(pp, gptr(B.p) + c.tau * Vs, c.g);
+    if constexpr (HALO) {
+        if (hl.g < 2) {
+            const size_t ho = (size_t)(hl.g == 0 ? hl.lo : hl.hi) * Vs;
+            load_cells<R, MC>(wm, gptr(B.w[ip]) + ho, c.g);
+            load_cells<R, MC>(sm, gptr(B.s[ip]) + ho, c.g);
+            load_cells<R, MC>(rm, gptr(B.r[ip]) + ho, c.g);
+        }
+    } else {
+        load_cells<R, MC>(wm, gptr(B.w[ip]) + c.tm * Vs, c.g);
+        load_cells<R, MC>(wn, gptr(B.w[ip]) + c.tp * Vs, c.g);
+        load_cells<R, MC>(sm, gptr(B.s[ip]) + c.tm * Vs, c.g);
+        load_cells<R, MC>(sn, gptr(B.s[ip]) + c.tp * Vs, c.g);
+        load_cells<R, MC>(rm, gptr(B.r[ip]) + c.tm * Vs, c.g);
+        load_cells<R, MC>(rn, gptr(B.r[ip]) + c.tp * Vs, c.g);
+    }
+    // (FP64 with the halo: later, where s and w are gone from the registers)
+    constexpr bool late = HALO && sizeof(R) == 8;
     cplx<R> hm[MC][12], ht[MC][12];
-    hops_of<R, MC>(gauge, lt, c.tm, c.idx, co, hm);
-    hops_of<R, MC>(gauge, lt, c.tau, c.idx, co, ht);
-    // x is read here with the rest (its update comes after stores that the
-    // compiler cannot tell apart from x, which would hold the read back)
-    Cells<double, MC> xo;
-    load_cells<double, MC>(xo, B.x + c.tau * Vs, c.g, c.own);
+    auto hops = [&]() {
+        hops_of<R, MC>(gptr(gauge), lt, c.tm, c.idx, co, hm);
+        hops_of<R, MC>(gptr(gauge), lt, c.tau, c.idx, co, ht);
+    };
+    if constexpr (!late) hops();
+    // x is behind by alpha_{i-1} p_{i-1} at odd ip: only every second iteration
+    // reads and writes it, and so does the launch that stops in between
+    const double aprev = sin_[S_APREV];
+    auto catch_up = [&]() {
+        if (!ip) return;
+        Cells<double, MC> xo;
+        load_cells<double, MC>(xo, gptr(B.x) + c.tau * Vs, c.g);
+        add_scaled<R, MC>(xo, aprev, pp);
+        store_cells<double, MC>(xo, gptr(B.x) + c.tau * Vs, c.g, c.own);
+    };
     if (done != 0.0 || it >= maxit) {
         // stopped or paused: carry the state over; a running solve that used
         // its iteration budget is marked for its final true residual (6)
+        if (done == 0.0) catch_up();
         if (lead && tl.ltid < S_NSLOT) {
             double v = sin_[tl.ltid];
             if (tl.ltid == S_DONE && v == 0.0) v = 6.0;
@@ -149,7 +203,7 @@ __device__ __forceinline__ void cg_iter_body(const Lat& lt, const CgBufs<R>& B, 
     }
 
     double pr[kNP];
-    reduce_partials(B.part + kNP * (size_t)lt.Nt * ip, lt.Nt, tl, pr);
+    ps.finish(tl.red, pr);
     const double gam = pr[0], del = pr[1], aux = pr[5];
     double b2 = sin_[S_B2], target = sin_[S_TARGET], rrupd = sin_[S_RRUPD];
     if (b2 < 0.0) {  // first iteration of the solve: the start kernel left |rhs|^2 partials in aux
@@ -165,6 +219,7 @@ __device__ __forceinline__ void cg_iter_body(const Lat& lt, const CgBufs<R>& B, 
     else if (mixed && (gam <= kDecade2 * rrupd || it - (int)sin_[S_ITUPD] >= kCap))
         stop = 2;
     if (stop) {
+        catch_up();
         if (lead && tl.ltid < S_NSLOT) {
             double v = sin_[tl.ltid];
             if (tl.ltid == S_DONE) v = (double)stop;
@@ -180,6 +235,7 @@ __device__ __forceinline__ void cg_iter_body(const Lat& lt, const CgBufs<R>& B, 
     const double beta = first ? 0.0 : gam / sin_[S_GPREV];
     const double den = first ? del : del + beta * (pr[2] + pr[3]) + beta * beta * pr[4];  // <p_i, s_i>
     if (!(den > 0.0)) {
+        catch_up();
         if (lead && tl.ltid < S_NSLOT) {
             double v = sin_[tl.ltid];
             if (tl.ltid == S_DONE) v = 3.0;
@@ -193,41 +249,74 @@ __device__ __forceinline__ void cg_iter_body(const Lat& lt, const CgBufs<R>& B, 
     }
     const double alpha = gam / den;
     const R b = (R)beta, a = (R)alpha;
+    const Cells<R, MC> pold = pp;
 
     // s_i = w_i + beta s_{i-1};  r_{i+1} = r_i - alpha s_i on the three slices
 #pragma unroll
     for (int m = 0; m < MC; m++)
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            sm.v[m][q] = cfma(b, sm.v[m][q], wm.v[m][q]);
             st.v[m][q] = cfma(b, st.v[m][q], wt.v[m][q]);
-            sn.v[m][q] = cfma(b, sn.v[m][q], wn.v[m][q]);
             pp.v[m][q] = cfma(b, pp.v[m][q], rt.v[m][q]);  // p_i = r_i + beta p_{i-1}
-            rm.v[m][q] = cfma(-a, sm.v[m][q], rm.v[m][q]);
             rt.v[m][q] = cfma(-a, st.v[m][q], rt.v[m][q]);
-            rn.v[m][q] = cfma(-a, sn.v[m][q], rn.v[m][q]);
         }
-    store_cells<R, MC>(st, B.s[nx] + c.tau * Vs, c.g, c.own);
-    store_cells<R, MC>(rt, B.r[nx] + c.tau * Vs, c.g, c.own);
-    store_cells<R, MC>(pp, B.p + c.tau * Vs, c.g, c.own);
-    // x_{i+1} = x_i + alpha p_i in FP64
+    auto advance = [&](Cells<R, MC>& r, const Cells<R, MC>& s, const Cells<R, MC>& w) {
 #pragma unroll
-    for (int m = 0; m < MC; m++)
+        for (int m = 0; m < MC; m++)
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            xo.v[m][q].re += alpha * (double)pp.v[m][q].re;
-            xo.v[m][q].im += alpha * (double)pp.v[m][q].im;
+            for (int q = 0; q < 4; q++) r.v[m][q] = cfma(-a, cfma(b, s.v[m][q], w.v[m][q]), r.v[m][q]);
+    };
+    if constexpr (HALO) {
+        cplx<R>* rs = reinterpret_cast<cplx<R>*>(hl.buf);
+        auto at = [&](int slot, int m) { return rs + (slot * lt.ncell + c.g[m].c) * 4; };
+        if (hl.g < 2) {
+            advance(rm, sm, wm);
+#pragma unroll
+            for (int m = 0; m < MC; m++)
+                if (tl.ltid + m * tl.G < lt.ncell)
+#pragma unroll
+                    for (int q = 0; q < 4; q++) at(hl.g == 0 ? 0 : hl.n + 1, m)[q] = rm.v[m][q];
         }
-    store_cells<double, MC>(xo, B.x + c.tau * Vs, c.g, c.own);
+#pragma unroll
+        for (int m = 0; m < MC; m++)
+            if (c.own[m])
+#pragma unroll
+                for (int q = 0; q < 4; q++) at(hl.g + 1, m)[q] = rt.v[m][q];
+        if constexpr (late) hops();
+        __syncthreads();
+        // (a padding group reads slots that may hold nothing, and uses none of it)
+#pragma unroll
+        for (int m = 0; m < MC; m++)
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                rm.v[m][q] = at(hl.g, m)[q];
+                rn.v[m][q] = at(hl.g + 2, m)[q];
+            }
+    } else {
+        advance(rm, sm, wm);
+        advance(rn, sn, wn);
+    }
+    store_cells<R, MC>(st, gptr(B.s[nx]) + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(rt, gptr(B.r[nx]) + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(pp, gptr(B.p) + c.tau * Vs, c.g, c.own);
+    // x_{i+1} = x_{i-1} + alpha_{i-1} p_{i-1} + alpha_i p_i in FP64, on its way
+    // while the operator runs
+    Cells<double, MC> xo;
+    if (ip) load_cells<double, MC>(xo, gptr(B.x) + c.tau * Vs, c.g);
     const Cells<R, MC> rnew = rt;
     Cells<R, MC> w;
     mdagm_cells<R, MC, NB>(rm, rt, rn, hm, ht, c.g, c.own, co, c.tau == 0 ? R(-1) : R(1),
                            c.tau == lt.Nt - 1 ? R(-1) : R(1), buf2, lt.Vs, w);
-    store_cells<R, MC>(w, B.w[nx] + c.tau * Vs, c.g, c.own);
-    double v[kNP] = {dot_cells<R, MC>(rnew, rnew, c.own), dot_cells<R, MC>(w, rnew, c.own),
+    store_cells<R, MC>(w, gptr(B.w[nx]) + c.tau * Vs, c.g, c.own);
+    if (ip) {
+        add_scaled<R, MC>(xo, aprev, pold);
+        add_scaled<R, MC>(xo, alpha, pp);
+        store_cells<double, MC>(xo, gptr(B.x) + c.tau * Vs, c.g, c.own);
+    }
+    double v[kNP - 1] = {dot_cells<R, MC>(rnew, rnew, c.own), dot_cells<R, MC>(w, rnew, c.own),
                      dot_cells<R, MC>(rnew, st, c.own), dot_cells<R, MC>(pp, w, c.own),
-                     dot_cells<R, MC>(pp, st, c.own), 0.0};
-    write_partials(B.part + kNP * ((size_t)lt.Nt * nx + c.tau), v, tl);
+                     dot_cells<R, MC>(pp, st, c.own)};
+    write_partials<kNP - 1>(gptr(B.part) + kNP * (size_t)lt.Nt * nx, lt.Nt, c.tau, v, tl);
     if (lead && tl.ltid < S_NSLOT) {
         double v = sin_[tl.ltid];
         if (tl.ltid == S_GPREV) v = gam;
@@ -257,30 +346,30 @@ __device__ __forceinline__ void cg_replace_body(const Lat& lt, const CgBufs<R>& 
     slice_ctx<MC>(lt, c, tau, tl);
     const size_t Vs = lt.Vs;
     cplx<R> hm[MC][12], ht[MC][12];
-    hops_of<R, MC>(gauge, lt, c.tm, c.idx, co, hm);
-    hops_of<R, MC>(gauge, lt, c.tau, c.idx, co, ht);
+    hops_of<R, MC>(gptr(gauge), lt, c.tm, c.idx, co, hm);
+    hops_of<R, MC>(gptr(gauge), lt, c.tau, c.idx, co, ht);
     Cells<R, MC> vm, vt, vn, w;
     double t2 = 0.0, dummy = 0.0;
-    load_cvt<R, MC>(vm, B.rhs + c.tm * Vs, B.Ox + c.tm * Vs, c.g, c.own, dummy);
-    load_cvt<R, MC>(vt, B.rhs + c.tau * Vs, B.Ox + c.tau * Vs, c.g, c.own, t2);
-    load_cvt<R, MC>(vn, B.rhs + c.tp * Vs, B.Ox + c.tp * Vs, c.g, c.own, dummy);
-    store_cells<R, MC>(vt, B.r[ip] + c.tau * Vs, c.g, c.own);
+    load_cvt<R, MC>(vm, gptr(B.rhs) + c.tm * Vs, gptr(B.Ox) + c.tm * Vs, c.g, c.own, dummy);
+    load_cvt<R, MC>(vt, gptr(B.rhs) + c.tau * Vs, gptr(B.Ox) + c.tau * Vs, c.g, c.own, t2);
+    load_cvt<R, MC>(vn, gptr(B.rhs) + c.tp * Vs, gptr(B.Ox) + c.tp * Vs, c.g, c.own, dummy);
+    store_cells<R, MC>(vt, gptr(B.r[ip]) + c.tau * Vs, c.g, c.own);
     const Cells<R, MC> r0 = vt;
     const R em = c.tau == 0 ? R(-1) : R(1), et = c.tau == lt.Nt - 1 ? R(-1) : R(1);
     mdagm_cells<R, MC, NB>(vm, vt, vn, hm, ht, c.g, c.own, co, em, et, buf2, lt.Vs, w);
-    store_cells<R, MC>(w, B.w[ip] + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(w, gptr(B.w[ip]) + c.tau * Vs, c.g, c.own);
     // s_{i-1} = O p_{i-1}, recomputed
     Cells<R, MC> pm, pt_, pn, sp;
-    load_cells<R, MC>(pm, B.p + c.tm * Vs, c.g, c.own);
-    load_cells<R, MC>(pt_, B.p + c.tau * Vs, c.g, c.own);
-    load_cells<R, MC>(pn, B.p + c.tp * Vs, c.g, c.own);
+    load_cells<R, MC>(pm, gptr(B.p) + c.tm * Vs, c.g);
+    load_cells<R, MC>(pt_, gptr(B.p) + c.tau * Vs, c.g);
+    load_cells<R, MC>(pn, gptr(B.p) + c.tp * Vs, c.g);
     __syncthreads();  // LDS exchange buffers are reused
     mdagm_cells<R, MC, NB>(pm, pt_, pn, hm, ht, c.g, c.own, co, em, et, buf2, lt.Vs, sp);
-    store_cells<R, MC>(sp, B.s[ip] + c.tau * Vs, c.g, c.own);
+    store_cells<R, MC>(sp, gptr(B.s[ip]) + c.tau * Vs, c.g, c.own);
     double v[kNP] = {dot_cells<R, MC>(r0, r0, c.own), dot_cells<R, MC>(w, r0, c.own),
                      dot_cells<R, MC>(r0, sp, c.own), dot_cells<R, MC>(pt_, w, c.own),
                      dot_cells<R, MC>(pt_, sp, c.own), t2};
-    write_partials(B.part + kNP * ((size_t)lt.Nt * ip + c.tau), v, tl);
+    write_partials<kNP>(gptr(B.part) + kNP * (size_t)lt.Nt * ip, lt.Nt, c.tau, v, tl);
 }
 
 

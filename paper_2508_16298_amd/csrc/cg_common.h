@@ -47,6 +47,15 @@ static constexpr int kNP = 6;
 static constexpr double kDecade2 = 0.01;  // pause when gamma fell by 10^2 (|r| by 10)
 static constexpr int kCap = 50;           // ... or after 50 iterations
 
+// A pointer to device memory that was itself read from memory (a row of the
+// batch's table) is generic to the compiler: its accesses become flat ones,
+// which return out of order and are all waited for together.  A kernel's own
+// pointer arguments are known to be global and are not changed by this.
+template <typename T>
+__device__ __forceinline__ T* gptr(T* p) {
+    return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
+
 template <typename R>
 struct CgBufs {
     cplx<R>* r[2];
@@ -56,7 +65,7 @@ struct CgBufs {
     cplx<double>* x;
     const cplx<double>* rhs;
     const cplx<double>* Ox;  // FP64 O x for the true residual
-    double* part;            // [2][Nt][kNP] per-slice partials, see kNP
+    double* part;            // [2][kNP][Nt] per-slice partials, see kNP
 };
 
 // Block reduction of K doubles in a fixed order; result valid in thread 0.
@@ -99,8 +108,8 @@ __device__ __forceinline__ Tile whole_block_tile(unsigned char* buf, double* red
 
 // Sum of K doubles over the threads of a group; the total is valid in the
 // group's last thread.  Every thread of the workgroup calls it (groups of 64
-// and more meet at workgroup barriers; smaller groups reduce within their
-// 16- or 32-lane rows through DPP alone).  Fixed order.
+// 128 and more meet at workgroup barriers; smaller groups reduce within their
+// 16, 32 or 64 lanes through DPP alone).  Fixed order.
 template <int K>
 __device__ __forceinline__ void group_sumk(double (&v)[K], const Tile& tl) {
     if (tl.G < 64) {
@@ -118,6 +127,7 @@ __device__ __forceinline__ void group_sumk(double (&v)[K], const Tile& tl) {
     }
 #pragma unroll
     for (int k = 0; k < K; k++) v[k] = wave_sum_f64(v[k]);
+    if (tl.G == 64) return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     __syncthreads();
     if (lane == 63)
@@ -134,46 +144,93 @@ __device__ __forceinline__ void group_sumk(double (&v)[K], const Tile& tl) {
     }
 }
 
-// Sum of the Nt partial tuples of one parity (a chain's: every group of the
-// workgroup belongs to it), broadcast to every thread of the workgroup.
+// The kNP sums over the slices' partials: each wavefront adds one sum (and
+// a second one by turns), 64 slices at a time, fixed order.  load() requests
+// them over the first 256 slices, so that a caller can put it before its other
+// loads and finish() waits for nothing else; with fewer than three wavefronts
+// everything is read in finish().
+// THREADS: the least the workgroup has.
+template <int THREADS>
+struct PartSum {
+    static constexpr int Q = 2, U = 4;
+    static constexpr bool kFew = THREADS / 64 * Q < kNP;  // may hold too few wavefronts
+    const double* part;
+    int Nt;
+    double a[Q][U];
+
+    __device__ __forceinline__ double at(int q, int t) const { return t < Nt ? part[(size_t)q * Nt + t] : 0.0; }
+
+    __device__ __forceinline__ void load(const double* p, int n) {
+        part = p;
+        Nt = n;
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
+        if (kFew && nw * Q < kNP) return;
+#pragma unroll
+        for (int j = 0; j < Q; j++) {
+            const int q = wave + j * nw < kNP ? wave + j * nw : 0;
+#pragma unroll
+            for (int u = 0; u < U; u++) a[j][u] = at(q, lane + 64 * u);
+        }
+    }
+
+    __device__ __forceinline__ void finish(double* red, double (&out)[kNP]) const {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
+        if (kFew && nw * Q < kNP) {
+            // one or two wavefronts: a slice per thread, all six sums at once
+            double v[kNP];
+#pragma unroll
+            for (int k = 0; k < kNP; k++) v[k] = 0.0;
+            for (int t0 = threadIdx.x; t0 < Nt; t0 += U * (int)blockDim.x) {
+                double b[U][kNP];
+#pragma unroll
+                for (int u = 0; u < U; u++)
+#pragma unroll
+                    for (int k = 0; k < kNP; k++) b[u][k] = at(k, t0 + u * (int)blockDim.x);
+#pragma unroll
+                for (int u = 0; u < U; u++)
+#pragma unroll
+                    for (int k = 0; k < kNP; k++) v[k] += b[u][k];
+            }
+            block_sumk<kNP>(v, red);
+            double* bc = red + kNP * 16;
+            if (threadIdx.x == 0)
+#pragma unroll
+                for (int k = 0; k < kNP; k++) bc[k] = v[k];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kNP; k++) out[k] = bc[k];
+            return;
+        }
+        for (int j = 0, q = wave; q < kNP; q += nw, j++) {
+            double s = 0.0;
+#pragma unroll
+            for (int u = 0; u < U; u++) s += j == 0 ? a[0][u] : a[1][u];
+            for (int t = lane + 64 * U; t < Nt; t += 64) s += part[(size_t)q * Nt + t];
+            s = wave_sum_f64(s);
+            if (lane == 63) red[q] = s;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kNP; k++) out[k] = red[k];
+    }
+};
+
 __device__ __forceinline__ void reduce_partials(const double* __restrict__ part, int Nt, const Tile& tl,
                                                 double (&out)[kNP]) {
-    double v[kNP];
-#pragma unroll
-    for (int k = 0; k < kNP; k++) v[k] = 0.0;
-    // tuples t, t + blockDim, ... in that order; up to four of them are
-    // loaded before any is added, so a workgroup smaller than Nt waits for
-    // memory once rather than once per tuple
-    constexpr int U = 4;
-    for (int t0 = threadIdx.x; t0 < Nt; t0 += U * blockDim.x) {
-        double a[U][kNP];
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int t = t0 + u * (int)blockDim.x;
-#pragma unroll
-            for (int k = 0; k < kNP; k++) a[u][k] = t < Nt ? part[kNP * t + k] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < U; u++)
-#pragma unroll
-            for (int k = 0; k < kNP; k++) v[k] += a[u][k];
-    }
-    block_sumk<kNP>(v, tl.red);
-    double* bc = tl.red + kNP * 16;
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int k = 0; k < kNP; k++) bc[k] = v[k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kNP; k++) out[k] = bc[k];
+    PartSum<64> ps;
+    ps.load(part, Nt);
+    ps.finish(tl.red, out);
 }
 
-// The group's partial tuple into pt (skipped for padding groups).
-__device__ __forceinline__ void write_partials(double* __restrict__ pt, double (&v)[kNP], const Tile& tl) {
-    group_sumk<kNP>(v, tl);
+// The group's first K partials of slice tau into part (skipped for padding
+// groups).
+template <int K>
+__device__ __forceinline__ void write_partials(double* __restrict__ part, int Nt, int tau, double (&v)[K],
+                                               const Tile& tl) {
+    group_sumk<K>(v, tl);
     if (tl.valid && tl.ltid == tl.G - 1)
 #pragma unroll
-        for (int k = 0; k < kNP; k++) pt[k] = v[k];
+        for (int k = 0; k < K; k++) part[(size_t)k * Nt + tau] = v[k];
 }
 
 template <typename R, int MC>
@@ -206,7 +263,7 @@ __device__ __forceinline__ void slice_ctx(const Lat& lt, SliceCtx<MC>& c, int ta
     for (int m = 0; m < MC; m++) {
         const int cell = tl.ltid + m * tl.G;
         c.own[m] = tl.valid && cell < lt.ncell;
-        c.g[m] = cell_geo(c.own[m] ? cell : 0, lt);
+        c.g[m] = cell_geo(cell < lt.ncell ? cell : 0, lt);
         phase_index(c.g[m], lt.Vs, c.idx[m]);
     }
 }

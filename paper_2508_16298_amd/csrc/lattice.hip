@@ -133,7 +133,7 @@ __global__ __launch_bounds__(BS) void k_apply_B(Lat lt, int tau, const cplx<R>* 
     cplx<R> hp[MC][12];
     load_hops_all<R, MC>(gauge, lt, tau, idx, co, hp);
     Cells<R, MC> c;
-    load_cells<R, MC>(c, in, g, own);
+    load_cells<R, MC>(c, in, g);
     apply_B_cells<R, MC, NB>(c, hp, g, own, co, xb);
     store_cells<R, MC>(c, out, g, own);
 }
@@ -170,8 +170,8 @@ __global__ __launch_bounds__(BS) void k_apply_M(Lat lt, int dagger, const cplx<R
     cplx<R> hp[MC][12];
     load_hops_all<R, MC>(gauge, lt, bsl, idx, co, hp);
     Cells<R, MC> c, d;
-    load_cells<R, MC>(c, in + (size_t)src * lt.Vs, g, own);
-    load_cells<R, MC>(d, in + (size_t)tau * lt.Vs, g, own);
+    load_cells<R, MC>(c, in + (size_t)src * lt.Vs, g);
+    load_cells<R, MC>(d, in + (size_t)tau * lt.Vs, g);
     apply_B_cells<R, MC, NB>(c, hp, g, own, co, xb);
 #pragma unroll
     for (int m = 0; m < MC; m++)
@@ -206,9 +206,9 @@ __global__ __launch_bounds__(BS) void k_mdagm(Lat lt, const cplx<R>* __restrict_
     Cells<R, MC> vm, vt, vn, o;
     load_hops_all<R, MC, true>(gauge, lt, tm, idx, co, hm);
     load_hops_all<R, MC, true>(gauge, lt, tau, idx, co, ht);
-    load_cells<R, MC>(vm, in + (size_t)tm * lt.Vs, g, own);
-    load_cells<R, MC>(vt, in + (size_t)tau * lt.Vs, g, own);
-    load_cells<R, MC>(vn, in + (size_t)tp * lt.Vs, g, own);
+    load_cells<R, MC>(vm, in + (size_t)tm * lt.Vs, g);
+    load_cells<R, MC>(vt, in + (size_t)tau * lt.Vs, g);
+    load_cells<R, MC>(vn, in + (size_t)tp * lt.Vs, g);
     mdagm_cells<R, MC, NB>(vm, vt, vn, hm, ht, g, own, co, eps_m, eps_t, buf2, lt.Vs, o);
     store_cells<R, MC>(o, out + (size_t)tau * lt.Vs, g, own);
 }
@@ -233,9 +233,9 @@ __global__ __launch_bounds__(BS) void k_mdagm_theta(Lat lt, const cplx<R>* __res
     int idx[1][12];
     my_cells<1>(lt, g, own, idx);
     Cells<R, 1> vm, vt, vn, o;
-    load_cells<R, 1>(vm, in + (size_t)tm * Vs, g, own);
-    load_cells<R, 1>(vt, in + (size_t)tau * Vs, g, own);
-    load_cells<R, 1>(vn, in + (size_t)tp * Vs, g, own);
+    load_cells<R, 1>(vm, in + (size_t)tm * Vs, g);
+    load_cells<R, 1>(vt, in + (size_t)tau * Vs, g);
+    load_cells<R, 1>(vn, in + (size_t)tp * Vs, g);
     for (int s = threadIdx.x; s < Vs; s += blockDim.x) {
         double t[4];
 #pragma unroll
@@ -383,8 +383,8 @@ __global__ __launch_bounds__(BS) void k_force(Lat lt, const cplx<R>* __restrict_
 #pragma unroll
         for (int k = 0; k < 12; k++) hn[m][k] = mk<R>(-hp[m][k].re, -hp[m][k].im);
     Cells<R, MC> u, w;
-    load_cells<R, MC>(u, X + (size_t)tau * lt.Vs, g, own);
-    load_cells<R, MC>(w, Y + (size_t)tn * lt.Vs, g, own);
+    load_cells<R, MC>(u, X + (size_t)tau * lt.Vs, g);
+    load_cells<R, MC>(w, Y + (size_t)tn * lt.Vs, g);
 #pragma unroll
     for (int m = 0; m < MC; m++)
 #pragma unroll

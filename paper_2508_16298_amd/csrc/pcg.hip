@@ -1329,7 +1329,7 @@ __global__ __launch_bounds__(BS) void k_pcg_begin(Lat lt, PcgBufs<R> B, const cp
     slice_ctx<MC>(lt, c, tau, whole_block_tile(smem, red));
     const size_t Vs = lt.Vs;
     Cells<double, MC> b, o;
-    load_cells<double, MC>(b, rhs + c.tau * Vs, c.g, c.own);
+    load_cells<double, MC>(b, rhs + c.tau * Vs, c.g);
     store_cells<double, MC>(b, keep + c.tau * Vs, c.g, c.own);
     double v[2] = {0.0, dot_cells<double, MC>(b, b, c.own)};
     Cells<double, MC> xt;
@@ -1342,9 +1342,9 @@ __global__ __launch_bounds__(BS) void k_pcg_begin(Lat lt, PcgBufs<R> B, const cp
         hops_of<double, MC>(gauge64, lt, c.tm, c.idx, co64, hm);
         hops_of<double, MC>(gauge64, lt, c.tau, c.idx, co64, ht);
         Cells<double, MC> xm, xn;
-        load_cells<double, MC>(xm, x0 + c.tm * Vs, c.g, c.own);
-        load_cells<double, MC>(xt, x0 + c.tau * Vs, c.g, c.own);
-        load_cells<double, MC>(xn, x0 + c.tp * Vs, c.g, c.own);
+        load_cells<double, MC>(xm, x0 + c.tm * Vs, c.g);
+        load_cells<double, MC>(xt, x0 + c.tau * Vs, c.g);
+        load_cells<double, MC>(xn, x0 + c.tp * Vs, c.g);
         mdagm_cells<double, MC, NB>(xm, xt, xn, hm, ht, c.g, c.own, co64, c.tau == 0 ? -1.0 : 1.0,
                                     c.tau == lt.Nt - 1 ? -1.0 : 1.0, buf2, lt.Vs, o);
     }
@@ -1586,36 +1586,36 @@ __global__ __launch_bounds__(BS) void k_pcg_mv(Lat lt, PcgBufs<R> B, const cplx<
     hops_of<R, MC>(gauge, lt, c.tm, c.idx, co, hm);
     hops_of<R, MC>(gauge, lt, c.tau, c.idx, co, ht);
     Cells<R, MC> um, ut, un, w;
-    load_cells<R, MC>(um, B.u + c.tm * Vs, c.g, c.own);
-    load_cells<R, MC>(ut, B.u + c.tau * Vs, c.g, c.own);
-    load_cells<R, MC>(un, B.u + c.tp * Vs, c.g, c.own);
+    load_cells<R, MC>(um, B.u + c.tm * Vs, c.g);
+    load_cells<R, MC>(ut, B.u + c.tau * Vs, c.g);
+    load_cells<R, MC>(un, B.u + c.tp * Vs, c.g);
     Cells<R, MC> rt, pt, st;
     constexpr bool early = MC == 1 && BS <= 512;
     if constexpr (early) {
-        load_cells<R, MC>(rt, B.r + c.tau * Vs, c.g, c.own);
-        load_cells<R, MC>(pt, B.p + c.tau * Vs, c.g, c.own);
-        load_cells<R, MC>(st, B.s + c.tau * Vs, c.g, c.own);
+        load_cells<R, MC>(rt, B.r + c.tau * Vs, c.g);
+        load_cells<R, MC>(pt, B.p + c.tau * Vs, c.g);
+        load_cells<R, MC>(st, B.s + c.tau * Vs, c.g);
     }
     if (UPD && done != 0.0) {
         if (!gate_open(done)) return;
         if constexpr (sizeof(R) == 8) {
             // x takes the place of u below (an FP64 solve restarts after every
             // update, so s is not needed)
-            load_cells<R, MC>(um, reinterpret_cast<const cplx<R>*>(B.x) + c.tm * Vs, c.g, c.own);
-            load_cells<R, MC>(ut, reinterpret_cast<const cplx<R>*>(B.x) + c.tau * Vs, c.g, c.own);
-            load_cells<R, MC>(un, reinterpret_cast<const cplx<R>*>(B.x) + c.tp * Vs, c.g, c.own);
+            load_cells<R, MC>(um, reinterpret_cast<const cplx<R>*>(B.x) + c.tm * Vs, c.g);
+            load_cells<R, MC>(ut, reinterpret_cast<const cplx<R>*>(B.x) + c.tau * Vs, c.g);
+            load_cells<R, MC>(un, reinterpret_cast<const cplx<R>*>(B.x) + c.tp * Vs, c.g);
         } else if constexpr (UPD) {
             static_assert(NB == 2, "one FP64 exchange buffer fits the two FP32 ones");
             Cells<double, MC> b, o;
-            load_cells<double, MC>(b, B.rhs + c.tau * Vs, c.g, c.own);
+            load_cells<double, MC>(b, B.rhs + c.tau * Vs, c.g);
             {
                 cplx<double> gm[MC][12], gt[MC][12];
                 hops_of<double, MC>(gauge64, lt, c.tm, c.idx, co64, gm);
                 hops_of<double, MC>(gauge64, lt, c.tau, c.idx, co64, gt);
                 Cells<double, MC> xm, xt, xn;
-                load_cells<double, MC>(xm, B.x + c.tm * Vs, c.g, c.own);
-                load_cells<double, MC>(xt, B.x + c.tau * Vs, c.g, c.own);
-                load_cells<double, MC>(xn, B.x + c.tp * Vs, c.g, c.own);
+                load_cells<double, MC>(xm, B.x + c.tm * Vs, c.g);
+                load_cells<double, MC>(xt, B.x + c.tau * Vs, c.g);
+                load_cells<double, MC>(xn, B.x + c.tp * Vs, c.g);
                 mdagm_cells<double, MC, 1>(xm, xt, xn, gm, gt, c.g, c.own, co64, (double)em, (double)et,
                                             reinterpret_cast<cplx<double>*>(smem), lt.Vs, o);
             }
@@ -1632,9 +1632,9 @@ __global__ __launch_bounds__(BS) void k_pcg_mv(Lat lt, PcgBufs<R> B, const cplx<
             store_cells<R, MC>(r, B.r + c.tau * Vs, c.g, c.own);
             block_sumk<1>(v, red);
             if (threadIdx.x == 0) B.partb[c.tau] = v[0];
-            load_cells<R, MC>(pm, B.p + c.tm * Vs, c.g, c.own);
-            load_cells<R, MC>(po, B.p + c.tau * Vs, c.g, c.own);
-            load_cells<R, MC>(pn, B.p + c.tp * Vs, c.g, c.own);
+            load_cells<R, MC>(pm, B.p + c.tm * Vs, c.g);
+            load_cells<R, MC>(po, B.p + c.tau * Vs, c.g);
+            load_cells<R, MC>(pn, B.p + c.tp * Vs, c.g);
             // (fetched again rather than held across the FP64 operator)
             cplx<R> gm[MC][12], gt[MC][12];
             hops_of<R, MC>(gauge, lt, c.tm, c.idx, co, gm);
@@ -1649,7 +1649,7 @@ __global__ __launch_bounds__(BS) void k_pcg_mv(Lat lt, PcgBufs<R> B, const cplx<
     if constexpr (UPD && sizeof(R) == 8) {
         if (done != 0.0) {
             Cells<R, MC> b;
-            load_cells<R, MC>(b, reinterpret_cast<const cplx<R>*>(B.rhs) + c.tau * Vs, c.g, c.own);
+            load_cells<R, MC>(b, reinterpret_cast<const cplx<R>*>(B.rhs) + c.tau * Vs, c.g);
 #pragma unroll
             for (int m = 0; m < MC; m++)
 #pragma unroll
@@ -1663,9 +1663,9 @@ __global__ __launch_bounds__(BS) void k_pcg_mv(Lat lt, PcgBufs<R> B, const cplx<
     }
     store_cells<R, MC>(w, B.w + c.tau * Vs, c.g, c.own);
     if constexpr (!early) {
-        load_cells<R, MC>(rt, B.r + c.tau * Vs, c.g, c.own);
-        load_cells<R, MC>(pt, B.p + c.tau * Vs, c.g, c.own);
-        load_cells<R, MC>(st, B.s + c.tau * Vs, c.g, c.own);
+        load_cells<R, MC>(rt, B.r + c.tau * Vs, c.g);
+        load_cells<R, MC>(pt, B.p + c.tau * Vs, c.g);
+        load_cells<R, MC>(st, B.s + c.tau * Vs, c.g);
     }
     const Cells<R, MC>& u0 = ut;  // the matvec reads its own slice without changing it
     double v[kNP6] = {dot_cells<R, MC>(rt, rt, c.own), dot_cells<R, MC>(rt, u0, c.own),

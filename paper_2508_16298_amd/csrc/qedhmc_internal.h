@@ -156,12 +156,12 @@ __device__ __forceinline__ void phase_index(const CellGeo& g, int Vs, int (&idx)
 template <typename R, bool TN = false>
 __device__ __forceinline__ void load_hops(const cplx<R>* __restrict__ gauge, const Lat& lt, int tau,
                                           const int (&idx)[12], const Coef<R>& co, cplx<R> (&h)[12]) {
+    const cplx<R>* const g0 = gauge + (size_t)tau * lt.Vs;
+    const cplx<R>* const g1 = g0 + (size_t)(lt.Nt - 1) * lt.Vs;  // d = 1: idx holds the other Vs
 #pragma unroll
     for (int k = 0; k < 12; k++) {
-        const int id = idx[k];
-        const int d = id >= lt.Vs ? 1 : 0;
-        const int s = id - d * lt.Vs;
-        const cplx<R> e = gauge[((size_t)d * lt.Nt + tau) * lt.Vs + s];
+        const bool d1 = (k >= 4 && k < 8) || k >= 10;
+        const cplx<R> e = (d1 ? g1 : g0)[idx[k]];
         const R sc = TN ? ((k < 2) ? co.t2 : co.t1) : ((k < 2) ? co.s2 : co.s1);
         h[k] = mk<R>(sc * e.re, sc * e.im);
     }
@@ -416,19 +416,14 @@ __device__ __forceinline__ void mdagm_cells(Cells<R, MC>& vm, const Cells<R, MC>
         for (int q = 0; q < 4; q++) out.v[m][q] = cfma(C, t.v[m][q], out.v[m][q]);
 }
 
+// (a thread without a cell reads the one its geometry names, in bounds: its
+// values are masked where they would count, and need no branch here)
 template <typename R, int MC>
-__device__ __forceinline__ void load_cells(Cells<R, MC>& c, const cplx<R>* __restrict__ slice, const CellGeo (&g)[MC],
-                                           const bool (&own)[MC]) {
+__device__ __forceinline__ void load_cells(Cells<R, MC>& c, const cplx<R>* __restrict__ slice, const CellGeo (&g)[MC]) {
 #pragma unroll
-    for (int m = 0; m < MC; m++) {
-        if (own[m]) {
+    for (int m = 0; m < MC; m++)
 #pragma unroll
-            for (int q = 0; q < 4; q++) c.v[m][q] = slice[g[m].s[q]];
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; q++) c.v[m][q] = mk<R>(0, 0);
-        }
-    }
+        for (int q = 0; q < 4; q++) c.v[m][q] = slice[g[m].s[q]];
 }
 
 template <typename R, int MC>
@@ -448,8 +443,9 @@ __device__ __forceinline__ void store_cells(const Cells<R, MC>& c, cplx<R>* __re
 // wavefront must take part.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_f64(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
+    // (all rows take part: nothing to keep in lanes without a source)
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, ROWS == 0xF);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, ROWS == 0xF);
     return __hiloint2double(hi, lo);
 }
 
