@@ -935,16 +935,23 @@ __device__ __forceinline__ int sp_slice(int s, int Nt, R& sign) {
 // z^(k, tau) = sum_a sign H(k, a) v^(k, tau + a): a thread per (momentum, run
 // of T slices) holds the T + 2 kSpTau input slices it needs in registers and
 // reads each block of H once for the run.  Bound by the FMAs (400 per
-// momentum and slice: 15 us of the 32 at L = 66, N_tau = 660).
+// momentum and slice: 15 us of the 28 at L = 66, N_tau = 660) with two
+// wavefronts a SIMD.
+// Workgroup i runs on XCD i mod 8: every XCD takes an eighth of the momenta
+// for all slices, so the runs' windows, which overlap in 24 slices, come from
+// its L2: P at L = 66 81.2 -> 77.7 us (FP32), 156 -> 145 us (FP64, N_tau = 640).
+__host__ __device__ __forceinline__ int tsum_first(int nk, int xcd) { return (int)((long)nk * xcd / 8); }
+
 template <typename R, int T>
 __global__ __launch_bounds__(256) void k_pcs_tsum(PcSpecGeo g, const cpair<R>* __restrict__ H,
                                                   const cplx<R>* __restrict__ in, cplx<R>* __restrict__ out,
                                                   const double* __restrict__ stop) {
     if (stop && *stop != 0.0) return;
     const int nk = g.nk, nrun = (g.Nt + T - 1) / T;
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= nk * nrun) return;
-    const int k = gid % nk, tau0 = (gid / nk) * T;
+    const int k0 = tsum_first(nk, blockIdx.x & 7), wk = tsum_first(nk, (blockIdx.x & 7) + 1) - k0;
+    const int i = (blockIdx.x >> 3) * blockDim.x + threadIdx.x;
+    if (i >= wk * nrun) return;
+    const int k = k0 + i % wk, tau0 = (i / wk) * T;
     constexpr int NW = T + 2 * kSpTau;
     cpair<R> v[NW];
     // window slices past the last one needed read the run's first slice and
@@ -1075,7 +1082,7 @@ static bool use_spectral(const qedhmc_ctx* h) {
 // the tau sum fused into the inverse DFT up to this many momenta per plane
 // (each workgroup then reads H and 2 reach + 1 input slices through the L2):
 // P in FP32, fused / separate, L = 48 35.0 / 43.7 us, L = 56 45.4 / 47.6 us,
-// L = 66 99.4 / 81.2 us.  QEDHMC_PC_FUSE=0|1 (read per call) forces either form
+// L = 66 99.4 / 81.2 us (77.7 since).  QEDHMC_PC_FUSE=0|1 (read per call) forces either form
 static constexpr int kSpecFuseNK = 1682;  // L = 58
 
 static bool spec_fused(const qedhmc_ctx* h) {
@@ -1152,9 +1159,9 @@ static qedhmc_status launch_pcs_rest(qedhmc_ctx* h, const cplx<R>* vhat, cplx<R>
         // L = 66, N_tau = 660 with runs of 4 / 6 / 8 / 10: FP32 87.4 / 81.2 /
         // 82.3 / 83.7 us, FP64 (N_tau = 640) 171 / 156 / - / 154 us.
         auto runs = [&]<int T>() {
-            const int nth = g.nk * ((g.Nt + T - 1) / T);
-            hipLaunchKernelGGL((k_pcs_tsum<R, T>), dim3((nth + 255) / 256), dim3(256), 0, h->stream, g, spec_H<R>(h),
-                               vhat, m1, stop);
+            const int nth = (g.nk + 7) / 8 * ((g.Nt + T - 1) / T);  // of an XCD, at most
+            hipLaunchKernelGGL((k_pcs_tsum<R, T>), dim3(8 * ((nth + 255) / 256)), dim3(256), 0, h->stream, g,
+                               spec_H<R>(h), vhat, m1, stop);
         };
         if ((size_t)g.nk * g.Nt >= ((size_t)1 << 20))
             runs.template operator()<6>();
@@ -1383,6 +1390,11 @@ __global__ __launch_bounds__(BS) void k_pcg_begin(Lat lt, PcgBufs<R> B, const cp
 // that a launch of a finished solve costs as much as one that works; those are
 // few where the updates run inside the triples.  8.5 -> 6.6 us at L = 24, N_tau
 // = 240 (FP32).
+// Large lattices: bound by the bytes, 96 a site on average in FP32 (x, FP64, is
+// read and written at every second iteration).  65 us at 104 a site at L = 66,
+// N_tau = 660 (4.6 TB/s), 58 us now; the sites past a thread's first kUpdPre
+// are also requested kUpdPre at a time, and the launch without a transform has
+// a thread for every four sites: CG at L = 80, N_tau = 200 43.9 -> 38.9 ms.
 static constexpr int kUpdPre = 4;
 
 template <typename R, int NY, int NX, bool TL>
@@ -1420,19 +1432,31 @@ __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBu
         return s;
     };
     double sum = wave <= kNP6 ? partial(wave) : 0.0;
+    // x is behind by alpha_{i-1} p_{i-1} after an odd number of iterations since
+    // the last update: it takes two steps at every second iteration, and one
+    // where the recursion stops in between
+    const int it = (int)sl[S_ITERS];
+    const bool behind = ((it - (int)sl[S_ITUPD]) & 1) != 0;
+    const double aprev = sl[S_APREV];
     cplx<R> p0[kUpdPre], u0[kUpdPre], s0[kUpdPre], w0[kUpdPre], r0[kUpdPre];
     cplx<double> x0[kUpdPre];
+    auto fetch = [&](int k0) {
+        size_t i[kUpdPre];
 #pragma unroll
-    for (int j = 0; j < kUpdPre; j++) {
-        const int k = (int)threadIdx.x + j * (int)blockDim.x;
-        const size_t i = base + (k < lt.Vs ? k : 0);
-        p0[j] = B.p[i];
-        u0[j] = B.u[i];
-        s0[j] = B.s[i];
-        w0[j] = B.w[i];
-        r0[j] = B.r[i];
-        x0[j] = B.x[i];
-    }
+        for (int j = 0; j < kUpdPre; j++) {
+            const int k = k0 + j * (int)blockDim.x;
+            i[j] = base + (k < lt.Vs ? k : 0);
+            p0[j] = B.p[i[j]];
+            u0[j] = B.u[i[j]];
+            s0[j] = B.s[i[j]];
+            w0[j] = B.w[i[j]];
+            r0[j] = B.r[i[j]];
+        }
+        if (behind)
+#pragma unroll
+            for (int j = 0; j < kUpdPre; j++) x0[j] = B.x[i[j]];
+    };
+    fetch(threadIdx.x);
     const R* tb = nullptr;
     if constexpr (DFT) tb = sp_tables<R, TL>(tab, V + sg.L * sg.ld, sg);
     for (int q = wave; q <= kNP6; q += nw) {
@@ -1444,7 +1468,7 @@ __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBu
 #pragma unroll
     for (int k = 0; k <= kNP6; k++) pr[k] = red[k];
     const double rr = pr[0], gam = pr[1], del = pr[2], done = sl[S_DONE];
-    const int it = (int)sl[S_ITERS], maxit = (int)sl[S_MAXIT];
+    const int maxit = (int)sl[S_MAXIT];
     double alpha = 0.0, beta = 0.0;
     bool go = false, resume = false;
     if (done == 0.0) {
@@ -1511,50 +1535,55 @@ __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBu
     if (blockIdx.x == 0 && threadIdx.x == 0)
 #pragma unroll
         for (int k = 0; k < S_NSLOT; k++) sout[k] = sl[k];
-    if (tau < 0 || !(go || resume)) return;
-    if (resume) {
-        if constexpr (DFT) {
-            auto place = [&](int k, cplx<R> v) {
-                const int y = k / sg.L;
-                *reinterpret_cast<cplx<R>*>(V + y * sg.ld + 2 * (k - y * sg.L)) = v;
-            };
+    if (tau < 0) return;
+    // f(site, the site's vectors), the first kUpdPre sites of a thread from its
+    // registers, the others as many at a time
+    const int stride = kUpdPre * (int)blockDim.x;
+    auto each = [&](auto&& f) {
+        for (int k0 = threadIdx.x; k0 < lt.Vs; k0 += stride) {
 #pragma unroll
             for (int j = 0; j < kUpdPre; j++) {
-                const int k = (int)threadIdx.x + j * (int)blockDim.x;
-                if (k < lt.Vs) place(k, r0[j]);
+                const int k = k0 + j * (int)blockDim.x;
+                if (k < lt.Vs) f(k, p0[j], u0[j], s0[j], w0[j], r0[j], x0[j]);
             }
-            for (int k = (int)threadIdx.x + kUpdPre * (int)blockDim.x; k < lt.Vs; k += blockDim.x)
-                place(k, B.r[base + k]);
+            if (k0 + stride < lt.Vs) fetch(k0 + stride);
+        }
+    };
+    auto step = [](cplx<double> x, double al, cplx<R> p) {
+        x.re += al * (double)p.re;
+        x.im += al * (double)p.im;
+        return x;
+    };
+    if (!go && done == 0.0 && behind)
+        each([&](int k, cplx<R> pk, cplx<R>, cplx<R>, cplx<R>, cplx<R>, cplx<double> xv) {
+            B.x[base + k] = step(xv, aprev, pk);
+        });
+    if (!(go || resume)) return;
+    if (resume) {
+        if constexpr (DFT) {
+            each([&](int k, cplx<R>, cplx<R>, cplx<R>, cplx<R>, cplx<R> rk, cplx<double>) {
+                const int y = k / sg.L;
+                *reinterpret_cast<cplx<R>*>(V + y * sg.ld + 2 * (k - y * sg.L)) = rk;
+            });
             sp_forward<R, NY, NX>(V, sg, tb, vhat + base);
         }
         return;
     }
     const R a = (R)alpha, b = (R)beta;
-    auto update = [&](int k, cplx<R> pk, cplx<R> uk, cplx<R> sk, cplx<R> wk, cplx<R> rk, cplx<double> xv) {
+    each([&](int k, cplx<R> pk, cplx<R> uk, cplx<R> sk, cplx<R> wk, cplx<R> rk, cplx<double> xv) {
         const size_t i = base + k;
         const cplx<R> pn = cfma(b, pk, uk);
         const cplx<R> sn = cfma(b, sk, wk);
         B.p[i] = pn;
         B.s[i] = sn;
-        xv.re += alpha * (double)pn.re;
-        xv.im += alpha * (double)pn.im;
-        B.x[i] = xv;
+        if (behind) B.x[i] = step(step(xv, aprev, pk), alpha, pn);
         const cplx<R> rn = cfma(-a, sn, rk);
         B.r[i] = rn;
         if (DFT) {
             const int y = k / sg.L;
             *reinterpret_cast<cplx<R>*>(V + y * sg.ld + 2 * (k - y * sg.L)) = rn;
         }
-    };
-#pragma unroll
-    for (int j = 0; j < kUpdPre; j++) {
-        const int k = (int)threadIdx.x + j * (int)blockDim.x;
-        if (k < lt.Vs) update(k, p0[j], u0[j], s0[j], w0[j], r0[j], x0[j]);
-    }
-    for (int k = (int)threadIdx.x + kUpdPre * (int)blockDim.x; k < lt.Vs; k += blockDim.x) {
-        const size_t i = base + k;
-        update(k, B.p[i], B.u[i], B.s[i], B.w[i], B.r[i], B.x[i]);
-    }
+    });
     if constexpr (DFT) sp_forward<R, NY, NX>(V, sg, tb, vhat + base);
 }
 
@@ -1831,8 +1860,10 @@ static qedhmc_status pcg_chunk(qedhmc_ctx* h, const PcgBufs<R>& B, int kpar, int
                 return QEDHMC_OK;
             }));
         else
-            hipLaunchKernelGGL((k_pcg_upd<R, 0, 0, false>), dim3(slice_grid(h->lat.Nt)), dim3(256), 0, h->stream,
-                               h->lat, B, h->scal, kpar, mixed ? 1 : 0, updates ? 1 : 0, sg, (const R*)nullptr,
+            // (four sites a thread, as many as it requests at once)
+            hipLaunchKernelGGL((k_pcg_upd<R, 0, 0, false>), dim3(slice_grid(h->lat.Nt)),
+                               dim3(std::clamp((h->lat.Vs / kUpdPre + 63) / 64 * 64, 256, spec_max_threads<R>())), 0,
+                               h->stream, h->lat, B, h->scal, kpar, mixed ? 1 : 0, updates ? 1 : 0, sg, (const R*)nullptr,
                                (cplx<R>*)nullptr);
         kpar ^= 1;
         const double* stop = h->scal + S_NSLOT * kpar + S_DONE;
@@ -2038,7 +2069,8 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
     QH_HIP(hipGetLastError());
     QH_TRY(pcg_tail<R>(h, B, nullptr, identity));
     while (true) {
-        const int left = maxit - it;
+        // one launch past the budget stops the recursion and brings x up to date
+        const int left = maxit - it + 1;
         const int n = left < chunk ? left : chunk;
         auto enqueue = [&]() { return pcg_chunk<R>(h, B, kpar, n, mixed, identity); };
         if (n == chunk && !no_graph) {
@@ -2054,7 +2086,7 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
         QH_TRY(read_slot(h, kpar));
         it = (int)h->h_pinned[S_ITERS];
         const double flag = h->h_pinned[S_DONE];
-        if (flag == 0.0 && it < maxit) continue;
+        if (flag == 0.0) continue;
         if (flag == 4.0) {
             broken = true;
             set_error("PCG breakdown: non-finite inner products after " + std::to_string(it) + " iterations");

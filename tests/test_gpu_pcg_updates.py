@@ -54,3 +54,29 @@ def test_solves_at_edges(L, Nt, prec, monkeypatch):
         _, st, it0, rel0 = solve(bad, TOL)
         assert st == Q.ENOCONV and it0 == 0 and rel0 == 1.0
         assert np.array_equal(solve(rhs, TOL)[0], x)  # not carried over
+
+
+@pytest.mark.parametrize("L,Nt", [(66, 6), (70, 4)])
+@pytest.mark.parametrize("prec,close", [("fp64", 1e-11), ("fp32", 1e-5)])
+def test_budgets_of_the_two_launch_cg(L, Nt, prec, close):
+    """Odd and even budgets on slices of more than 1024 cells (the solution
+    takes two steps at a time) against textbook CG with the FP64 operator: the
+    same iterates up to rounding, 1e-16 (FP32 recursion: 1e-7) growing by the
+    condition of at most 8 steps."""
+    th = _dev(inputs.noisy_pi_flux_theta(L, Nt, 0.3, 3 + L))
+    b = _dev(inputs.gauss_cvec(L, Nt, 4 + L).reshape(Nt, L, L))
+    with Q.Lattice(L, Nt) as lat:
+        x, r = torch.zeros_like(b), b.clone()
+        p, rr = r.clone(), torch.sum(r.abs() ** 2)
+        want = {}
+        for k in range(1, 9):
+            s = lat.apply_MdagM(th, p, prec="fp64")
+            alpha = rr / torch.sum((p.conj() * s).real)
+            x, r = x + alpha * p, r - alpha * s
+            rn = torch.sum(r.abs() ** 2)
+            p, rr = r + (rn / rr) * p, rn
+            want[k] = x
+        for k in (1, 2, 7, 8):
+            got, st, it, _ = lat.cg_solve(th, b, tol=1e-12, maxit=k, prec=prec)
+            err = float(torch.linalg.vector_norm(got - want[k]) / torch.linalg.vector_norm(want[k]))
+            assert st == Q.ENOCONV and it == k and err < close, (L, k, err)
