@@ -23,8 +23,8 @@ Prints one JSON line.  The roofline block is for the dominant kernel of the
 timed path, by default the fused CG iteration k_cg_iter (one launch per
 iteration: recurrences, x update, M^dag M, inner products).  Its algorithmic
 bytes per site are, in the mixed path, r, w, s, p read (4 x 8 B), two FP32
-angles (8 B), x read and written (2 x 16 B, FP64) and r, s, p, w written
-(4 x 8 B): 104 B per site (176 B in FP64).  Its duration comes from event
+angles (8 B), x read and written at every second iteration (16 B on average,
+FP64) and r, s, p, w written (4 x 8 B): 88 B per site (160 B in FP64).  Its duration comes from event
 pairs around every 8th graph replay of 51 back-to-back iteration launches (a
 replay holds nothing else) over the timed region; `traffic` is the
 counter-measured HBM bytes per launch.  The metric's M^dag M bandwidth is
@@ -53,14 +53,14 @@ VALU_PEAK_FP32_TFLOPS = 157.3
 VALU_PEAK_FP64_TFLOPS = 78.6
 
 # HBM bytes per launch of the fused CG iteration from rocprofv3 counters
-# (profiles/k_cg_iter_mixed_l24_hbm_counters.md): FETCH_SIZE and WRITE_SIZE in
-# KiB, scaled by the copy-kernel calibration (x2.0 and x1.0).  Valid for the
-# kernel as measured there; set to None whenever k_cg_iter changes.
-CG_ITER_COUNTER_BYTES = {"fp32": (4652.0 * 2.0 + 6491.4 * 1.0) * 1024, "fp64": None}
+# (profiles/mixed_l24_and_cases.md): FETCH_SIZE and WRITE_SIZE in KiB, the mean
+# of the launches that leave and that take x, scaled by the copy-kernel
+# calibration (x2.0 and x1.0).  Valid for the kernel as measured there; set to
+# None whenever k_cg_iter changes.
+CG_ITER_COUNTER_BYTES = {"fp32": (4086.3 * 2.0 + 5410.1 * 1.0) * 1024, "fp64": None}
 # the same for the spectral preconditioner's tau-sum + inverse-DFT kernel at
-# L=24, Nt=240 with a tau reach of 12 (profiles/k_pcs_tconv_idft_mixed_l24.md):
-# 2009.0 KiB fetched, 1080.0 KiB written per live launch, x2.0 and x1.0
-PC_SPEC_COUNTER_BYTES = {"fp32": (2009.0 * 2.0 + 1080.0 * 1.0) * 1024, "fp64": None}
+# L=24, Nt=240 with a tau reach of 12: 1523.5 KiB fetched, 1080.0 KiB written
+PC_SPEC_COUNTER_BYTES = {"fp32": (1523.5 * 2.0 + 1080.0 * 1.0) * 1024, "fp64": None}
 
 
 def parse():
@@ -278,7 +278,7 @@ def run_batched(a):
     one step = one trajectory of every chain; value = sites x trajectories
     per second.  The roofline block is the batched CG iteration k_b_cg_iter at the
     autotuned tile shape, timed by the autotuner with events around 24
-    back-to-back launches with every chain active (104 B per site of every
+    back-to-back launches with every chain active (88 B per site of every
     chain, as k_cg_iter)."""
     import numpy as np
     import torch
@@ -305,7 +305,7 @@ def run_batched(a):
     mc, nt, nb, us = b.tile("fp32" if prec != "fp64" else "fp64")
     shape_idx = {(1, 2): 0, (2, 2): 1, (1, 1): 2, (2, 1): 3}[(mc, nb)]
     N = sum(L * L * Nt for L, Nt in sizes)
-    it_bytes = (104 if prec != "fp64" else 176) * N
+    it_bytes = (88 if prec != "fp64" else 160) * N
     it_us = float(us[shape_idx])
     achieved = it_bytes / (it_us * 1e-6) / 1e9
     s_per = elapsed / a.steps
@@ -343,7 +343,7 @@ def run_se(a):
     precision, true residual 1e-8, one gauge field for all 40 right-hand
     sides) and the FFT-averaged spin correlator over the 780 probe pairs, at
     L=24, Nt=240 on the angles of the trajectory workload.  value = seconds
-    per measurement.  The roofline block is the solve phase: 104 B per site
+    per measurement.  The roofline block is the solve phase: 88 B per site
     and right-hand side for every batched CG iteration (as k_cg_iter), over
     the solve's measured time (reliable updates and launch gaps included:
     a lower bound on the kernel's rate)."""
@@ -387,9 +387,11 @@ def run_se(a):
     iters = np.array([r[1] for r in rows])
     # every launch of the batched iteration covers the right-hand sides still running
     it_sum = float(iters.sum(axis=1).mean())
-    achieved = (104 if prec != "fp64" else 176) * N * it_sum / t_solve / 1e9
+    achieved = (88 if prec != "fp64" else 160) * N * it_sum / t_solve / 1e9
     npairs = n_rv * (n_rv - 1) // 2
-    dft_flop = 8.0 * N * (2 * L + Nt)          # one 3-D DFT by direct sums along each axis
+    # one 3-D DFT by direct sums along each axis, a quarter of their products
+    # left by pairing the points k and n - k
+    dft_flop = 2.0 * N * (2 * L + Nt)
     corr_tflops = (2 * npairs + 1) * dft_flop / t_corr / 1e12
     Ch = C.cpu().numpy()
     out = {
@@ -408,11 +410,11 @@ def run_se(a):
         "status": [int(r[0]) for r in rows],
         "C_S": {"Delta0": float(Ch[0, 0, 0].real), "Delta_x1": float(Ch[0, 0, 1].real),
                 "Delta_tau1": float(Ch[1, 0, 0].real)},
-        "correlator": {"kernels": "k_se_xy / k_se_t / k_se_accum (FP64 DFTs by direct sums)",
+        "correlator": {"kernels": "k_se_xy / k_se_t_acc (FP64 DFTs as MFMA products)",
                        "dft_count": 2 * npairs + 1, "tflops": corr_tflops, "peak_fp64_tflops": 78.6},
         "roofline": {"bound": "hbm", "kernel": "k_b_cg_iter (multi-RHS CG iteration, 40 right-hand sides)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": None, "alg_bytes_per_launch": (104 if prec != "fp64" else 176) * N * n_rv,
+                     "traffic": None, "alg_bytes_per_launch": (88 if prec != "fp64" else 160) * N * n_rv,
                      "timing": "solve phase between events (includes updates and launch gaps)"},
     }
     se.close()
@@ -901,18 +903,19 @@ def main():
                                                 "k_conv_mfma<true> (one 32->32 3x3x3 layer, BF16 MFMA)")
     elif pc == "paper":
         # the largest of the PCG iteration's three kernels: the tau sum over
-        # 2R + 1 offsets (2 x 2 blocks: 2(2R + 1) complex FMAs per site) and
-        # the inverse DFT (L/2 + L complex FMAs per site), 8 flops per complex
-        # FMA; 43 flops per algorithmic HBM byte (16 B per site) at R = 12,
-        # so vector-ALU bound by the roofline
+        # 2R + 1 offsets (2 x 2 blocks: 2(2R + 1) complex FMAs per site, 8
+        # flops each, on the vector ALUs) and the inverse DFT (L/2 + L complex
+        # FMAs per site, a quarter of them left by pairing the points k and
+        # n - k, on the FP32 / FP64 matrix cores); 30 flops per algorithmic
+        # HBM byte (16 B per site) at R = 12, so ALU bound by the roofline
         kcls = Q.K_PC_SPEC_FP32 if prec != "fp64" else Q.K_PC_SPEC_FP64
-        work = 8.0 * (2 * (2 * Q.PC_TAU_REACH + 1) + wl.L // 2 + wl.L) * N
+        work = (16.0 * (2 * Q.PC_TAU_REACH + 1) + 2.0 * (wl.L // 2 + wl.L)) * N
         unit, bound, peak = "TFLOP/s", "alu", (VALU_PEAK_FP32_TFLOPS if prec != "fp64" else VALU_PEAK_FP64_TFLOPS)
-        kname = (f"k_pcs_tconv_idft<{'float' if prec != 'fp64' else 'double'}> (spectral paper preconditioner: "
+        kname = (f"k_pcs_tsum_inv<{'float' if prec != 'fp64' else 'double'}> (spectral paper preconditioner: "
                  f"tau sum + inverse 2D DFT; 200 applications of P back to back)")
     else:
         kcls = Q.K_CG_FP32 if prec != "fp64" else Q.K_CG_FP64
-        work, unit, bound, peak = (104 if prec != "fp64" else 176) * N, "GB/s", "hbm", HBM_PEAK_GBS
+        work, unit, bound, peak = (88 if prec != "fp64" else 160) * N, "GB/s", "hbm", HBM_PEAK_GBS
         kname = f"k_cg_iter<{'float' if prec != 'fp64' else 'double'}> (one fused CG iteration)"
     n_k, ms_k = pc_block if pc == "paper" else prof[kcls]
     avg_ms = ms_k / max(n_k, 1)
