@@ -444,11 +444,12 @@ qedhmc_status qedhmc_hmc_trajectory(qedhmc_t h, double* theta, uint64_t traj, in
     double max_rel = 0.0;
     // The solves after the first share eta and see theta moved by one drift:
     // each starts from the previous X (QEDHMC_WARM_START=0, read per
-    // trajectory, starts every solve from zero).  It solves O e = eta - O X
-    // for the correction from zero, to the tolerance that keeps the same
-    // target |eta - O (X + e)| <= tol |eta|, and adds e to X; solves that
-    // reach the tolerance give the same X to that tolerance, and every solver
-    // (CG, PCG, flexible CG) runs unchanged.
+    // trajectory, starts every solve from zero).  The PCG starts from X itself
+    // where its updates run inside its launches; otherwise O e = eta - O X is
+    // solved for the correction from zero, to the tolerance that keeps the same
+    // target |eta - O (X + e)| <= tol |eta|, e is added to X, and the solver
+    // (CG, PCG, flexible CG) runs unchanged.  Solves that reach the tolerance
+    // give the same X to that tolerance either way.
     const char* ews = std::getenv("QEDHMC_WARM_START");
     const bool warm_ok = !(ews && *ews && std::atoi(ews) == 0);
     double* bres = (double*)h->ws[0];  // eta - O X
