@@ -1156,8 +1156,8 @@ static qedhmc_status launch_pcs_rest(qedhmc_ctx* h, const cplx<R>* vhat, cplx<R>
     if (!spec_fused(h)) {
         // Runs of 6 slices (a run reads 24 slices more than it writes) once
         // they give a thread to every lane of the chip, of 3 below.  P at
-        // L = 66, N_tau = 660 with runs of 4 / 6 / 8 / 10: FP32 87.4 / 81.2 /
-        // 82.3 / 83.7 us, FP64 (N_tau = 640) 171 / 156 / - / 154 us.
+        // L = 66, N_tau = 660 with runs of 3 / 4 / 5 / 6: FP32 77.9 / 76.7 /
+        // 81.7 / 77.3 us, FP64 (N_tau = 640) 153 / 147 / 149 / 145 us.
         auto runs = [&]<int T>() {
             const int nth = (g.nk + 7) / 8 * ((g.Nt + T - 1) / T);  // of an XCD, at most
             hipLaunchKernelGGL((k_pcs_tsum<R, T>), dim3(8 * ((nth + 255) / 256)), dim3(256), 0, h->stream, g,
