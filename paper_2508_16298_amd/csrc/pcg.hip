@@ -1005,7 +1005,7 @@ __global__ __launch_bounds__(512) void k_pcs_tsum_inv(PcSpecGeo g, const cpair<R
     R* V = reinterpret_cast<R*>(smem);
     const int tau = slice_of_block(blockIdx.x, g.Nt), nk = g.nk;
     if (tau < 0) return;
-    // (looked at once the first momentum's sum is in LDS: one round trip less)
+    // (looked at once the first momentum's sum is formed: one round trip less)
     const double done = stop ? *stop : 0.0;
     const R* tb = sp_tables<R, TL>(tab, V + g.L * g.ld, g);
     constexpr int CH = sizeof(R) == 8 ? 3 : 6;  // offsets per load batch
@@ -1039,8 +1039,9 @@ __global__ __launch_bounds__(512) void k_pcs_tsum_inv(PcSpecGeo g, const cpair<R
         sp_up<R>(z, hc0, hc1, vc);
         const int y = k / g.Lh;
         *reinterpret_cast<cpair<R>*>(V + y * g.ld + 4 * (k - y * g.Lh)) = z;
-        if (done != 0.0) return;
+        if (done != 0.0) break;
     }
+    if (done != 0.0) return;  // every thread, those without a momentum too
     sp_inverse<R, NY, NX>(V, g, tb, out + (size_t)tau * g.Vs);
 }
 
@@ -1234,15 +1235,16 @@ qedhmc_status launch_apply_precond_fp32(qedhmc_ctx* h, const double* in, double*
     return QEDHMC_OK;
 }
 
-qedhmc_status launch_apply_precond(qedhmc_ctx* h, qedhmc_precision prec, const void* in, void* out) {
+qedhmc_status launch_apply_precond(qedhmc_ctx* h, qedhmc_precision prec, const void* in, void* out,
+                                   const double* stop) {
     QH_TRY(ensure_paper_precond(h));
     // the caller's vectors are read and written element by element; the
     // momentum form lives in the handle's scratch
     if (prec == QEDHMC_FP64)
         return apply_P_t<double>(h, (const cplx<double>*)in, (cplx<double>*)out, (cplx<double>*)h->ws[9],
-                                 (cplx<double>*)h->ws[8], nullptr);
+                                 (cplx<double>*)h->ws[8], stop);
     return apply_P_t<float>(h, (const cplx<float>*)in, (cplx<float>*)out, (cplx<float>*)h->ws[9],
-                            (cplx<float>*)h->ws[8], nullptr);
+                            (cplx<float>*)h->ws[8], stop);
 }
 
 // ---------------------------------------------------------------------------

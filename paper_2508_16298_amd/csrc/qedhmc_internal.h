@@ -679,7 +679,9 @@ bool pcg_warm_ok(const qedhmc_ctx* h);
 qedhmc_status cg2_solve_impl(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit,
                              qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable);
 qedhmc_status ensure_paper_precond(qedhmc_ctx* h);
-qedhmc_status launch_apply_precond(qedhmc_ctx* h, qedhmc_precision prec, const void* in, void* out);
+// (stop: nullable flag on the device; non-zero makes every launch a no-op)
+qedhmc_status launch_apply_precond(qedhmc_ctx* h, qedhmc_precision prec, const void* in, void* out,
+                                   const double* stop = nullptr);
 // FP64 in and out, stencil passes in FP32 (scratch ws[8], ws[9])
 qedhmc_status launch_apply_precond_fp32(qedhmc_ctx* h, const double* in, double* out);
 
