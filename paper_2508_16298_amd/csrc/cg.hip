@@ -2,6 +2,7 @@
 // (thin wrappers over the device bodies of cg_body.h, one workgroup per
 // time slice) and the host driver that launches them in chunks, reads the
 // stop flag once per chunk and runs the FP64 reliable updates.
+#include <algorithm>
 #include <cstdlib>
 
 #include "cg_body.h"
@@ -350,9 +351,9 @@ static qedhmc_status cg_t(qedhmc_ctx* h, const double* rhs, double* x, double to
     while (true) {
         // one launch past the budget marks a running solve for its final true
         // residual and brings x up to date
-        const int left = maxit - it + 1;
+        const int n = std::min(maxit - it, chunk - 1) + 1;
         // buffer parity: iterations since the last reliable update
-        QH_TRY(launch_iters<R>(h, B, kpar, it - itupd, left < chunk ? left : chunk, tol * tol, mixed ? 1 : 0, maxit));
+        QH_TRY(launch_iters<R>(h, B, kpar, it - itupd, n, tol * tol, mixed ? 1 : 0, maxit));
         QH_TRY(read_slot(h, kpar));
         it = (int)h->h_pinned[S_ITERS];
         itupd = (int)h->h_pinned[S_ITUPD];

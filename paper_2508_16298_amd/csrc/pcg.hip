@@ -2072,8 +2072,7 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
     QH_TRY(pcg_tail<R>(h, B, nullptr, identity));
     while (true) {
         // one launch past the budget stops the recursion and brings x up to date
-        const int left = maxit - it + 1;
-        const int n = left < chunk ? left : chunk;
+        const int n = std::min(maxit - it, chunk - 1) + 1;
         auto enqueue = [&]() { return pcg_chunk<R>(h, B, kpar, n, mixed, identity); };
         if (n == chunk && !no_graph) {
             qedhmc_ctx::PcgGraph key{};
