@@ -174,8 +174,12 @@ __device__ __forceinline__ void cg_iter_body(const Lat& lt, const CgBufs<R>& B, 
     }
     // (with the halo later, where s and w are gone from the registers: FP64 98.0
     // -> 88.9 ms, FP32 50.3 -> 49.4 ms a trajectory of 16 chains of 8 to 20 cells
-    // a side)
-    constexpr bool late = HALO;
+    // a side.  FP64 with two cells a thread has no registers for the phases beside
+    // the three slices, nor for x under the operator: 200 iterations of four
+    // chains of 44 cells a side took 18.2 ms with both, 15.3 ms without, and
+    // 16.1 ms with x read and written every time)
+    constexpr bool tight = MC == 2 && sizeof(R) == 8;
+    constexpr bool late = HALO || tight;
     cplx<R> hm[MC][12], ht[MC][12];
     auto hops = [&]() {
         hops_of<R, MC>(gptr(gauge), lt, c.tm, c.idx, co, hm);
@@ -297,24 +301,28 @@ __device__ __forceinline__ void cg_iter_body(const Lat& lt, const CgBufs<R>& B, 
     } else {
         advance(rm, sm, wm);
         advance(rn, sn, wn);
+        if constexpr (late) hops();
     }
     store_cells<R, MC>(st, gptr(B.s[nx]) + c.tau * Vs, c.g, c.own);
     store_cells<R, MC>(rt, gptr(B.r[nx]) + c.tau * Vs, c.g, c.own);
     store_cells<R, MC>(pp, gptr(B.p) + c.tau * Vs, c.g, c.own);
     // x_{i+1} = x_{i-1} + alpha_{i-1} p_{i-1} + alpha_i p_i in FP64, on its way
-    // while the operator runs
+    // while the operator runs (tight: before it)
     Cells<double, MC> xo;
+    auto step_x = [&]() {
+        if (!ip) return;
+        add_scaled<R, MC>(xo, aprev, pold);
+        add_scaled<R, MC>(xo, alpha, pp);
+        store_cells<double, MC>(xo, gptr(B.x) + c.tau * Vs, c.g, c.own);
+    };
     if (ip) load_cells<double, MC>(xo, gptr(B.x) + c.tau * Vs, c.g);
+    if constexpr (tight) step_x();
     const Cells<R, MC> rnew = rt;
     Cells<R, MC> w;
     mdagm_cells<R, MC, NB>(rm, rt, rn, hm, ht, c.g, c.own, co, c.tau == 0 ? R(-1) : R(1),
                            c.tau == lt.Nt - 1 ? R(-1) : R(1), buf2, lt.Vs, w);
     store_cells<R, MC>(w, gptr(B.w[nx]) + c.tau * Vs, c.g, c.own);
-    if (ip) {
-        add_scaled<R, MC>(xo, aprev, pold);
-        add_scaled<R, MC>(xo, alpha, pp);
-        store_cells<double, MC>(xo, gptr(B.x) + c.tau * Vs, c.g, c.own);
-    }
+    if constexpr (!tight) step_x();
     double v[kNP - 1] = {dot_cells<R, MC>(rnew, rnew, c.own), dot_cells<R, MC>(w, rnew, c.own),
                      dot_cells<R, MC>(rnew, st, c.own), dot_cells<R, MC>(pp, w, c.own),
                      dot_cells<R, MC>(pp, st, c.own)};
