@@ -27,7 +27,7 @@ __global__ __launch_bounds__(BS) void k_cg_iter(Lat lt, CgBufs<R> B, const cplx<
     const int tau = slice_of_block(blockIdx.x, lt.Nt);
     if (tau < 0) return;
     const Tile tl = whole_block_tile(smem, reinterpret_cast<double*>(smem + (size_t)NB * 2 * lt.Vs * sizeof(cplx<R>)));
-    cg_iter_body<R, MC, NB, (BS > 256 ? 257 : 64), false>(lt, B, gauge, co, scal, kpar, ipar, tol2, mixed, maxit, tau, tau == 0, tl);
+    cg_iter_body<R, MC, NB, (BS > 512 ? 513 : (BS > 256 ? 257 : 64)), false>(lt, B, gauge, co, scal, kpar, ipar, tol2, mixed, maxit, tau, tau == 0, tl);
 }
 
 template <typename R, int MC, int NB, int BS>

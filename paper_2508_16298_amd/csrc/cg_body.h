@@ -177,8 +177,10 @@ __device__ __forceinline__ void cg_iter_body(const Lat& lt, const CgBufs<R>& B, 
     // a side.  FP64 with two cells a thread has no registers for the phases beside
     // the three slices, nor for x under the operator: 200 iterations of four
     // chains of 44 cells a side took 18.2 ms with both, 15.3 ms without, and
-    // 16.1 ms with x read and written every time)
-    constexpr bool tight = MC == 2 && sizeof(R) == 8;
+    // 16.1 ms with x read and written every time.  Workgroups of more than 512
+    // threads have 128 registers: L = 48, N_tau = 480 62.3 -> 57.6 ms a 300
+    // iterations)
+    constexpr bool tight = sizeof(R) == 8 && (MC == 2 || THREADS > 512);
     constexpr bool late = HALO || tight;
     cplx<R> hm[MC][12], ht[MC][12];
     auto hops = [&]() {
