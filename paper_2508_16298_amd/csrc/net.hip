@@ -245,13 +245,13 @@ __global__ void k_features(NetGeo g, const cplx<float>* __restrict__ g32, const 
     feat[(size_t)m * 8 + 7] = 0.0f;
 }
 
-// grad[e] = sum over chunks b (in order) of part[b][e]
+// grad[e] = sum over chunks b (in order, in FP64) of part[b][e]
 __global__ void k_wgrad_reduce(const float* __restrict__ part, int nchunk, int E, float* __restrict__ grad) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= E) return;
-    float s = 0.0f;
-    for (int b = 0; b < nchunk; b++) s += part[(size_t)b * E + e];
-    grad[e] = s;
+    double s = 0.0;
+    for (int b = 0; b < nchunk; b++) s += (double)part[(size_t)b * E + e];
+    grad[e] = (float)s;
 }
 
 // The same sum in two passes for many chunks: group g of kWgGroups adds its
@@ -264,9 +264,9 @@ __global__ void k_wgrad_reduce_groups(const float* __restrict__ part, int nchunk
     if (e >= E) return;
     const int per = (nchunk + kWgGroups - 1) / kWgGroups;
     const int b0 = gidx * per, b1 = min(nchunk, b0 + per);
-    float s = 0.0f;
-    for (int b = b0; b < b1; b++) s += part[(size_t)b * E + e];
-    tmp[(size_t)gidx * E + e] = s;
+    double s = 0.0;
+    for (int b = b0; b < b1; b++) s += (double)part[(size_t)b * E + e];
+    tmp[(size_t)gidx * E + e] = (float)s;
 }
 
 // ---------------------------------------------------------------------------

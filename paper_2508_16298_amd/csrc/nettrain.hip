@@ -447,14 +447,21 @@ __global__ __launch_bounds__(256) void k_wgrad_brick(NetGeo g, Brick b, const fl
     }
 }
 
-// workgroups (one partial each) of layer l's weight gradient; every lattice
-// has at least one brick
+// Workgroups (one partial each) of layer l's weight gradient; every lattice has
+// at least one brick.  A workgroup's FP32 sums run over all its bricks, so the
+// chip is filled as many times over as keeps them to 288 sites, 256 more for
+// every 2^19 sites; the partials are added in FP64.  Filled once at every size
+// the sums grew to 1500 sites: error against 64 bits in the hidden layers, in
+// units of the sum's own random size, at N = 262144, 524288, 1048576 4.4e-7,
+// 5.7e-7, 6.9e-7; now 2.8e-7, 2.9e-7, 4.0e-7 (chunks of 256, 256, 512 sites, the
+// partials added in FP32: 3.1e-7, 3.3e-7, 3.9e-7).  Step at L = 48, N_tau = 228
+// 4.77 -> 4.99 ms, at L = 64, N_tau = 256 10.1 -> 9.6 ms.
 int wgrad_parts(const qedhmc_net* n, int l) {
     const Brick b = brick_of(n->g);
-    const int per_cu = l > 0 && l < kNetLayers - 1 ? 2 : 4;
-    // at most about 1500 sites per running sum, up to 2048 partials
-    const int most = std::max(n->h->n_cu * per_cu, std::min(2048, n->g.N / 1536));
-    return 8 * std::max(1, std::min(most / 8, (b.total + 7) / 8));
+    const int slots = n->h->n_cu * (l > 0 && l < kNetLayers - 1 ? 2 : 4);
+    const int most = (288 + (n->g.N - 1) / (1 << 19) * 256) / (b.BX * b.BY);  // bricks per workgroup
+    const int fills = (b.total + slots * most - 1) / (slots * most);
+    return 8 * std::max(1, std::min(slots * fills / 8, (b.total + 7) / 8));
 }
 
 qedhmc_status launch_wgrad_mfma(qedhmc_net* n, int l, const float* in, const float* gout) {
