@@ -1951,7 +1951,7 @@ static constexpr int kPcgTriples = 10;
 template <typename R>
 static qedhmc_status pcg_device(qedhmc_ctx* h, const PcgBufs<R>& B, const double* rhs, double* x, bool warm, double tol,
                                 int maxit, qedhmc_precision prec, bool direct, int* iters, double* true_rel,
-                                int* n_reliable) {
+                                int* n_reliable, long most) {
     const bool mixed = prec != QEDHMC_FP64;
     for (auto& e : h->cg_ev)
         if (!e) QH_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -1991,8 +1991,9 @@ static qedhmc_status pcg_device(qedhmc_ctx* h, const PcgBufs<R>& B, const double
     };
     // a triple iterates, or belongs to an update; three updates without an
     // iteration between them end the solve
-    const long max_rounds = (9L * maxit + 32) / kPcgTriples + 4;
+    const long max_rounds = most ? most : (9L * maxit + 32) / kPcgTriples + 4;
     long queued = 0;
+    bool over = false;
     double prev = -1.0;
     const double* r = nullptr;
     QH_TRY(round(queued++));
@@ -2002,21 +2003,18 @@ static qedhmc_status pcg_device(qedhmc_ctx* h, const PcgBufs<R>& B, const double
         QH_HIP(hipEventSynchronize(h->cg_ev[n & 1]));
         r = h->h_pinned + 32 + 16 * (n & 1);
         if (r[CR_DONE] == 4.0 || r[CR_DONE] == 5.0) break;
-        if (n + 2 >= max_rounds) {
-            QH_HIP(hipStreamSynchronize(h->stream));
-            set_error("PCG did not end within " + std::to_string(max_rounds) + " rounds");
-            return QEDHMC_ENOCONV;
-        }
+        over = n + 2 >= max_rounds;
+        if (over) break;
         if (queued < n + 2) QH_TRY(round(queued++));  // round n + 1 was held back wrongly
         const double tr = r[CR_EST], target = tol * tol * r[CR_B2];
         const bool last = prev > 0.0 && tr > 0.0 && tr * (tr / prev) <= target;
         prev = tr;
         if (!last && queued < n + 3) QH_TRY(round(queued++));
     }
-    const double rec[CR_N] = {r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7]};
     QH_HIP(hipMemcpyAsync(x, B.x, (size_t)h->lat.Nt * h->lat.Vs * sizeof(cplx<double>), hipMemcpyDeviceToDevice,
                           h->stream));
     QH_HIP(hipStreamSynchronize(h->stream));
+    const double* rec = h->h_pinned + 32 + 16 * ((queued - 1) & 1);  // rounds past the end repeat the slot
     const int it = (int)rec[CR_ITERS];
     if (iters) *iters = it;
     // (a breakdown before the first update: the start's residual, 1 from zero)
@@ -2024,6 +2022,7 @@ static qedhmc_status pcg_device(qedhmc_ctx* h, const PcgBufs<R>& B, const double
         *true_rel = rec[CR_NREL] == 0.0 && !warm ? 1.0 : (rec[CR_B2] > 0.0 ? std::sqrt(rec[CR_TRUE] / rec[CR_B2]) : 0.0);
     if (n_reliable) *n_reliable = (int)rec[CR_NREL];
     if (rec[CR_DONE] == 5.0) return QEDHMC_OK;
+    if (over) set_error("PCG did not end within " + std::to_string(max_rounds) + " rounds");
     switch ((int)rec[CR_WHY]) {
         case WHY_BREAKDOWN:
             set_error("PCG breakdown: non-finite inner products after " + std::to_string(it) + " iterations");
@@ -2046,7 +2045,8 @@ static qedhmc_status pcg_device(qedhmc_ctx* h, const PcgBufs<R>& B, const double
 // cells per thread and more registers than a 576-thread workgroup has.
 template <typename R>
 static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit, qedhmc_precision prec,
-                           int* iters, double* true_rel, int* n_reliable, bool identity, bool warm = false) {
+                           int* iters, double* true_rel, int* n_reliable, bool identity, bool warm = false,
+                           long most = 0) {
     if (!identity) QH_TRY(ensure_paper_precond(h));
     const bool mixed = prec != QEDHMC_FP64;
     PcgBufs<R> B = pbufs_of<R>(h);
@@ -2055,7 +2055,7 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
     // QEDHMC_NO_GRAPH (read per solve): no captured graphs
     const bool no_graph = std::getenv("QEDHMC_NO_GRAPH") != nullptr;
     if (!identity && h->lat.ncell <= kUpdCells)
-        return pcg_device<R>(h, B, rhs, x, warm, tol, maxit, prec, no_graph, iters, true_rel, n_reliable);
+        return pcg_device<R>(h, B, rhs, x, warm, tol, maxit, prec, no_graph, iters, true_rel, n_reliable, most);
     // iterations per host round trip: the plain recursion pauses after kCap at
     // most; with the paper's preconditioner a decade, and with it a pause, takes
     // about 9 to 30 iterations, and the launches past a pause are wasted (chunks
@@ -2135,10 +2135,11 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
 bool pcg_warm_ok(const qedhmc_ctx* h) { return h->lat.ncell <= kUpdCells; }
 
 qedhmc_status pcg_solve_impl(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit,
-                             qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable, bool warm) {
+                             qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable, bool warm,
+                             long most) {
     if (prec == QEDHMC_FP64)
-        return pcg_t<double>(h, rhs, x, tol, maxit, prec, iters, true_rel, n_reliable, false, warm);
-    return pcg_t<float>(h, rhs, x, tol, maxit, prec, iters, true_rel, n_reliable, false, warm);
+        return pcg_t<double>(h, rhs, x, tol, maxit, prec, iters, true_rel, n_reliable, false, warm, most);
+    return pcg_t<float>(h, rhs, x, tol, maxit, prec, iters, true_rel, n_reliable, false, warm, most);
 }
 
 qedhmc_status cg2_solve_impl(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit,

@@ -670,9 +670,11 @@ qedhmc_status launch_bond_tables(qedhmc_ctx* h);
 qedhmc_status cg_solve_impl(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit,
                             qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable);
 // warm: started from x instead of zero, to the same |rhs - O x| <= tol |rhs|
-// (where pcg_warm_ok: slices whose updates run inside the solver's launches)
+// (where pcg_warm_ok: slices whose updates run inside the solver's launches);
+// most: rounds of launches at most there (0: more than any solve takes)
 qedhmc_status pcg_solve_impl(qedhmc_ctx* h, const double* rhs, double* x, double tol, int maxit,
-                             qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable, bool warm = false);
+                             qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable, bool warm = false,
+                             long most = 0);
 bool pcg_warm_ok(const qedhmc_ctx* h);
 // plain CG as two launches per iteration (update; M^dag M with partials), for
 // lattices with more than 1024 cells per slice
