@@ -194,8 +194,8 @@ qedhmc_status qedhmc_apply_MdagM_noalloc(const qedhmc_params *params,
  * taken on the device on slices of at most 1024 cells without a preconditioner
  * and of at most 512 with one (otherwise by the host between chunks).  The
  * environment variable QEDHMC_NO_GRAPH (read on every call) makes the host
- * launch every iteration itself and, without a preconditioner, take every
- * decision (same results bit for bit; tests). */
+ * launch every iteration and take every decision itself (same results bit for
+ * bit; tests). */
 qedhmc_status qedhmc_cg_solve(qedhmc_t h, const double *theta,
                               const double *rhs, double *x, double tol,
                               int32_t maxit, qedhmc_precision prec,

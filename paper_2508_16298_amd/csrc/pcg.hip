@@ -1378,6 +1378,19 @@ __global__ __launch_bounds__(BS) void k_pcg_begin(Lat lt, PcgBufs<R> B, const cp
     }
 }
 
+// A wavefront's share of the sum of n partials, the same wherever it is taken
+__device__ __forceinline__ double lane_sum(const double* __restrict__ src, int n) {
+    double s = 0.0;
+    for (int i0 = threadIdx.x & 63; i0 < n; i0 += 4 * 64) {
+        double a[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) a[u] = i0 + 64 * u < n ? src[i0 + 64 * u] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; u++) s += a[u];
+    }
+    return s;
+}
+
 // One slice per block (dealt to the XCDs as slice_of_block deals them):
 // scalars from the partials, then the elementwise update.
 // DFT (NY > 0): the block then also transforms the new r of its slice (both
@@ -1421,17 +1434,7 @@ __global__ __launch_bounds__(spec_max_threads<R>()) void k_pcg_upd(Lat lt, PcgBu
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
     // sum q over the partials: q < 6 the inner products, q = 6 partb
     auto partial = [&](int q) {
-        const double* src = q < kNP6 ? B.part + (size_t)q * B.nparts : B.partb;
-        const int n = q < kNP6 ? B.nparts : lt.Nt;
-        double s = 0.0;
-        for (int i0 = lane; i0 < n; i0 += 4 * 64) {
-            double a[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++) a[u] = i0 + 64 * u < n ? src[i0 + 64 * u] : 0.0;
-#pragma unroll
-            for (int u = 0; u < 4; u++) s += a[u];
-        }
-        return s;
+        return q < kNP6 ? lane_sum(B.part + (size_t)q * B.nparts, B.nparts) : lane_sum(B.partb, lt.Nt);
     };
     double sum = wave <= kNP6 ? partial(wave) : 0.0;
     // x is behind by alpha_{i-1} p_{i-1} after an odd number of iterations since
@@ -1734,25 +1737,32 @@ __global__ __launch_bounds__(256) void k_pcg_rep(Lat lt, PcgBufs<R> B) {
     if (threadIdx.x == 0) B.partb[blockIdx.x] = v[0];
 }
 
-// After a replacement and a fresh u, w and partials: converged -> stop 1;
-// otherwise resume (restart sets beta = 0 on the next iteration).
-__global__ void k_pcg_check(double* __restrict__ scal, int kpar, const double* __restrict__ part, int nparts,
-                            const double* __restrict__ partb, int Nt, int restart) {
-    __shared__ double red[64];
-    double v[2] = {0.0, 0.0};
-    for (int t = threadIdx.x; t < Nt; t += blockDim.x) v[0] += partb[t];
-    for (int t = threadIdx.x; t < nparts; t += blockDim.x) v[1] += part[t];
-    block_sumk<2>(v, red);
+// After a replacement: converged -> stop 1; otherwise resume (restart sets
+// beta = 0 on the next iteration).  rr: the partials of the replaced r's
+// <r, r> in the working precision, or null (the FP64 residual is taken); b2:
+// at the start of a solve whose slot holds tol^2, the partials of |rhs|^2.
+__global__ void k_pcg_check(double* __restrict__ scal, int kpar, const double* __restrict__ rr, int nparts,
+                            const double* __restrict__ partb, int Nt, int restart, const double* __restrict__ b2) {
+    __shared__ double red[3];
+    const int wave = threadIdx.x >> 6;
+    const double* src = wave == 0 ? partb : (wave == 1 ? rr : b2);
+    const double s = wave_sum_f64(src ? lane_sum(src, wave == 1 ? nparts : Nt) : 0.0);
+    if ((threadIdx.x & 63) == 63) red[wave] = s;
+    __syncthreads();
     if (threadIdx.x == 0) {
         double* sl = scal + S_NSLOT * kpar;
-        sl[S_TRUE] = v[0];
-        if (v[0] <= sl[S_TARGET]) {
+        if (b2) {
+            sl[S_B2] = red[2];
+            sl[S_TARGET] *= red[2];
+        }
+        sl[S_TRUE] = red[0];
+        if (red[0] <= sl[S_TARGET]) {
             sl[S_DONE] = 1.0;
         } else {
             sl[S_DONE] = 0.0;
             if (restart) sl[S_FIRST] = 1.0;
             sl[S_ITUPD] = sl[S_ITERS];
-            sl[S_RRUPD] = v[1];
+            sl[S_RRUPD] = rr ? red[1] : red[0];
         }
     }
 }
@@ -1842,9 +1852,11 @@ static qedhmc_status pcg_tail(qedhmc_ctx* h, const PcgBufs<R>& B, const double* 
 }
 
 // n iterations from launch parity kpar: update, then preconditioner and
-// matvec, each gated on the slot's stop flag
+// matvec, each gated on the slot's stop flag.  decide: the update kernel also
+// takes the decision after a reliable update.
 template <typename R>
-static qedhmc_status pcg_chunk(qedhmc_ctx* h, const PcgBufs<R>& B, int kpar, int n, bool mixed, bool identity) {
+static qedhmc_status pcg_chunk(qedhmc_ctx* h, const PcgBufs<R>& B, int kpar, int n, bool mixed, bool identity,
+                               bool decide) {
     const bool updates = !identity && h->lat.ncell <= kUpdCells;  // inside the triples
     // spectral P: the update kernel does its first step
     const bool fdft = !identity && use_spectral<R>(h);
@@ -1858,14 +1870,14 @@ static qedhmc_status pcg_chunk(qedhmc_ctx* h, const PcgBufs<R>& B, int kpar, int
                 if (lds > 65536 - 2048) QH_TRY(allow_lds((const void*)k_pcg_upd<R, NY, NX, TL>, h->max_lds));
                 hipLaunchKernelGGL((k_pcg_upd<R, NY, NX, TL>), dim3(slice_grid(h->lat.Nt)),
                                    dim3(spec_threads(sg, sg.Vs, spec_max_threads<R>())), lds, h->stream, h->lat, B,
-                                   h->scal, kpar, mixed ? 1 : 0, updates ? 1 : 0, sg, spec_tab<R>(h), vhat);
+                                   h->scal, kpar, mixed ? 1 : 0, decide ? 1 : 0, sg, spec_tab<R>(h), vhat);
                 return QEDHMC_OK;
             }));
         else
             // (four sites a thread, as many as it requests at once)
             hipLaunchKernelGGL((k_pcg_upd<R, 0, 0, false>), dim3(slice_grid(h->lat.Nt)),
                                dim3(std::clamp((h->lat.Vs / kUpdPre + 63) / 64 * 64, 256, spec_max_threads<R>())), 0,
-                               h->stream, h->lat, B, h->scal, kpar, mixed ? 1 : 0, updates ? 1 : 0, sg, (const R*)nullptr,
+                               h->stream, h->lat, B, h->scal, kpar, mixed ? 1 : 0, decide ? 1 : 0, sg, (const R*)nullptr,
                                (cplx<R>*)nullptr);
         kpar ^= 1;
         const double* stop = h->scal + S_NSLOT * kpar + S_DONE;
@@ -1878,6 +1890,23 @@ static qedhmc_status pcg_chunk(qedhmc_ctx* h, const PcgBufs<R>& B, int kpar, int
     }
     QH_HIP(hipGetLastError());
     return QEDHMC_OK;
+}
+
+// the start of a solve on slices of up to kUpdCells cells (x0 null: from zero)
+template <typename R>
+static qedhmc_status launch_begin(qedhmc_ctx* h, const PcgBufs<R>& B, const double* rhs, const double* x0, double tol,
+                                  int maxit) {
+    return with_shape<double>(h, [&]<int MC, int NB, int BS>(int nt, size_t lds) -> qedhmc_status {
+        if constexpr (MC == 1 && BS <= 512) {
+            QH_TRY(lds_attr(h, k_pcg_begin<R, MC, NB, BS>, lds));
+            hipLaunchKernelGGL((k_pcg_begin<R, MC, NB, BS>), dim3(slice_grid(h->lat.Nt)), dim3(nt), lds, h->stream,
+                               h->lat, B, (const cplx<double>*)h->gauge64, coef_of<double>(h->p),
+                               (const cplx<double>*)rhs, (cplx<double>*)h->ws[2], (const cplx<double>*)x0, h->scal,
+                               tol * tol, maxit);
+            QH_HIP(hipGetLastError());
+        }
+        return QEDHMC_OK;
+    });
 }
 
 // Runs enqueue(), or replays it from the graph captured the first time this
@@ -1946,26 +1975,15 @@ static constexpr int kPcgTriples = 10;
 // L = 24, N_tau = 240, tol 1e-10 (mixed), 4.0 -> 3.0 ms per solve at tol 1e-12.  The host keeps the next one queued behind
 // the running one and holds it back only when the residual estimates of the
 // last two, extrapolated geometrically, say that the running one converges (a
-// wrong guess costs one host round trip).  direct (QEDHMC_NO_GRAPH): the same
-// launches without graphs.
+// wrong guess costs one host round trip).
 template <typename R>
 static qedhmc_status pcg_device(qedhmc_ctx* h, const PcgBufs<R>& B, const double* rhs, double* x, bool warm, double tol,
-                                int maxit, qedhmc_precision prec, bool direct, int* iters, double* true_rel,
-                                int* n_reliable, long most) {
+                                int maxit, qedhmc_precision prec, int* iters, double* true_rel, int* n_reliable,
+                                long most) {
     const bool mixed = prec != QEDHMC_FP64;
     for (auto& e : h->cg_ev)
         if (!e) QH_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    QH_TRY(with_shape<double>(h, [&]<int MC, int NB, int BS>(int nt, size_t lds) -> qedhmc_status {
-        if constexpr (MC == 1 && BS <= 512) {
-            QH_TRY(lds_attr(h, k_pcg_begin<R, MC, NB, BS>, lds));
-            hipLaunchKernelGGL((k_pcg_begin<R, MC, NB, BS>), dim3(slice_grid(h->lat.Nt)), dim3(nt), lds, h->stream,
-                               h->lat, B, (const cplx<double>*)h->gauge64, coef_of<double>(h->p),
-                               (const cplx<double>*)rhs, (cplx<double>*)h->ws[2],
-                               warm ? (const cplx<double>*)x : nullptr, h->scal, tol * tol, maxit);
-            QH_HIP(hipGetLastError());
-        }
-        return QEDHMC_OK;
-    }));
+    QH_TRY(launch_begin<R>(h, B, rhs, warm ? x : nullptr, tol, maxit));
     auto& graphs = h->pcg_round[sizeof(R) == 8 ? 1 : 0];
     // the first launches of a handle's first solve set the kernel attributes
     const bool eager0 = !graphs[0].exec;
@@ -1977,12 +1995,12 @@ static qedhmc_status pcg_device(qedhmc_ctx* h, const PcgBufs<R>& B, const double
         const int par = (int)(n & 1);
         double* out = h->h_pinned + 32 + 16 * par;
         auto enqueue = [&]() -> qedhmc_status {
-            QH_TRY(pcg_chunk<R>(h, B, 0, kPcgTriples, mixed, false));
+            QH_TRY(pcg_chunk<R>(h, B, 0, kPcgTriples, mixed, false, true));
             hipLaunchKernelGGL(k_pcg_record, dim3(1), dim3(64), 0, h->stream, (const double*)h->scal, out);
             QH_HIP(hipGetLastError());
             return QEDHMC_OK;
         };
-        if (direct || (n == 0 && eager0))
+        if (n == 0 && eager0)
             QH_TRY(enqueue());
         else
             QH_TRY(run_graph(h, graphs[par], key, enqueue));
@@ -2052,28 +2070,54 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
     PcgBufs<R> B = pbufs_of<R>(h);
     if (identity) B.u = B.r;
     const int Nt = h->lat.Nt;
-    // QEDHMC_NO_GRAPH (read per solve): no captured graphs
+    // QEDHMC_NO_GRAPH (read per solve): no captured graphs, and every decision here
     const bool no_graph = std::getenv("QEDHMC_NO_GRAPH") != nullptr;
-    if (!identity && h->lat.ncell <= kUpdCells)
-        return pcg_device<R>(h, B, rhs, x, warm, tol, maxit, prec, no_graph, iters, true_rel, n_reliable, most);
+    const bool small = !identity && h->lat.ncell <= kUpdCells;
+    if (small && !no_graph)
+        return pcg_device<R>(h, B, rhs, x, warm, tol, maxit, prec, iters, true_rel, n_reliable, most);
     // iterations per host round trip: the plain recursion pauses after kCap at
     // most; with the paper's preconditioner a decade, and with it a pause, takes
     // about 9 to 30 iterations, and the launches past a pause are wasted (chunks
     // of 51 and 12: 34.4 and 30.1 ms per solve at L = 66, N_tau = 600, tol 1e-12)
-    const int chunk = mixed ? (identity ? kCap + 1 : 12) : 64;
+    // (small: every iteration by itself, its matvec carrying out an update)
+    const int chunk = small ? 1 : (mixed ? (identity ? kCap + 1 : 12) : 64);
     int kpar = 0, nrel = 0, it = 0, stalled = 0, last_it = -1;
     double rel = 1.0;
     bool converged = false, broken = false;
-    hipLaunchKernelGGL(k_pcg_start<R>, dim3(Nt), dim3(256), 0, h->stream, h->lat, B, (const cplx<double>*)rhs,
-                       (cplx<double>*)h->ws[2]);
-    hipLaunchKernelGGL(k_pcg_init_slot, dim3(1), dim3(256), 0, h->stream, h->scal, (const double*)B.partb, Nt,
-                       tol * tol, maxit);
-    QH_HIP(hipGetLastError());
-    QH_TRY(pcg_tail<R>(h, B, nullptr, identity));
-    while (true) {
+    // the true residual's decision, into the slot and to the host
+    auto check = [&](bool restart, bool begin) -> qedhmc_status {
+        hipLaunchKernelGGL(k_pcg_check, dim3(1), dim3(192), 0, h->stream, h->scal, kpar,
+                           (const double*)(small ? nullptr : B.part), B.nparts, (const double*)B.partb, Nt,
+                           restart ? 1 : 0, (const double*)(begin ? B.part : nullptr));
+        QH_HIP(hipGetLastError());
+        QH_TRY(read_slot(h, kpar));
+        const double b2 = h->h_pinned[S_B2];
+        if (!std::isfinite(h->h_pinned[S_TRUE]) || !std::isfinite(b2)) {
+            broken = true;
+            set_error(begin ? "PCG breakdown: non-finite inner products after 0 iterations"
+                            : "PCG breakdown: non-finite true residual after " + std::to_string(it) + " iterations");
+        }
+        converged = !broken && h->h_pinned[S_DONE] == 1.0;
+        if (!begin || warm || converged) rel = b2 > 0.0 ? std::sqrt(h->h_pinned[S_TRUE] / b2) : 0.0;
+        return QEDHMC_OK;
+    };
+    if (small) {
+        QH_TRY(launch_begin<R>(h, B, rhs, warm ? x : nullptr, tol, maxit));
+        QH_TRY(check(true, true));
+        if (converged) nrel = 1;  // the start was this solve's check
+        if (!broken && !converged) QH_TRY(pcg_tail<R>(h, B, nullptr, false, true));
+    } else {
+        hipLaunchKernelGGL(k_pcg_start<R>, dim3(Nt), dim3(256), 0, h->stream, h->lat, B, (const cplx<double>*)rhs,
+                           (cplx<double>*)h->ws[2]);
+        hipLaunchKernelGGL(k_pcg_init_slot, dim3(1), dim3(256), 0, h->stream, h->scal, (const double*)B.partb, Nt,
+                           tol * tol, maxit);
+        QH_HIP(hipGetLastError());
+        QH_TRY(pcg_tail<R>(h, B, nullptr, identity));
+    }
+    while (!broken && !converged) {
         // one launch past the budget stops the recursion and brings x up to date
         const int n = std::min(maxit - it, chunk - 1) + 1;
-        auto enqueue = [&]() { return pcg_chunk<R>(h, B, kpar, n, mixed, identity); };
+        auto enqueue = [&]() { return pcg_chunk<R>(h, B, kpar, n, mixed, identity, false); };
         if (n == chunk && !no_graph) {
             qedhmc_ctx::PcgGraph key{};
             key.mixed = mixed ? 1 : 0;
@@ -2095,31 +2139,27 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
         }
         stalled = (it == last_it) ? stalled + 1 : 0;
         last_it = it;
-        if (stalled >= 3) {
+        if (!small && stalled >= 3) {
             set_error("PCG made no progress across reliable updates at iteration " + std::to_string(it));
             break;
         }
         // FP64 true residual; r replaced, s = O p refreshed, u, w and partials recomputed
-        QH_TRY(launch_mdagm(h, QEDHMC_FP64, B.x, h->ws[3], nullptr));
-        hipLaunchKernelGGL(k_pcg_rep<R>, dim3(Nt), dim3(256), 0, h->stream, h->lat, B);
-        QH_HIP(hipGetLastError());
-        QH_TRY(launch_mdagm(h, prec == QEDHMC_FP64 ? QEDHMC_FP64 : QEDHMC_FP32, B.p, B.s, nullptr));
-        QH_TRY(pcg_tail<R>(h, B, nullptr, identity));
-        hipLaunchKernelGGL(k_pcg_check, dim3(1), dim3(256), 0, h->stream, h->scal, kpar, (const double*)B.part,
-                           B.nparts, (const double*)B.partb, Nt, (!mixed || flag == 3.0) ? 1 : 0);
-        QH_HIP(hipGetLastError());
+        const bool restart = !mixed || flag == 3.0;
         nrel++;
-        QH_TRY(read_slot(h, kpar));
-        const double b2 = h->h_pinned[S_B2];
-        rel = b2 > 0.0 ? std::sqrt(h->h_pinned[S_TRUE] / b2) : 0.0;
-        if (!std::isfinite(rel)) {
-            broken = true;
-            set_error("PCG breakdown: non-finite true residual after " + std::to_string(it) + " iterations");
-            break;
-        }
-        if (h->h_pinned[S_DONE] == 1.0) {
-            converged = true;
-            break;
+        if (small) {
+            QH_TRY(check(restart, false));  // the matvec's launch has replaced r
+            if (!broken && !converged && it < maxit && stalled >= 3) {
+                set_error("PCG made no progress across reliable updates at iteration " + std::to_string(it));
+                break;
+            }
+            if (!broken && !converged && it < maxit) QH_TRY(pcg_tail<R>(h, B, nullptr, false, true));
+        } else {
+            QH_TRY(launch_mdagm(h, QEDHMC_FP64, B.x, h->ws[3], nullptr));
+            hipLaunchKernelGGL(k_pcg_rep<R>, dim3(Nt), dim3(256), 0, h->stream, h->lat, B);
+            QH_HIP(hipGetLastError());
+            QH_TRY(launch_mdagm(h, prec == QEDHMC_FP64 ? QEDHMC_FP64 : QEDHMC_FP32, B.p, B.s, nullptr));
+            QH_TRY(pcg_tail<R>(h, B, nullptr, identity));
+            QH_TRY(check(restart, false));
         }
         if (it >= maxit) break;
     }
