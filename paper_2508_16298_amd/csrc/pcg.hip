@@ -1080,16 +1080,19 @@ static bool use_spectral(const qedhmc_ctx* h) {
     return !ek || !*ek || std::strcmp(ek, "spectral") == 0;
 }
 
-// the tau sum fused into the inverse DFT up to this many momenta per plane
-// (each workgroup then reads H and 2 reach + 1 input slices through the L2):
-// P in FP32, fused / separate, L = 48 35.0 / 43.7 us, L = 56 45.4 / 47.6 us,
-// L = 66 99.4 / 81.2 us (77.7 since).  QEDHMC_PC_FUSE=0|1 (read per call) forces either form
-static constexpr int kSpecFuseNK = 1682;  // L = 58
-
+// The tau sum is fused into the inverse DFT on small slices (each workgroup then
+// reads H and 2 reach + 1 input slices through the L2, in FP64 three offsets at
+// a time).  P fused / separate, N_tau = 10 L: FP32 L = 24 15.2 / 18.9 us, L = 48
+// 38.1 / 38.9, L = 52 55.0 / 51.5, L = 58 66.5 / 53.8; FP64 L = 24 17.3 / 21.0,
+// L = 26 26.8 / 22.8, L = 40 50.9 / 46.5, L = 58 132 / 96.5.  A solve to 1e-8:
+// mixed L = 48, N_tau = 200 4.09 / 4.14 ms, L = 50 3.75 / 3.66, L = 58 4.79 /
+// 4.53; FP64 L = 24 2.25 / 2.44, L = 26, N_tau = 260 2.13 / 1.88, L = 40, N_tau =
+// 200 3.62 / 3.46.  QEDHMC_PC_FUSE=0|1 (read per call) forces either form.
+template <typename R>
 static bool spec_fused(const qedhmc_ctx* h) {
     const char* ef = std::getenv("QEDHMC_PC_FUSE");
     if (ef && *ef) return std::atoi(ef) != 0;
-    return h->lat.L * (h->lat.L / 2) <= kSpecFuseNK;
+    return h->lat.L <= (sizeof(R) == 8 ? 24 : 48);
 }
 
 template <typename R>
@@ -1130,7 +1133,7 @@ static int spec_threads(const PcSpecGeo& g, int n, int most) {
 // neighbouring slices and writes z), z otherwise
 template <typename R>
 static cplx<R>* spec_vhat(const qedhmc_ctx* h, cplx<R>* z, cplx<R>* tmp) {
-    return spec_fused(h) ? tmp : z;
+    return spec_fused<R>(h) ? tmp : z;
 }
 
 template <typename R>
@@ -1154,7 +1157,7 @@ template <typename R>
 static qedhmc_status launch_pcs_rest(qedhmc_ctx* h, const cplx<R>* vhat, cplx<R>* z, cplx<R>* m1,
                                      const double* stop) {
     const PcSpecGeo g = spec_geo<R>(h);
-    if (!spec_fused(h)) {
+    if (!spec_fused<R>(h)) {
         // Runs of 6 slices (a run reads 24 slices more than it writes) once
         // they give a thread to every lane of the chip, of 3 below.  P at
         // L = 66, N_tau = 660 with runs of 3 / 4 / 5 / 6: FP32 77.9 / 76.7 /
@@ -1173,7 +1176,7 @@ static qedhmc_status launch_pcs_rest(qedhmc_ctx* h, const cplx<R>* vhat, cplx<R>
     return with_spec<R>(g, [&]<int NY, int NX, bool TL>() -> qedhmc_status {
         bool tl;
         const size_t lds = spec_lds<R>(g, tl);
-        if (!spec_fused(h)) {
+        if (!spec_fused<R>(h)) {
             if (lds > 65536) QH_TRY(allow_lds((const void*)k_pcs_inv<R, NY, NX, TL>, h->max_lds));
             hipLaunchKernelGGL((k_pcs_inv<R, NY, NX, TL>), dim3(slice_grid(g.Nt)),
                                dim3(spec_threads(g, g.nk / 2, spec_max_threads<R>())), lds, h->stream, g,
@@ -1952,7 +1955,7 @@ static qedhmc_status run_graph(qedhmc_ctx* h, qedhmc_ctx::PcgGraph& gr, const qe
 // the launches a graph of the solver holds besides its length
 template <typename R>
 static int pcg_plan(const qedhmc_ctx* h, bool identity) {
-    return identity ? 0 : (use_spectral<R>(h) ? 1 : 0) | (spec_fused(h) ? 2 : 0);
+    return identity ? 0 : (use_spectral<R>(h) ? 1 : 0) | (spec_fused<R>(h) ? 2 : 0);
 }
 
 // Triples per graph of the solver whose reliable updates run inside them (an
