@@ -569,6 +569,8 @@ static qedhmc_status launch_gauge(qedhmc_batch* b, const double* theta_all) {
 // sides from the heat bath (Gaussian angles: a disordered but well-posed
 // system), 4 warm-up and 24 timed iterations of the recursion in the working
 // precision R, best of two.  The fastest shape is kept for R.
+// QEDHMC_BATCH_TILE=0 .. 3 (read at creation; tests) leaves only that shape,
+// where it fits.
 template <typename R>
 static qedhmc_status autotune(qedhmc_batch* b, const std::vector<const double*>& rhs, const std::vector<double*>& x) {
     hipEvent_t e0, e1;
@@ -578,9 +580,12 @@ static qedhmc_status autotune(qedhmc_batch* b, const std::vector<const double*>&
     int best_shape = -1;
     qedhmc_status st = QEDHMC_OK;
     float* us_out = b->tune_us[pidx<R>()];
+    const char* ef = std::getenv("QEDHMC_BATCH_TILE");
+    const int f = ef && *ef ? std::atoi(ef) : -1;
+    const int only = f >= 0 && f < 4 && shape_ok(b, f) ? f : -1;
     for (int s = 0; s < 4 && st == QEDHMC_OK; s++) {
         us_out[s] = 0.0f;
-        if (!shape_ok(b, s)) continue;
+        if (!shape_ok(b, s) || (only >= 0 && s != only)) continue;
         float t_best = 0.0f;
         for (int rep = 0; rep < 2 && st == QEDHMC_OK; rep++) {
             st = push_tab<R>(b, rhs, x, 1 << 30, false);
