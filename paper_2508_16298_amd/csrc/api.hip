@@ -466,6 +466,12 @@ qedhmc_status qedhmc_hmc_trajectory(qedhmc_t h, double* theta, uint64_t traj, in
             QH_TRY(ensure_gauge(h, th, QEDHMC_FP64));
             if (prec != QEDHMC_FP64) QH_TRY(ensure_gauge(h, th, QEDHMC_FP32));
             st = pcg_solve_impl(h, eta, X, tol, maxit, prec, &it, &rel, &nr, true);
+            if (!std::isfinite(rel) && it == 0) {
+                // X leaves no finite residual: as below
+                worst = 2;
+                max_rel = HUGE_VAL;
+                return QEDHMC_OK;
+            }
             if (!std::isfinite(rel)) rel = HUGE_VAL;
         } else {
             QH_TRY(ensure_gauge(h, th, QEDHMC_FP64));

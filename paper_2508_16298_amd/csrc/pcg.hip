@@ -2039,9 +2039,13 @@ static qedhmc_status pcg_device(qedhmc_ctx* h, const PcgBufs<R>& B, const double
     const int it = (int)rec[CR_ITERS];
     if (iters) *iters = it;
     // (a breakdown before the first update: the start's residual, 1 from zero)
-    if (true_rel)
-        *true_rel = rec[CR_NREL] == 0.0 && !warm ? 1.0 : (rec[CR_B2] > 0.0 ? std::sqrt(rec[CR_TRUE] / rec[CR_B2]) : 0.0);
-    if (n_reliable) *n_reliable = (int)rec[CR_NREL];
+    const double tr = rec[CR_TRUE], b2 = rec[CR_B2];
+    double rel = b2 > 0.0 ? std::sqrt(tr / b2) : 0.0;
+    if (warm && !(std::isfinite(tr) && std::isfinite(b2))) rel = HUGE_VAL;
+    if (!warm && rec[CR_NREL] == 0.0) rel = 1.0;
+    if (true_rel) *true_rel = rel;
+    // (a warm start that meets the target has had no update)
+    if (n_reliable) *n_reliable = warm && it == 0 && rec[CR_DONE] == 5.0 ? 0 : (int)rec[CR_NREL];
     if (rec[CR_DONE] == 5.0) return QEDHMC_OK;
     if (over) set_error("PCG did not end within " + std::to_string(max_rounds) + " rounds");
     switch ((int)rec[CR_WHY]) {
@@ -2102,12 +2106,13 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
         }
         converged = !broken && h->h_pinned[S_DONE] == 1.0;
         if (!begin || warm || converged) rel = b2 > 0.0 ? std::sqrt(h->h_pinned[S_TRUE] / b2) : 0.0;
+        if (warm && broken) rel = HUGE_VAL;
         return QEDHMC_OK;
     };
     if (small) {
         QH_TRY(launch_begin<R>(h, B, rhs, warm ? x : nullptr, tol, maxit));
         QH_TRY(check(true, true));
-        if (converged) nrel = 1;  // the start was this solve's check
+        if (converged && !warm) nrel = 1;  // the start was this solve's check
         if (!broken && !converged) QH_TRY(pcg_tail<R>(h, B, nullptr, false, true));
     } else {
         hipLaunchKernelGGL(k_pcg_start<R>, dim3(Nt), dim3(256), 0, h->stream, h->lat, B, (const cplx<double>*)rhs,
