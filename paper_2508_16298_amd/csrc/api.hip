@@ -157,7 +157,7 @@ qedhmc_status qedhmc_init_lattice(const qedhmc_params* params, void* stream, qed
     ok = ok && hipMalloc(&h->partial, ((size_t)12 * p.Nt + 4096) * sizeof(double)) == hipSuccess;
     if (ok && h->lat.ncell > 1024) {
         h->tpart_tiles = std::max(mdagm_tiled_tiles(h->lat, false), mdagm_tiled_tiles(h->lat, true));
-        ok = hipMalloc(&h->tpart, ((size_t)7 * p.Nt * h->tpart_tiles + p.Nt + 64) * sizeof(double)) == hipSuccess;
+        ok = hipMalloc(&h->tpart, ((size_t)6 * p.Nt * h->tpart_tiles + p.Nt) * sizeof(double)) == hipSuccess;
     }
     ok = ok && hipMalloc(&h->scal, 128 * sizeof(double)) == hipSuccess;
     ok = ok && hipHostMalloc(&h->h_pinned, 64 * sizeof(double), hipHostMallocDefault) == hipSuccess;

@@ -27,7 +27,9 @@
 // reads what a concurrent workgroup writes.  x takes two steps at a time, at
 // every second iteration after an update and where the recursion stops in
 // between (the launch past the last iteration always runs): alpha_{i-1} and
-// p_{i-1} are at hand there, and 16 of 112 bytes a site and iteration go.
+// p_{i-1} are at hand there, and 16 of 112 bytes a site and iteration go (FP32:
+// r, w, s, p read and r, s, w, p written 64, the phases of both directions 16, x
+// 32 every second time).
 //
 // Stop and pause: an iteration that finds gamma_i <= tol^2 |rhs|^2 turns
 // itself and all later launches into no-ops (the host reads the flag once per

@@ -107,9 +107,9 @@ __device__ __forceinline__ Tile whole_block_tile(unsigned char* buf, double* red
 }
 
 // Sum of K doubles over the threads of a group; the total is valid in the
-// group's last thread.  Every thread of the workgroup calls it (groups of 64
-// 128 and more meet at workgroup barriers; smaller groups reduce within their
-// 16, 32 or 64 lanes through DPP alone).  Fixed order.
+// group's last thread.  Every thread of the workgroup calls it (groups of 128
+// threads and more meet at workgroup barriers; groups of 16, 32 and 64 reduce
+// through DPP alone).  Fixed order.
 template <int K>
 __device__ __forceinline__ void group_sumk(double (&v)[K], const Tile& tl) {
     if (tl.G < 64) {

@@ -324,7 +324,7 @@ static constexpr int kTileMaxThreads = sizeof(R) == 8 ? 512 : 1024;
 // <r,r>, <r,u>, <w,u>, <u,s>, <p,w>, <p,s> of every (slice, tile) over the
 // tile's output cells go to part[q * Nt * ntile + tau * ntile + tile]; a
 // non-zero *stop makes the launch a no-op.
-static constexpr int kTileParts = 7;
+static constexpr int kTileParts = 6;
 
 template <typename R>
 struct TPart {
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(kTileMaxThreads<R>) void k_mdagm_tiled(TiledGeo G, 
             o[k.s0 + G.L + 1] = w[3];
         }
         if constexpr (PART) {
-            double v[kTileParts] = {0, 0, 0, 0, 0, 0, 0};
+            double v[kTileParts] = {0, 0, 0, 0, 0, 0};
             if (k.store) {
                 cplx<R> rt[4], ut[4], pt[4], st[4];
                 tile_load<R>(rt, ops.r + (size_t)tau * Vs, G, k);
@@ -447,20 +447,20 @@ __global__ __launch_bounds__(kTileMaxThreads<R>) void k_mdagm_tiled(TiledGeo G, 
             // reuse of red from one slice to the next)
             const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-            for (int q = 0; q < kTileParts - 1; q++) v[q] = wave_sum_f64(v[q]);
+            for (int q = 0; q < kTileParts; q++) v[q] = wave_sum_f64(v[q]);
             if (lane == 63)
 #pragma unroll
-                for (int q = 0; q < kTileParts - 1; q++) red[(kTileParts - 1) * wv + q] = v[q];
+                for (int q = 0; q < kTileParts; q++) red[kTileParts * wv + q] = v[q];
             __syncthreads();
             if (threadIdx.x == 0) {
-                double t[kTileParts] = {0, 0, 0, 0, 0, 0, 0};
+                double t[kTileParts] = {0, 0, 0, 0, 0, 0};
                 const int nw = (int)(blockDim.x + 63) >> 6;
                 for (int i = 0; i < nw; i++)
 #pragma unroll
-                    for (int q = 0; q < kTileParts - 1; q++) t[q] += red[(kTileParts - 1) * i + q];
+                    for (int q = 0; q < kTileParts; q++) t[q] += red[kTileParts * i + q];
                 double* dst = ops.part + (size_t)tau * ntile + tile;
 #pragma unroll
-                for (int q = 0; q < kTileParts - 1; q++) dst[(size_t)q * Nt * ntile] = t[q];
+                for (int q = 0; q < kTileParts; q++) dst[(size_t)q * Nt * ntile] = t[q];
             }
         }
 #pragma unroll

@@ -1408,9 +1408,10 @@ __device__ __forceinline__ double lane_sum(const double* __restrict__ src, int n
 // that a launch of a finished solve costs as much as one that works; those are
 // few where the updates run inside the triples.  8.5 -> 6.6 us at L = 24, N_tau
 // = 240 (FP32).
-// Large lattices: bound by the bytes, 96 a site on average in FP32 (x, FP64, is
-// read and written at every second iteration).  65 us at 104 a site at L = 66,
-// N_tau = 660 (4.6 TB/s), 58 us now; the sites past a thread's first kUpdPre
+// Large lattices: bound by the bytes, 88 a site on average in FP32 with the
+// transform, 80 without (x, FP64, is read and written at every second
+// iteration).  65 us at 104 a site at L = 66, N_tau = 660 (4.6 TB/s), 58 us now
+// (4.4 TB/s); the sites past a thread's first kUpdPre
 // are also requested kUpdPre at a time, and the launch without a transform has
 // a thread for every four sites: CG at L = 80, N_tau = 200 43.9 -> 38.9 ms.
 static constexpr int kUpdPre = 4;
@@ -1961,11 +1962,13 @@ static int pcg_plan(const qedhmc_ctx* h, bool identity) {
 // Triples per graph of the solver whose reliable updates run inside them (an
 // even count: every graph starts at launch parity 0); the host reads the
 // record of each.  The launches of the last graph past the end of a solve, and
-// of one queued behind it in vain, do nothing but load (4.8 us a triple), and
+// of one queued behind it in vain, do little but load (11 us a triple at L = 24
+// in FP32 and at L = 12 in FP64, 9 of them inside the kernels; 13 at L = 40), and
 // each graph costs about 8 us between the record and the next one's first
 // launch: 4, 6, 8, 10 measured 7.69, 7.48, 7.61, 7.37 ms per trajectory at L =
 // 24, N_tau = 240 (mixed) and 4.70, 4.57, 4.45, 4.34 ms at L = 12, N_tau = 120
-// (FP64).
+// (FP64); 6, 10, 30 a solve at L = 24 to 1e-6 1.47, 1.47, 1.63 ms, to 1e-10 2.46,
+// 2.32, 2.35 ms.
 static constexpr int kPcgTriples = 10;
 
 // The solve with every decision taken on the device: graphs of kPcgTriples
@@ -1975,8 +1978,9 @@ static constexpr int kPcgTriples = 10;
 // the host and none is wasted between a pause and its update.  Against whole
 // rounds of 12 iterations with gated update launches, and a solve for the
 // correction where a trajectory starts warm: 8.7 -> 7.4 ms per trajectory at
-// L = 24, N_tau = 240, tol 1e-10 (mixed), 4.0 -> 3.0 ms per solve at tol 1e-12.  The host keeps the next one queued behind
-// the running one and holds it back only when the residual estimates of the
+// L = 24, N_tau = 240, tol 1e-10 (mixed), 4.0 -> 3.0 ms per solve at tol 1e-12.
+// The host keeps the next one queued behind the running one and holds it back
+// only when the residual estimates of the
 // last two, extrapolated geometrically, say that the running one converges (a
 // wrong guess costs one host round trip).
 template <typename R>
@@ -2084,8 +2088,10 @@ static qedhmc_status pcg_t(qedhmc_ctx* h, const double* rhs, double* x, double t
         return pcg_device<R>(h, B, rhs, x, warm, tol, maxit, prec, iters, true_rel, n_reliable, most);
     // iterations per host round trip: the plain recursion pauses after kCap at
     // most; with the paper's preconditioner a decade, and with it a pause, takes
-    // about 9 to 30 iterations, and the launches past a pause are wasted (chunks
-    // of 51 and 12: 34.4 and 30.1 ms per solve at L = 66, N_tau = 600, tol 1e-12)
+    // about 9 to 30 iterations, and the launches past a pause are wasted.  Chunks
+    // of 51 / 24 / 12, ms per solve: L = 46, N_tau = 200, tol 1e-8 5.55 / 3.78 /
+    // 3.12, L = 66, N_tau = 200, 1e-4 3.43 / 2.76 / 2.58, L = 66, N_tau = 660,
+    // 1e-12 31.5 / 29.0 / 28.6, L = 80, N_tau = 200, 1e-12 18.0 / 16.0 / 15.8
     // (small: every iteration by itself, its matvec carrying out an update)
     const int chunk = small ? 1 : (mixed ? (identity ? kCap + 1 : 12) : 64);
     int kpar = 0, nrel = 0, it = 0, stalled = 0, last_it = -1;

@@ -327,27 +327,24 @@ __global__ void k_se_fold(int Nt, int Vs, int nrp, int nchunk, const int* __rest
     S[k] = s;
 }
 
-// DFT along tau of KT spatial columns of one vector, staged in LDS:
-// out(kt, c) = sum_tau in(tau, c) w^{tau kt}.
-__global__ __launch_bounds__(kBS) void k_se_t(int Nt, int Vs, int64_t N, int KT, const cplx<double>* __restrict__ in,
-                                              const cplx<double>* __restrict__ tw, int conj,
-                                              cplx<double>* __restrict__ out) {
+// Inverse DFT along tau of KT spatial columns, staged in LDS:
+// out(kt, c) = sum_tau in(tau, c) conj(tw)^{tau kt}.
+__global__ __launch_bounds__(kBS) void k_se_t(int Nt, int Vs, int KT, const cplx<double>* __restrict__ in,
+                                              const cplx<double>* __restrict__ tw, cplx<double>* __restrict__ out) {
     extern __shared__ unsigned char smem[];
     cplx<double>* col = reinterpret_cast<cplx<double>*>(smem);  // [Nt][KT]
     cplx<double>* w = col + (size_t)Nt * KT;
-    const int c0 = blockIdx.x * KT, v = blockIdx.y;
+    const int c0 = blockIdx.x * KT;
     const int nc = min(KT, Vs - c0);
-    const cplx<double>* src = in + (int64_t)v * N;
     for (int k = threadIdx.x; k < Nt; k += blockDim.x) {
         const cplx<double> t = tw[k];
-        w[k] = mk<double>(t.re, conj ? -t.im : t.im);
+        w[k] = mk<double>(t.re, -t.im);
     }
     for (int e = threadIdx.x; e < Nt * KT; e += blockDim.x) {
         const int tau = e / KT, c = e - tau * KT;
-        col[e] = c < nc ? src[(int64_t)tau * Vs + c0 + c] : mk<double>(0.0, 0.0);
+        col[e] = c < nc ? in[(int64_t)tau * Vs + c0 + c] : mk<double>(0.0, 0.0);
     }
     __syncthreads();
-    cplx<double>* dst = out + (int64_t)v * N;
     for (int e = threadIdx.x; e < Nt * KT; e += blockDim.x) {
         const int kt = e / KT, c = e - kt * KT;
         if (c >= nc) continue;
@@ -360,7 +357,7 @@ __global__ __launch_bounds__(kBS) void k_se_t(int Nt, int Vs, int64_t N, int KT,
             idx += kt;
             if (idx >= Nt) idx -= Nt;
         }
-        dst[(int64_t)kt * Vs + c0 + c] = acc;
+        out[(int64_t)kt * Vs + c0 + c] = acc;
     }
 }
 
@@ -675,8 +672,8 @@ qedhmc_status qedhmc_se_spin_correlator(qedhmc_se_t se, const double* xi_all, co
                        se->S);
     // T(Delta) = sum_k S_k e^{+i k.Delta}
     QH_TRY(spatial.template operator()<false>(0, 1, se->S, se->S + N));
-    hipLaunchKernelGGL(k_se_t, dim3((Vs + kTauTile - 1) / kTauTile, 1), dim3(kBS), t_lds(Nt), se->stream, Nt, Vs, N,
-                       kTauTile, se->S + N, se->twT, 1, se->T);
+    hipLaunchKernelGGL(k_se_t, dim3((Vs + kTauTile - 1) / kTauTile), dim3(kBS), t_lds(Nt), se->stream, Nt, Vs, kTauTile,
+                       se->S + N, se->twT, se->T);
     QH_HIP(hipGetLastError());
     const double scale = 1.0 / ((double)n * (double)(n - 1) * (double)N * (double)N);
     hipLaunchKernelGGL(k_se_finish, dim3(eg), dim3(256), 0, se->stream, N, scale, se->n_part, se->part,
