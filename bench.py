@@ -22,9 +22,10 @@ the method's own solves); dH, decisions, iterations and seconds side by side.
 Prints one JSON line.  The roofline block is for the dominant kernel of the
 timed path, by default the fused CG iteration k_cg_iter (one launch per
 iteration: recurrences, x update, M^dag M, inner products).  Its algorithmic
-bytes per site are, in the mixed path, r, w, s, p read (4 x 8 B), two FP32
-angles (8 B), x read and written at every second iteration (16 B on average,
-FP64) and r, s, p, w written (4 x 8 B): 88 B per site (160 B in FP64).  Its duration comes from event
+bytes per site are, in the mixed path, r, w, s, p read (4 x 8 B), the phases
+of both directions (2 x 8 B), x read and written at every second iteration (16 B
+on average, FP64) and r, s, p, w written (4 x 8 B): 96 B per site (176 B in
+FP64).  Its duration comes from event
 pairs around every 8th graph replay of 51 back-to-back iteration launches (a
 replay holds nothing else) over the timed region; `traffic` is the
 counter-measured HBM bytes per launch.  The metric's M^dag M bandwidth is
@@ -278,7 +279,7 @@ def run_batched(a):
     one step = one trajectory of every chain; value = sites x trajectories
     per second.  The roofline block is the batched CG iteration k_b_cg_iter at the
     autotuned tile shape, timed by the autotuner with events around 24
-    back-to-back launches with every chain active (88 B per site of every
+    back-to-back launches with every chain active (96 B per site of every
     chain, as k_cg_iter)."""
     import numpy as np
     import torch
@@ -305,7 +306,7 @@ def run_batched(a):
     mc, nt, nb, us = b.tile("fp32" if prec != "fp64" else "fp64")
     shape_idx = {(1, 2): 0, (2, 2): 1, (1, 1): 2, (2, 1): 3}[(mc, nb)]
     N = sum(L * L * Nt for L, Nt in sizes)
-    it_bytes = (88 if prec != "fp64" else 160) * N
+    it_bytes = (96 if prec != "fp64" else 176) * N
     it_us = float(us[shape_idx])
     achieved = it_bytes / (it_us * 1e-6) / 1e9
     s_per = elapsed / a.steps
@@ -343,7 +344,7 @@ def run_se(a):
     precision, true residual 1e-8, one gauge field for all 40 right-hand
     sides) and the FFT-averaged spin correlator over the 780 probe pairs, at
     L=24, Nt=240 on the angles of the trajectory workload.  value = seconds
-    per measurement.  The roofline block is the solve phase: 88 B per site
+    per measurement.  The roofline block is the solve phase: 96 B per site
     and right-hand side for every batched CG iteration (as k_cg_iter), over
     the solve's measured time (reliable updates and launch gaps included:
     a lower bound on the kernel's rate)."""
@@ -387,7 +388,7 @@ def run_se(a):
     iters = np.array([r[1] for r in rows])
     # every launch of the batched iteration covers the right-hand sides still running
     it_sum = float(iters.sum(axis=1).mean())
-    achieved = (88 if prec != "fp64" else 160) * N * it_sum / t_solve / 1e9
+    achieved = (96 if prec != "fp64" else 176) * N * it_sum / t_solve / 1e9
     npairs = n_rv * (n_rv - 1) // 2
     # one 3-D DFT by direct sums along each axis, a quarter of their products
     # left by pairing the points k and n - k
@@ -414,7 +415,7 @@ def run_se(a):
                        "dft_count": 2 * npairs + 1, "tflops": corr_tflops, "peak_fp64_tflops": 78.6},
         "roofline": {"bound": "hbm", "kernel": "k_b_cg_iter (multi-RHS CG iteration, 40 right-hand sides)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": None, "alg_bytes_per_launch": (88 if prec != "fp64" else 160) * N * n_rv,
+                     "traffic": None, "alg_bytes_per_launch": (96 if prec != "fp64" else 176) * N * n_rv,
                      "timing": "solve phase between events (includes updates and launch gaps)"},
     }
     se.close()
@@ -915,7 +916,7 @@ def main():
                  f"tau sum + inverse 2D DFT; 200 applications of P back to back)")
     else:
         kcls = Q.K_CG_FP32 if prec != "fp64" else Q.K_CG_FP64
-        work, unit, bound, peak = (88 if prec != "fp64" else 160) * N, "GB/s", "hbm", HBM_PEAK_GBS
+        work, unit, bound, peak = (96 if prec != "fp64" else 176) * N, "GB/s", "hbm", HBM_PEAK_GBS
         kname = f"k_cg_iter<{'float' if prec != 'fp64' else 'double'}> (one fused CG iteration)"
     n_k, ms_k = pc_block if pc == "paper" else prof[kcls]
     avg_ms = ms_k / max(n_k, 1)

@@ -554,9 +554,9 @@ static qedhmc_status mdagm_theta_t(qedhmc_ctx* h, const double* theta, const voi
 // L = 62 46.4 -> 51.9; FP64 L = 24 12.8 -> 10.3, L = 44 32.1 -> 28.2, L = 48
 // (which spills at its 1024 threads) 70.4 -> 72.2.  Below L = 24 a call is bound
 // by the host's launches, one instead of two.  All of these are calls in a row;
-// a single call on vectors not touched before, which waits for its loads and
-// then for the chain of sines and exchanges, takes as long in either form (L = 6
-// FP64 1.03 times faster, L = 24 FP32 0.96).
+// one call that is waited for takes 27.4 -> 23.7 us at L = 6 (FP64) and 29.3 ->
+// 25.4 us at L = 24 (FP32), the first on vectors not touched before as long in
+// either form (30 to 43 us, of which its loads and sines are a chain).
 static int theta_cells(qedhmc_precision prec) { return prec == QEDHMC_FP64 ? 512 : 576; }
 
 qedhmc_status launch_mdagm_theta(qedhmc_ctx* h, qedhmc_precision prec, const double* theta, const void* in, void* out) {
