@@ -1087,12 +1087,30 @@ static bool use_spectral(const qedhmc_ctx* h) {
 // L = 26 26.8 / 22.8, L = 40 50.9 / 46.5, L = 58 132 / 96.5.  A solve to 1e-8:
 // mixed L = 48, N_tau = 200 4.09 / 4.14 ms, L = 50 3.75 / 3.66, L = 58 4.79 /
 // 4.53; FP64 L = 24 2.25 / 2.44, L = 26, N_tau = 260 2.13 / 1.88, L = 40, N_tau =
-// 200 3.62 / 3.46.  QEDHMC_PC_FUSE=0|1 (read per call) forces either form.
+// 200 3.62 / 3.46.
+// The number of slices counts too.  The fused form is a workgroup a slice.  FP64
+// in one round of one per compute unit: L = 26, N_tau = 100 17.2 / 20.4 us, L = 32,
+// N_tau = 64 and 240 19.8 / 21.7 and 22.7 / 25.1, L = 36, N_tau = 64 and 240 24.6 /
+// 23.6 and 26.3 / 27.3, L = 40, N_tau = 240 31.3 / 29.4 (solves to 1e-10, L = 28,
+// N_tau = 64 and 240 1.28 / 1.32 and 2.85 / 3.09 ms).  Where that round is at least
+// two thirds full and the separate sum's workgroups (256 threads of more than 256
+// registers, three slices a thread: one to a unit) need a second one: L = 44,
+// N_tau = 240 33.7 / 37.9 us (6.18 / 6.63 ms a solve), L = 58 52.0 / 54.5 (10.7 /
+// 10.8 ms); less full: L = 54, N_tau = 160 43.3 / 40.9.  FP32 with too few slices
+// for the chip, which the separate sum fills: L = 48, N_tau = 13, 64, 100, 240 20.3 /
+// 19.9, 21.0 / 20.8, 21.0 / 21.5, 22.4 / 24.2 us (mixed solves to 1e-8 1.76 / 1.58,
+// 2.38 / 2.23, 2.91 / 2.80, 4.86 / 4.83 ms), L = 44, N_tau = 13 18.5 / 19.8 us;
+// L = 58, N_tau = 240 28.5 / 30.3 us, but 5.13 / 4.98 ms.
+// QEDHMC_PC_FUSE=0|1 (read per call) forces either form.
 template <typename R>
 static bool spec_fused(const qedhmc_ctx* h) {
     const char* ef = std::getenv("QEDHMC_PC_FUSE");
     if (ef && *ef) return std::atoi(ef) != 0;
-    return h->lat.L <= (sizeof(R) == 8 ? 24 : 48);
+    const int L = h->lat.L, Nt = h->lat.Nt, cu = h->n_cu;
+    if (sizeof(R) == 4) return L <= 44 || (L <= 48 && Nt >= 100);
+    if (L <= 24 || Nt > cu) return L <= 24;
+    const bool full = 3 * Nt >= 2 * cu, second = L * (L / 2) * ((Nt + 2) / 3) > 256 * cu;
+    return L <= 32 || (full && (L <= 36 || (second && L <= 58)));
 }
 
 template <typename R>
